@@ -290,7 +290,7 @@ lbm_status lbm_run_status(lbm_ctx *ctx, int32_t *status);
  * (k >= 1; 0 disables graphs and launches every kernel directly).  Default 16. */
 lbm_status lbm_set_graph_steps(lbm_ctx *ctx, int32_t k);
 
-/* Tile shape of the step kernels: tx in {32, 64, 128, 256}, ty in {1, 2, 4, 8},
+/* Tile shape of the single-step kernels (see lbm_set_fused): tx in {32, 64, 128, 256}, ty in {1, 2, 4, 8},
  * 64 <= tx*ty <= 512 threads.  Default 64 x 4.  Rebuilds the work list and drops any
  * captured graph; synchronises. */
 lbm_status lbm_set_tile(lbm_ctx *ctx, int32_t tx, int32_t ty);
@@ -303,16 +303,20 @@ lbm_status lbm_set_tile(lbm_ctx *ctx, int32_t tx, int32_t ty);
  * to the second population buffer of the workspace, in the same layout, so
  * the populations cross HBM once each way per step instead of being read
  * twice (bf16 storage: the writer densities of the previous step are staged
- * with the halo, and the tile writes its own for the next step).  Every
- * schedule gives the same bits.  Default: 2.  LBM_EINVAL for other values.
- * Drops any captured graph; synchronises. */
+ * with the halo, and the tile writes its own for the next step).  With rows
+ * > 0, FP64 or FP32 storage, no multi-range run and every run's populations
+ * below 4 GiB, lbm_step advances two or four steps per launch from an even
+ * step count while at least as many remain (tiles of the library's choice,
+ * the intermediate states in LDS); tx, ty and rows then shape the remaining
+ * single steps.  Every schedule gives the same bits.  Default: 2.
+ * LBM_EINVAL for other values.  Drops any captured graph; synchronises. */
 lbm_status lbm_set_fused(lbm_ctx *ctx, int32_t rows);
 
 /* Tile autotuner: times `steps` (>= 2) steps of this context under each
  * candidate schedule and tile shape (two-kernel 64x4, 128x2, 32x8, 256x1, 64x2,
  * 32x4; fused, as tx x ty threads / rows: 64x4 / 1, 64x4 / 2, 64x4 / 4,
  * 128x2 / 2, 128x2 / 4, 256x1 / 4, 32x8 / 2, 64x2 / 4, 256x2 / 4, 128x4 / 2),
- * graph replay included, and keeps the fastest.  The
+ * graph replay included, one step per launch, and keeps the fastest.  The
  * candidates compute the same step, so the timed steps are real work: the
  * state advances by about 16 * (steps + 2 * graph steps).  The chosen shape is
  * written to tx, ty, fused (each may be NULL).  Synchronises. */
@@ -328,8 +332,8 @@ lbm_status lbm_set_xcd_order(lbm_ctx *ctx, int32_t on);
 /* Advance n >= 1 steps with every kernel launched on its own (no graph), each
  * launch carrying its own start/stop HIP events on the context's stream, and
  * return the mean duration in milliseconds of the density/psi kernel and of
- * the collide-stream kernel (with the fused schedule: 0 and the fused step
- * kernel).  Synchronises.  The state advances exactly as with lbm_step(ctx, n). */
+ * the collide-stream kernel per step (with the fused schedule: 0 and the
+ * launches' total over the n steps, see lbm_set_fused).  Synchronises.  The state advances exactly as with lbm_step(ctx, n). */
 lbm_status lbm_time_kernels(lbm_ctx *ctx, int64_t n, double *psi_ms, double *collide_ms);
 
 /* Plain device copy of `bytes` bytes (16-byte multiple, 16-byte aligned

@@ -40,6 +40,8 @@ size_t align256(size_t x) { return (x + 255) & ~size_t(255); }
 size_t pop_bytes(int prec) { return prec == LBM_FP64 ? 8 : (prec == LBM_FP32 ? 4 : 2); }
 size_t psi_bytes(int prec) { return prec == LBM_FP64 ? 8 : 4; }
 
+int kernel_precision(int p) { return p == LBM_FP64 ? lbm::PREC_FP64 : (p == LBM_FP32 ? lbm::PREC_FP32 : lbm::PREC_BF16); }
+
 bool is_finite(double v) { return std::isfinite(v); }
 
 const int kTileX[] = {32, 64, 128, 256};
@@ -79,10 +81,11 @@ int64_t dstride_of(int64_t nodes, int prec)
 }
 
 struct Layout {
-    size_t f = 0, f2 = 0, psi = 0, r0 = 0, r1 = 0, seed = 0, runs = 0, tiles = 0, ftiles = 0, status = 0,
+    size_t f = 0, f2 = 0, psi = 0, r0 = 0, r1 = 0, seed = 0, runs = 0, tiles = 0, ftiles = 0, mtiles = 0, status = 0,
            partial = 0, dout = 0, regions = 0, staging = 0;
     size_t total = 0;
     int64_t max_tiles = 0;
+    int64_t max_mtiles = 0;  // tiles of the multi-step kernel, over its variants
     int64_t pop_elems = 0;   // population elements of all runs, 9 x dstride each
     int64_t total_nodes = 0; // nodes of all runs including the row padding (pitch x ny each)
     int64_t max_nodes = 0;   // the same for the largest run (sizes the host staging area)
@@ -104,6 +107,12 @@ Layout make_layout(int nruns, const lbm_run_desc *runs, int prec)
             for (int i = 0; i < nruns; ++i) t += tiles_of(runs[i].grid, tx, ty);
             L.max_tiles = std::max(L.max_tiles, t);
         }
+    lbm::MultiShape ms;
+    for (int v = 0; lbm::multi_shape(kernel_precision(prec), v, ms); ++v) {
+        int64_t t = 0;
+        for (int i = 0; i < nruns && nruns > 1; ++i) t += lbm::multi_tiles(ms, runs[i].grid.nx, runs[i].grid.ny);
+        L.max_mtiles = std::max(L.max_mtiles, t);
+    }
     size_t off = 0;
     L.f = off;
     off = align256(off + pop_bytes(prec) * (size_t)L.pop_elems);
@@ -127,6 +136,8 @@ Layout make_layout(int nruns, const lbm_run_desc *runs, int prec)
     off = align256(off + sizeof(lbm::Tile) * (size_t)L.max_tiles);
     L.ftiles = off; // tiles of tx x (R ty) nodes: never more than of tx x ty
     off = align256(off + sizeof(lbm::Tile) * (size_t)L.max_tiles);
+    L.mtiles = off;
+    off = align256(off + sizeof(lbm::Tile) * (size_t)L.max_mtiles);
     L.status = off;
     off = align256(off + sizeof(int32_t) * nruns);
     L.partial = off;
@@ -182,8 +193,6 @@ lbm_status validate_run(const lbm_run_desc *r)
 
 bool valid_precision(int p) { return p == LBM_FP64 || p == LBM_FP32 || p == LBM_FP32_BF16STORE; }
 
-int kernel_precision(int p) { return p == LBM_FP64 ? lbm::PREC_FP64 : (p == LBM_FP32 ? lbm::PREC_FP32 : lbm::PREC_BF16); }
-
 } // namespace
 
 struct lbm_ctx {
@@ -195,6 +204,10 @@ struct lbm_ctx {
     std::vector<int> ref_set;       // FP32: 1 once lbm_run_set_reference_density chose the run's base
     std::vector<lbm::Tile> tiles;   // tx x ty tiles of every run (two-kernel step and diagnostics)
     std::vector<lbm::Tile> ftiles;  // tx x (fused ty) tiles of every run (fused step)
+    std::vector<lbm::Tile> mtiles;  // tiles of the multi-step kernel
+    int multi = -1;                 // its variant; -1: none (single steps only)
+    lbm::MultiShape mshape{0, 0, 0};
+    bool single_steps = false;      // set while the autotuner times the single-step shapes
     Layout L;
     unsigned char *ws = nullptr;
     bool own_ws = false;
@@ -208,8 +221,8 @@ struct lbm_ctx {
                            // (2 at creation)
     int halo = 1;          // psi halo of the collide tile: 2 once a run uses the multi-range force
     int cur = 0;           // population buffer holding the current state (0: L.f, 1: L.f2)
-    int graph_cur = 0;     // buffer the captured graph starts from
-    hipGraphExec_t graph = nullptr;
+    hipGraphExec_t graph[2] = {nullptr, nullptr}; // 2k steps from population buffer 0 / 1
+    int graph_swap = 0;    // 1: a replay ends on the other buffer than it started from
     bool graph_failed = false;
 
     template <typename T> T *at(size_t off) { return reinterpret_cast<T *>(ws + off); }
@@ -232,6 +245,12 @@ struct lbm_ctx {
         a.fused = fused;
         a.ftiles = at<lbm::Tile>(L.ftiles);
         a.nftiles = (int)ftiles.size();
+        a.mtiles = at<lbm::Tile>(L.mtiles);
+        a.nmtiles = (int)mtiles.size();
+        if (nruns == 1 && multi >= 0) {
+            a.mntx = (desc[0].grid.nx + mshape.tx - 1) / mshape.tx;
+            a.nmtiles = (int)lbm::multi_tiles(mshape, desc[0].grid.nx, desc[0].grid.ny);
+        }
         if (precision == LBM_FP32_BF16STORE) {
             a.r0 = at<float>(L.r0);
             a.r1 = at<float>(L.r1);
@@ -246,11 +265,25 @@ struct lbm_ctx {
 
 namespace {
 
+// Variant of the multi-step kernel, -1 for single steps only: it needs the
+// second population buffer (fused schedule), the single-range force, FP64 or
+// FP32 storage, and run blocks that a 32-bit byte offset spans.
+int multi_variant(const lbm_ctx *c)
+{
+    if (!c->fused || c->single_steps || c->halo != 1 || c->precision == LBM_FP32_BF16STORE) return -1;
+    for (const lbm::RunDev &r : c->rdev)
+        if ((uint64_t)r.dstride * 9 * pop_bytes(c->precision) >= (uint64_t)1 << 32) return -1;
+    return lbm::pick_multi(kernel_precision(c->precision), c->rdev.data(), c->nruns);
+}
+
 // Work lists: tiles of every run in row-major order, runs one after another.
 void build_tiles(lbm_ctx *c)
 {
     c->tiles.clear();
     c->ftiles.clear();
+    c->mtiles.clear();
+    c->multi = multi_variant(c);
+    if (c->multi >= 0) lbm::multi_shape(kernel_precision(c->precision), c->multi, c->mshape);
     const int fty = c->ty * std::max(c->fused, 1);
     for (int r = 0; r < c->nruns; ++r) {
         const lbm_grid &g = c->desc[r].grid;
@@ -260,6 +293,10 @@ void build_tiles(lbm_ctx *c)
         c->rdev[r].tile_count = (int32_t)c->tiles.size() - c->rdev[r].tile_begin;
         for (int y0 = 0; y0 < g.ny; y0 += fty)
             for (int x0 = 0; x0 < g.nx; x0 += c->tx) c->ftiles.push_back(lbm::Tile{r, x0, y0, 0});
+        // (the tiles of a single run follow from the workgroup's index)
+        if (c->multi >= 0 && c->nruns > 1)
+            for (int y0 = 0; y0 < g.ny; y0 += c->mshape.ty)
+                for (int x0 = 0; x0 < g.nx; x0 += c->mshape.tx) c->mtiles.push_back(lbm::Tile{r, x0, y0, 0});
     }
 }
 
@@ -272,6 +309,9 @@ lbm_status upload_tables(lbm_ctx *c)
                            hipMemcpyHostToDevice, c->stream));
     LBM_HIP(hipMemcpyAsync(c->ws + c->L.ftiles, c->ftiles.data(), sizeof(lbm::Tile) * c->ftiles.size(),
                            hipMemcpyHostToDevice, c->stream));
+    if (!c->mtiles.empty())
+        LBM_HIP(hipMemcpyAsync(c->ws + c->L.mtiles, c->mtiles.data(), sizeof(lbm::Tile) * c->mtiles.size(),
+                               hipMemcpyHostToDevice, c->stream));
     LBM_HIP(hipStreamSynchronize(c->stream));
     return LBM_OK;
 }
@@ -288,10 +328,11 @@ lbm_status upload_run(lbm_ctx *c, int run)
 
 void drop_graph(lbm_ctx *c)
 {
-    if (c->graph) {
-        (void)hipGraphExecDestroy(c->graph);
-        c->graph = nullptr;
-    }
+    for (hipGraphExec_t &g : c->graph)
+        if (g) {
+            (void)hipGraphExecDestroy(g);
+            g = nullptr;
+        }
 }
 
 lbm::RunDev make_rundev(const lbm_run_desc &d)
@@ -387,28 +428,37 @@ lbm_status read_status(lbm_ctx *c, std::vector<int32_t> &st)
     return LBM_OK;
 }
 
-// After a fused step the state lives in the other buffer.
-void swap_buffers(lbm_ctx *c, lbm::StepArgs &a)
+// One launch: the steps of the multi-step kernel from an even step count when
+// at least that many remain, else one step.  A fused or multi-step launch
+// leaves the state in the other buffer (swapped in `a`); `taken` receives the
+// number of steps.
+hipError_t launch_some(const lbm_ctx *c, lbm::StepArgs &a, int parity, int64_t left, int64_t *taken)
 {
-    std::swap(a.f, a.f_alt);
-    c->cur ^= 1;
+    const int prec = kernel_precision(c->precision);
+    const bool multi = c->multi >= 0 && parity == 0 && left >= c->mshape.steps;
+    const hipError_t e = multi      ? lbm::launch_multi(prec, c->multi, a)
+                         : c->fused ? lbm::launch_fused(prec, a, parity)
+                                    : lbm::launch_step(prec, a, parity);
+    *taken = multi ? c->mshape.steps : 1;
+    if (c->fused) std::swap(a.f, a.f_alt);
+    return e;
 }
 
 lbm_status step_eager(lbm_ctx *c, int64_t n)
 {
-    const int prec = kernel_precision(c->precision);
     lbm::StepArgs a = c->step_args();
-    for (int64_t i = 0; i < n; ++i) {
-        LBM_HIP(lbm::launch_step(prec, a, c->parity()));
-        ++c->steps;
-        if (c->fused) swap_buffers(c, a);
+    while (n > 0) {
+        int64_t taken = 0;
+        LBM_HIP(launch_some(c, a, c->parity(), n, &taken));
+        c->steps += taken;
+        n -= taken;
+        if (c->fused) c->cur ^= 1;
     }
     return LBM_OK;
 }
 
 lbm_status build_graph(lbm_ctx *c)
 {
-    const int prec = kernel_precision(c->precision);
     lbm::StepArgs a = c->step_args();
     hipGraph_t g = nullptr;
     if (hipStreamBeginCapture(c->stream, hipStreamCaptureModeRelaxed) != hipSuccess) {
@@ -416,14 +466,12 @@ lbm_status build_graph(lbm_ctx *c)
         c->graph_failed = true;
         return LBM_OK;
     }
-    // 2k steps from an even step count; fused steps alternate the buffers
-    // and end on the one they started from
+    // 2k steps from an even step count on the buffer of the current state
     hipError_t e = hipSuccess;
-    for (int i = 0; i < 2 * c->graph_k && e == hipSuccess; ++i) {
-        e = lbm::launch_step(prec, a, i & 1);
-        if (c->fused) std::swap(a.f, a.f_alt);
-    }
-    c->graph_cur = c->cur;
+    for (int64_t i = 0, taken = 0; i < 2 * (int64_t)c->graph_k && e == hipSuccess; i += taken)
+        e = launch_some(c, a, (int)(i & 1), 2 * (int64_t)c->graph_k - i, &taken);
+    c->graph_swap = a.f != c->fbuf(c->cur);
+    hipGraphExec_t &exec = c->graph[c->cur];
     hipError_t e2 = hipStreamEndCapture(c->stream, &g);
     if (e != hipSuccess || e2 != hipSuccess || !g) {
         if (g) (void)hipGraphDestroy(g);
@@ -431,10 +479,10 @@ lbm_status build_graph(lbm_ctx *c)
         c->graph_failed = true;
         return LBM_OK;
     }
-    hipError_t e3 = hipGraphInstantiate(&c->graph, g, nullptr, nullptr, 0);
+    hipError_t e3 = hipGraphInstantiate(&exec, g, nullptr, nullptr, 0);
     (void)hipGraphDestroy(g);
     if (e3 != hipSuccess) {
-        c->graph = nullptr;
+        exec = nullptr;
         (void)hipGetLastError();
         c->graph_failed = true;
     }
@@ -660,17 +708,15 @@ lbm_status lbm_step(lbm_ctx *ctx, int64_t n)
             --n;
             if (s != LBM_OK) return s;
         }
-        if (ctx->graph && ctx->graph_cur != ctx->cur) drop_graph(ctx); // captured from the other buffer
-        if (!ctx->graph) {
-            s = build_graph(ctx);
-            if (s != LBM_OK) return s;
-        }
-        if (ctx->graph) {
-            while (n >= block) {
-                LBM_HIP(hipGraphLaunch(ctx->graph, ctx->stream));
-                ctx->steps += block;
-                n -= block;
+        while (n >= block && !ctx->graph_failed) {
+            if (!ctx->graph[ctx->cur]) {
+                if ((s = build_graph(ctx)) != LBM_OK) return s;
+                continue;
             }
+            LBM_HIP(hipGraphLaunch(ctx->graph[ctx->cur], ctx->stream));
+            ctx->cur ^= ctx->graph_swap;
+            ctx->steps += block;
+            n -= block;
         }
     }
     return step_eager(ctx, n);
@@ -843,8 +889,12 @@ lbm_status lbm_run_set_multirange(lbm_ctx *ctx, int32_t run, double G1, double G
     int halo = 1;
     for (int i = 0; i < ctx->nruns; ++i)
         if (ctx->rdev[i].pd.G2 != 0.0) halo = 2;
-    if (halo != ctx->halo) drop_graph(ctx); // the captured launches carry the tile halo
-    ctx->halo = halo;
+    if (halo != ctx->halo) {
+        drop_graph(ctx); // the captured launches carry the tile halo
+        ctx->halo = halo;
+        build_tiles(ctx);
+        if ((s = upload_tables(ctx)) != LBM_OK) return s;
+    }
     if ((s = upload_run(ctx, run)) != LBM_OK) return s;
     LBM_HIP(hipStreamSynchronize(ctx->stream));
     return LBM_OK;
@@ -1101,16 +1151,19 @@ lbm_status lbm_time_kernels(lbm_ctx *ctx, int64_t n, double *psi_ms, double *col
     double tp = 0.0, tc = 0.0;
     if (rc == LBM_OK) {
         hipError_t e = hipSuccess;
-        for (int64_t i = 0; i < n && e == hipSuccess; ++i) {
+        int64_t launches = 0;
+        for (int64_t left = n; left > 0 && e == hipSuccess; ++launches) {
+            const int64_t i = launches;
             const int par = ctx->parity();
             lbm::StepArgs a = ctx->step_args();
+            int64_t taken = 1;
             if (ctx->fused) {
-                // one kernel per step: the psi pair brackets an empty interval
+                // one kernel per launch: the psi pair brackets an empty interval
                 e = hipEventRecord(ev[4 * i], ctx->stream);
                 if (e == hipSuccess) e = hipEventRecord(ev[4 * i + 1], ctx->stream);
                 a.ev_start = ev[4 * i + 2];
                 a.ev_stop = ev[4 * i + 3];
-                if (e == hipSuccess) e = lbm::launch_fused(prec, a, par);
+                if (e == hipSuccess) e = launch_some(ctx, a, par, left, &taken);
                 if (e == hipSuccess) ctx->cur ^= 1;
             } else {
                 a.ev_start = ev[4 * i];
@@ -1120,10 +1173,11 @@ lbm_status lbm_time_kernels(lbm_ctx *ctx, int64_t n, double *psi_ms, double *col
                 a.ev_stop = ev[4 * i + 3];
                 if (e == hipSuccess) e = lbm::launch_collide(prec, a, par);
             }
-            if (e == hipSuccess) ++ctx->steps;
+            if (e == hipSuccess) ctx->steps += taken;
+            left -= taken;
         }
         if (e == hipSuccess) e = hipStreamSynchronize(ctx->stream);
-        for (int64_t i = 0; i < n && e == hipSuccess; ++i) {
+        for (int64_t i = 0; i < launches && e == hipSuccess; ++i) {
             float a1 = 0.f, a2 = 0.f;
             e = hipEventElapsedTime(&a1, ev[4 * i], ev[4 * i + 1]);
             if (e == hipSuccess) e = hipEventElapsedTime(&a2, ev[4 * i + 2], ev[4 * i + 3]);
@@ -1177,6 +1231,8 @@ lbm_status lbm_autotune(lbm_ctx *ctx, int32_t steps, int32_t *tx, int32_t *ty, i
     Cand pick = {ctx->tx, ctx->ty, ctx->fused};
     lbm_status rc = LBM_OK;
     const int64_t n = steps + (steps & 1);
+    // the shapes are those of the single steps; lbm_set_fused below restores the multi-step kernel
+    ctx->single_steps = true;
     for (const Cand &c : cands) {
         if ((rc = lbm_set_tile(ctx, c.tx, c.ty)) != LBM_OK) break;
         if ((rc = lbm_set_fused(ctx, c.fused)) != LBM_OK) break;
@@ -1199,7 +1255,13 @@ lbm_status lbm_autotune(lbm_ctx *ctx, int32_t steps, int32_t *tx, int32_t *ty, i
     }
     (void)hipEventDestroy(e0);
     (void)hipEventDestroy(e1);
-    if (rc != LBM_OK) return rc;
+    ctx->single_steps = false;
+    if (rc != LBM_OK) {
+        // keep the failure's message; the tables go back to the multi-step kernel
+        const std::string msg = g_error;
+        (void)lbm_set_fused(ctx, ctx->fused);
+        return fail(rc, msg);
+    }
     if ((rc = lbm_set_tile(ctx, pick.tx, pick.ty)) != LBM_OK) return rc;
     if ((rc = lbm_set_fused(ctx, pick.fused)) != LBM_OK) return rc;
     if (tx) *tx = pick.tx;

@@ -194,41 +194,45 @@ template <typename C> __device__ __forceinline__ C div_const(C x, double d)
 
 // ------------------------------------------------------------------ EOS
 // psi(rho) of the three pseudopotential forms; returns false where psi is not
-// real (rho <= 0, eta >= 1, or p_EOS > rho / 3 with G < 0).
+// real (rho <= 0, eta >= 1, or p_EOS > rho / 3 with G < 0; psi is then
+// unspecified).  The EOS kind is uniform over a launch's workgroup (a scalar
+// branch); the domain tests are combined at the end, so no lane branches.
 template <typename C>
-__device__ __forceinline__ bool eval_psi(const RunDev &r, C rho, C &psi)
+__device__ __forceinline__ bool eval_psi(const RunPar<C> &k, int eos_kind, C rho, C &psi)
 {
-    const RunPar<C> &k = r.template par<C>();
-    if (!(rho > C(0))) return false;
-    if (r.eos_kind == EOS_EXP) {
+    bool ok = rho > C(0);
+    if (eos_kind == EOS_EXP) {
         psi = k.eos[0] * exp(-k.eos[1] / rho);
-        return true;
+        return ok;
     }
     C p;
-    if (r.eos_kind == EOS_CS) {
+    if (eos_kind == EOS_CS) {
         const C a = k.eos[0], RT = k.RT;
         const C eta = k.eta_scale * rho;
-        if (!(eta < C(1))) return false;
+        ok &= eta < C(1);
         const C om = C(1) - eta;
         p = rho * RT * (C(1) + eta * (C(1) + eta * (C(1) - eta))) * recip<C>(om * om * om) - a * rho * rho;
     } else {
         const C thV = k.eos[0], thM = k.eos[1], thL = k.eos[2];
         const C r1 = k.eos[3], r2 = k.eos[4];
-        if (rho <= r1)
-            p = rho * thV;
-        else if (rho < r2)
-            p = r1 * thV + (rho - r1) * thM;
-        else
-            p = r1 * thV + (r2 - r1) * thM + (rho - r2) * thL;
+        const C pv = rho * thV;
+        const C pm = r1 * thV + (rho - r1) * thM;
+        const C pl = r1 * thV + (r2 - r1) * thM + (rho - r2) * thL;
+        p = rho <= r1 ? pv : (rho < r2 ? pm : pl);
     }
     C rad;
     if constexpr (std::is_same<C, float>::value)
         rad = (p - rho * C(1.0 / 3.0)) * k.two_over_G;
     else
         rad = C(2) * (p - rho * C(1.0 / 3.0)) / k.G_eos;
-    if (!(rad >= C(0))) return false;
+    ok &= rad >= C(0);
     psi = sqrt(rad);
-    return true;
+    return ok;
+}
+template <typename C>
+__device__ __forceinline__ bool eval_psi(const RunDev &r, C rho, C &psi)
+{
+    return eval_psi<C>(r.template par<C>(), r.eos_kind, rho, psi);
 }
 
 // Bulk pressure p_EOS(rho) in FP64 (diagnostics only).

@@ -31,6 +31,9 @@ struct StepArgs {
     void *f_alt = nullptr;          // second population buffer of the fused schedule (FP64 / FP32)
     const Tile *ftiles = nullptr;   // work list of the fused kernel: tiles of tx x (fused ty) nodes
     int nftiles = 0;
+    const Tile *mtiles = nullptr;   // work list of the multi-step kernel
+    int nmtiles = 0;
+    int mntx = 0;                   // > 0: one run, its tiles in row-major order, mntx to a row (no list read)
     float *r0 = nullptr;            // writer densities of bf16 storage: a step of parity p
     float *r1 = nullptr;            // reads R[p ^ 1] and writes R[p] (r0 = R[0], r1 = R[1])
     uint32_t *seed = nullptr;       // rounding-seed counter pair, slot p written by step p
@@ -63,6 +66,21 @@ struct UtilArgs {
 hipError_t launch_step(int precision, const StepArgs &a, int parity);
 hipError_t launch_collide(int precision, const StepArgs &a, int parity);
 hipError_t launch_fused(int precision, const StepArgs &a, int parity);
+
+// Tile of the multi-step kernel: tx x ty nodes advanced `steps` steps a launch.
+struct MultiShape {
+    int steps, tx, ty;
+};
+inline int64_t multi_tiles(const MultiShape &s, int nx, int ny)
+{
+    return (int64_t)((nx + s.tx - 1) / s.tx) * ((ny + s.ty - 1) / s.ty);
+}
+// Shape of variant v of a precision; false when there is none.
+bool multi_shape(int precision, int v, MultiShape &s);
+// The variant for these runs; -1 when the precision has none.
+int pick_multi(int precision, const RunDev *runs, int nruns);
+// From an even step count: f -> f_alt, shape.steps steps later.
+hipError_t launch_multi(int precision, int v, const StepArgs &a);
 hipError_t launch_copy(void *dst, const void *src, size_t bytes, hipStream_t stream);
 hipError_t launch_psi(int precision, const StepArgs &a, int parity);
 hipError_t launch_util(int precision, const UtilArgs &u);

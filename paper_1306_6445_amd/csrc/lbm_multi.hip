@@ -1,0 +1,383 @@
+// Several D2Q9 steps in one launch (FP64 and FP32 storage, single-range force):
+// multi_kernel reads the populations of an even step count, advances its tile
+// K steps with the intermediate states in LDS and writes the state K steps
+// later, in the same layout, to the other buffer.
+//
+// Why: one step per launch reads and writes every population of the grid each
+// step (72 B per node and step in FP32), which bounded the grids that do not
+// fit a cache, and costs a launch and a chain of dependent loads, which
+// bounded the small ones.  Step s of the K collides the tile and a margin of
+// 2 (K - s) nodes, for which it needs psi one node further out, so the margin's
+// work is done again by the neighbouring tiles: 1.14 collisions and 1.29
+// densities per node and step for 64 x 16 tiles and K = 2.  HBM traffic halves
+// (82 B per node and 2 steps in FP32 by the counters) and the kernel is bound by
+// vector instruction issue: 380 a node and step, the vector units 93% busy.
+// The intermediate state passes through LDS in its storage form (FP32
+// deviations), so that K steps in one launch and K launches give the same bits.
+//
+// Measured against one step per launch (us per step): 4096 x 2048 FP32 142 ->
+// 88, FP64 261 -> 172; 40 x 256^2 FP32 32.7 -> 25.1, FP64 87 -> 57; 64 uneven
+// drops FP32 128 -> 77; 2048 x 1024 with walls FP32 27.8 -> 21; 100^2 FP64 6.0 ->
+// 2.2; 256 grids of 4 x 256 FP32 38 -> 5.9.
+#include <hip/hip_ext.h>
+
+#include "lbm_device.hpp"
+#include "lbm_kernels.hpp"
+#include "lbm_node.hpp"
+
+namespace lbm {
+
+// Populations of one run through a buffer descriptor: a 32-bit byte offset per
+// lane plus a scalar one per direction, so that a load or store takes no
+// address arithmetic in vector registers (the run's block is below 4 GiB).
+template <typename S> struct PopBuf {
+    __amdgpu_buffer_rsrc_t rsrc;
+    __device__ __forceinline__ explicit PopBuf(const S *base)
+        : rsrc(__builtin_amdgcn_make_buffer_rsrc(const_cast<S *>(base), 0, -1, 0x00020000))
+    {
+    }
+    __device__ __forceinline__ S load(uint32_t lane, uint32_t uni) const
+    {
+        if constexpr (sizeof(S) == 4)
+            return __builtin_bit_cast(S, __builtin_amdgcn_raw_buffer_load_b32(rsrc, (int)lane, (int)uni, 0));
+        else
+            return __builtin_bit_cast(S, __builtin_amdgcn_raw_buffer_load_b64(rsrc, (int)lane, (int)uni, 0));
+    }
+    __device__ __forceinline__ void store(uint32_t lane, uint32_t uni, S v) const
+    {
+        if constexpr (sizeof(S) == 4)
+            __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned int, v), rsrc, (int)lane, (int)uni, 0);
+        else {
+            typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
+            __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, v), rsrc, (int)lane, (int)uni, 0);
+        }
+    }
+};
+
+// Geometry of a tile of TX x TY nodes advanced K steps: step s (1..K) collides
+// the tile and a margin of 2 (K - s) nodes around it, for which it needs psi
+// one node further out.
+template <int K, int TX, int TY> struct MultiGeom {
+    static constexpr int M = 2 * (K - 1);                       // margin of the first step
+    static constexpr int FX = TX + 2 * M, FY = TY + 2 * M, FN = FX * FY; // LDS populations
+    static constexpr int PX = FX + 2, PN = PX * (FY + 2);       // LDS psi
+    static constexpr int w(int s) { return TX + 4 * (K - s); }
+    static constexpr int h(int s) { return TY + 4 * (K - s); }
+    static constexpr int cells(int s) { return w(s) * h(s); }
+    static constexpr int ring(int s) { return 2 * (w(s) + 2) + 2 * h(s); }
+};
+
+// Position, relative to the tile's origin, of item k of step s: first the
+// colliding cells row by row, then the one-node ring around them (top row,
+// bottom row, left and right columns).
+template <typename Gm, int s, int K> __device__ __forceinline__ void multi_item(int k, int &dx, int &dy)
+{
+    constexpr int W = Gm::w(s), H = Gm::h(s), N = Gm::cells(s), m = 2 * (K - s);
+    if (k < N) {
+        const int ly = (unsigned)k / (unsigned)W;
+        dx = k - ly * W - m;
+        dy = ly - m;
+    } else {
+        const int q = k - N;
+        const bool rows = q < 2 * (W + 2);
+        const bool second = rows ? q >= W + 2 : (q & 1);
+        const int c = rows ? (second ? q - (W + 2) : q) : (q - 2 * (W + 2)) >> 1;
+        dx = rows ? c - 1 - m : (second ? W - m : -1 - m);
+        dy = rows ? (second ? H - m : -1 - m) : c - m;
+    }
+}
+
+constexpr int kMGeneral = 0, kMPeriodic = 1, kMInner = 2;
+
+template <typename S, int K, int TX, int TY, int NT, int MODE>
+struct MultiTile {
+    using C = typename Store<S>::C;
+    using Gm = MultiGeom<K, TX, TY>;
+    const RunPar<C> k;
+    const int eos, nx, ny, ld, bcx, bcy, x0, y0;
+    const uint32_t ds; // bytes from one direction's array to the next
+    const PopBuf<S> in, out;
+    C *psi;
+    S *pop;
+    bool bad = false;
+
+    template <int A> __device__ __forceinline__ C decode(S v) const { return Store<S>::template load<A>(&v, 0, k.rho_ref); }
+    template <int A> __device__ __forceinline__ S encode(C v) const
+    {
+        S r;
+        Store<S>::template store<A>(&r, 0, v, k.rho_ref);
+        return r;
+    }
+    // the node an item stands for: wrapped on periodic axes (global), clamped across walls
+    __device__ __forceinline__ int wrap_x(int x) const { return MODE == kMInner ? x : psi_coord(x, nx, MODE == kMPeriodic ? BC_PERIODIC : bcx); }
+    __device__ __forceinline__ int wrap_y(int y) const { return MODE == kMInner ? y : psi_coord(y, ny, MODE == kMPeriodic ? BC_PERIODIC : bcy); }
+
+    struct LoadG {
+        const MultiTile &t;
+        uint32_t off;
+        C *f;
+        template <int A> __device__ __forceinline__ void operator()() { f[A] = t.template decode<A>(t.in.load(off, A * t.ds)); }
+    };
+    // f_a(x) of an intermediate state: f*_a(x - e_a), or f*_opp(a)(x) across a wall
+    struct LoadL {
+        const MultiTile &t;
+        int cell; // of the item's node
+        bool wxm, wxp, wym, wyp;
+        C *f;
+        template <int A> __device__ __forceinline__ void operator()()
+        {
+            constexpr int ex = ex_of(A), ey = ey_of(A);
+            int i = A * Gm::FN + cell - (ey * Gm::FX + ex);
+            if constexpr (MODE == kMGeneral && A > 0) {
+                const bool wall = (ex > 0 && wxm) || (ex < 0 && wxp) || (ey > 0 && wym) || (ey < 0 && wyp);
+                i = wall ? opp_of(A) * Gm::FN + cell : i;
+            }
+            f[A] = t.template decode<A>(t.pop[i]);
+        }
+    };
+    struct StoreL {
+        const MultiTile &t;
+        int cell;
+        const C *f;
+        template <int A> __device__ __forceinline__ void operator()() { t.pop[A * Gm::FN + cell] = t.template encode<A>(f[A]); }
+    };
+    // f*_a(x) to slot a of x + e_a, or slot opp(a) of x across a wall (the even-state layout)
+    struct StoreG {
+        const MultiTile &t;
+        uint32_t xo[3], yo[3]; // byte offsets of x - 1, x, x + 1 and of rows y - 1, y, y + 1
+        bool wxm, wxp, wym, wyp;
+        const C *f;
+        template <int A> __device__ __forceinline__ void operator()()
+        {
+            constexpr int ex = ex_of(A), ey = ey_of(A);
+            const S v = t.template encode<A>(f[A]);
+            if constexpr (MODE == kMInner) {
+                t.out.store(xo[1], A * t.ds + (uint32_t)((ey * t.ld + ex) * (int)sizeof(S)), v);
+            } else if constexpr (MODE == kMPeriodic || A == 0) {
+                t.out.store(xo[1 + ex] + yo[1 + ey], A * t.ds, v);
+            } else {
+                const bool wall = (ex > 0 && wxp) || (ex < 0 && wxm) || (ey > 0 && wyp) || (ey < 0 && wym);
+                t.out.store(wall ? opp_of(A) * t.ds + xo[1] + yo[1] : A * t.ds + xo[1 + ex] + yo[1 + ey], 0, v);
+            }
+        }
+    };
+
+    template <int s> __device__ __forceinline__ void load(int dx, int dy, C *f) const
+    {
+        const int gx = wrap_x(x0 + dx), gy = wrap_y(y0 + dy);
+        if constexpr (s == 1) {
+            LoadG op{*this, (uint32_t)(gy * ld + gx) * (uint32_t)sizeof(S), f};
+            for9(op);
+        } else {
+            // LDS cell: unwrapped on a periodic axis, the clamped node's across a wall
+            int cx = dx, cy = dy;
+            bool wxm = false, wxp = false, wym = false, wyp = false;
+            if constexpr (MODE == kMGeneral) {
+                if (bcx == BC_WALL) cx = gx - x0, wxm = gx == 0, wxp = gx == nx - 1;
+                if (bcy == BC_WALL) cy = gy - y0, wym = gy == 0, wyp = gy == ny - 1;
+            }
+            LoadL op{*this, (cy + Gm::M) * Gm::FX + cx + Gm::M, wxm, wxp, wym, wyp, f};
+            for9(op);
+        }
+    }
+
+    template <int s> __device__ __forceinline__ C put_psi(int dx, int dy, const C *f)
+    {
+        C ps, rho;
+        bad |= !node_psi<C>(k, eos, f, ps, rho);
+        psi[(dy + Gm::M + 1) * Gm::PX + dx + Gm::M + 1] = ps;
+        return rho;
+    }
+
+    template <int s> __device__ __forceinline__ void step(int tid)
+    {
+        constexpr int N = Gm::cells(s), NI = N + Gm::ring(s), R = (N + NT - 1) / NT;
+        C fv[R][9], rho[R];
+#pragma unroll
+        for (int j = 0; j < R; ++j) {
+            const int i = tid + j * NT;
+            if (i < NI) {
+                int dx, dy;
+                multi_item<Gm, s, K>(i, dx, dy);
+                load<s>(dx, dy, fv[j]);
+                rho[j] = put_psi<s>(dx, dy, fv[j]);
+            }
+        }
+        for (int i = tid + R * NT; i < NI; i += NT) {
+            int dx, dy;
+            multi_item<Gm, s, K>(i, dx, dy);
+            C fr[9];
+            load<s>(dx, dy, fr);
+            put_psi<s>(dx, dy, fr);
+        }
+        __syncthreads();
+#pragma unroll
+        for (int j = 0; j < R; ++j) {
+            const int i = tid + j * NT;
+            if (i < N) {
+                const int ly = (unsigned)i / (unsigned)Gm::w(s), lx = i - ly * Gm::w(s);
+                const int dx = lx - 2 * (K - s), dy = ly - 2 * (K - s);
+                C fs[9];
+                collide_node<C>(k, fv[j], rho[j], psi + (dy + Gm::M + 1) * Gm::PX + dx + Gm::M + 1, Gm::PX, fs);
+                if constexpr (s < K) {
+                    StoreL op{*this, (dy + Gm::M) * Gm::FX + dx + Gm::M, fs};
+                    for9(op);
+                } else {
+                    const int x = x0 + dx, y = y0 + dy;
+                    if (MODE == kMInner || (x < nx && y < ny)) {
+                        constexpr uint32_t z = sizeof(S);
+                        StoreG op{*this, {}, {}, false, false, false, false, fs};
+                        if constexpr (MODE == kMInner) {
+                            op.xo[1] = (uint32_t)(y * ld + x) * z;
+                        } else {
+                            const Nbr n = neighbours(x, y, nx, ny, MODE == kMPeriodic ? BC_PERIODIC : bcx,
+                                                     MODE == kMPeriodic ? BC_PERIODIC : bcy);
+                            op.xo[0] = n.xm * z, op.xo[1] = x * z, op.xo[2] = n.xp * z;
+                            op.yo[0] = n.ym * ld * z, op.yo[1] = y * ld * z, op.yo[2] = n.yp * ld * z;
+                            op.wxm = n.wxm, op.wxp = n.wxp, op.wym = n.wym, op.wyp = n.wyp;
+                        }
+                        for9(op);
+                    }
+                }
+            }
+        }
+        if constexpr (s < K) {
+            __syncthreads();
+            step<s + 1>(tid);
+        }
+    }
+};
+
+template <typename S, int K, int TX, int TY, int NT, int MODE>
+__device__ __forceinline__ bool multi_tile(const RunDev &r, const Tile &t, const S *src, S *dst, unsigned char *lds)
+{
+    using C = typename Store<S>::C;
+    using Gm = MultiGeom<K, TX, TY>;
+    MultiTile<S, K, TX, TY, NT, MODE> m{r.template par<C>(), r.eos_kind, r.nx, r.ny, r.pitch, r.bc_x, r.bc_y, t.x0, t.y0,
+                                       (uint32_t)r.dstride * (uint32_t)sizeof(S), PopBuf<S>(src), PopBuf<S>(dst),
+                                       reinterpret_cast<C *>(lds), reinterpret_cast<S *>(lds + sizeof(C) * Gm::PN)};
+    m.template step<1>((int)threadIdx.x);
+    return m.bad;
+}
+
+// Grid: one workgroup per tile of the list, or of the one run (ntx tiles to a row).
+template <typename S, int K, int TX, int TY, int NT>
+__global__ void __launch_bounds__(NT) multi_kernel(const RunDev *__restrict__ runs, const Tile *__restrict__ tiles, int ntx,
+                                              const S *__restrict__ src, S *__restrict__ dst,
+                                              int32_t *__restrict__ status, int xcd)
+{
+    static_assert(K % 2 == 0, "the state returns to the layout of an even step count");
+    using C = typename Store<S>::C;
+    using Gm = MultiGeom<K, TX, TY>;
+    __shared__ __align__(16) unsigned char lds[sizeof(C) * Gm::PN + sizeof(S) * 9 * Gm::FN];
+    const int wi = work_index(xcd);
+    // one run: the tile follows from the work index (no dependent load of the list)
+    const Tile t = ntx > 0 ? Tile{0, wi % ntx * TX, wi / ntx * TY, 0} : tiles[wi];
+    const RunDev &r = runs[t.run];
+    constexpr int E = Gm::M + 2; // reach of the first step's loads and of the last step's stores
+    const bool inner = t.x0 - E >= 0 && t.x0 + TX + E <= r.nx && t.y0 - E >= 0 && t.y0 + TY + E <= r.ny;
+    bool bad;
+    if (inner)
+        bad = multi_tile<S, K, TX, TY, NT, kMInner>(r, t, src + r.f_off, dst + r.f_off, lds);
+    else if (r.bc_x == BC_PERIODIC && r.bc_y == BC_PERIODIC)
+        bad = multi_tile<S, K, TX, TY, NT, kMPeriodic>(r, t, src + r.f_off, dst + r.f_off, lds);
+    else
+        bad = multi_tile<S, K, TX, TY, NT, kMGeneral>(r, t, src + r.f_off, dst + r.f_off, lds);
+    if (bad) status[t.run] = 1;
+}
+
+} // namespace lbm
+
+// ------------------------------------------------------------ launchers
+namespace lbm {
+
+namespace {
+
+template <typename S, int K, int TX, int TY, int NT> hipError_t launch_multi_t(const StepArgs &a)
+{
+    hipExtLaunchKernelGGL((multi_kernel<S, K, TX, TY, NT>), dim3(a.nmtiles), dim3(NT), 0, a.stream, a.ev_start, a.ev_stop,
+                          0, a.runs, a.mtiles, a.mntx, static_cast<const S *>(a.f), static_cast<S *>(a.f_alt), a.status,
+                          a.xcd);
+    return hipGetLastError();
+}
+
+struct Variant {
+    MultiShape shape;
+    // vector instructions of a tile, about 93 per density and 200 per collision
+    int64_t work;
+    // small tiles of several steps: taken when the work list has no more of them than this
+    int64_t max_tiles;
+    hipError_t (*launch)(const StepArgs &);
+};
+
+template <typename S, int K, int TX, int TY, int NT> constexpr Variant make_variant(int64_t max_tiles)
+{
+    using Gm = MultiGeom<K, TX, TY>;
+    int64_t work = 0;
+    for (int s = 1; s <= K; ++s) work += 93 * (Gm::cells(s) + Gm::ring(s)) + 200 * Gm::cells(s);
+    return {{K, TX, TY}, work, max_tiles, launch_multi_t<S, K, TX, TY, NT>};
+}
+
+// The variants of one precision, the latency-bound ones (max_tiles > 0) first.
+// Threads are a multiple of 256 (four waves, one per SIMD: 576 threads ran 20%
+// slower than 512), and the first step's cells fill them in one or two rounds.
+//  - K = 4 tiles for few nodes, where a step is the launch and one chain of
+//    latencies: the smaller the tile the shorter the chain, as long as each
+//    tile has a CU of its own (FP64: 100^2 2.2 us a step with 8 x 8 against 2.5
+//    with 12 x 12; 256^2 4.3 / 3.8 / 3.7 with 8 x 8, 12 x 12 and 28 x 12, K = 2);
+//  - otherwise the shape with the least work, counting whole tiles: 60 x 20 has
+//    the smallest margins (64 uneven drops 76 against 80 us with 64 x 16),
+//    64 x 16 fits widths of 64 k (256^2 drops 25.1 against 27.7), 4 x 60 and
+//    8 x 60 grids a few nodes wide (256 of 4 x 256: 5.9 us against 12 with
+//    16 x 16 tiles and 32 with 60 x 20).
+const Variant kF32[] = {
+    make_variant<float, 4, 8, 8, 512>(512),  make_variant<float, 4, 20, 20, 1024>(512),
+    make_variant<float, 2, 64, 16, 768>(0),  make_variant<float, 2, 60, 20, 768>(0),
+    make_variant<float, 2, 4, 60, 512>(0),   make_variant<float, 2, 8, 60, 768>(0),
+};
+const Variant kF64[] = {
+    make_variant<double, 4, 8, 8, 512>(256), make_variant<double, 4, 12, 12, 768>(256),
+    make_variant<double, 2, 28, 12, 512>(768), make_variant<double, 2, 32, 16, 512>(0),
+    make_variant<double, 2, 28, 20, 768>(0), make_variant<double, 2, 4, 60, 512>(0),
+};
+
+const Variant *variant(int precision, int v)
+{
+    if (precision == PREC_FP32) return v >= 0 && v < (int)(sizeof(kF32) / sizeof(kF32[0])) ? &kF32[v] : nullptr;
+    if (precision == PREC_FP64) return v >= 0 && v < (int)(sizeof(kF64) / sizeof(kF64[0])) ? &kF64[v] : nullptr;
+    return nullptr;
+}
+
+} // namespace
+
+bool multi_shape(int precision, int v, MultiShape &s)
+{
+    const Variant *p = variant(precision, v);
+    if (p) s = p->shape;
+    return p != nullptr;
+}
+
+int pick_multi(int precision, const RunDev *runs, int nruns)
+{
+    int best = -1;
+    int64_t least = 0;
+    for (int v = 0; const Variant *p = variant(precision, v); ++v) {
+        int64_t tiles = 0;
+        for (int i = 0; i < nruns; ++i) tiles += multi_tiles(p->shape, runs[i].nx, runs[i].ny);
+        if (p->max_tiles > 0) {
+            if (tiles <= p->max_tiles) return v;
+        } else if (best < 0 || tiles * p->work < least) {
+            best = v;
+            least = tiles * p->work;
+        }
+    }
+    return best;
+}
+
+hipError_t launch_multi(int precision, int v, const StepArgs &a)
+{
+    const Variant *p = variant(precision, v);
+    return p && a.f_alt && (a.mntx > 0 || a.mtiles) ? p->launch(a) : hipErrorInvalidValue;
+}
+
+} // namespace lbm
