@@ -6,6 +6,7 @@
 
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cmath>
 #include <cstring>
 #include <new>
@@ -35,6 +36,11 @@ size_t al256(size_t x) { return (x + 255) & ~size_t(255); }
 // population elements from one direction's array to the next: the nodes
 // rounded up to 256 bytes plus a skew of 17 x 256 bytes (as in 2D)
 int64_t dstride3(int64_t nodes, size_t s) { return (int64_t)((((size_t)nodes * s + 255) & ~size_t(255)) + 17 * 256) / (int64_t)s; }
+
+// The state that a step writes is what the next one reads: a buffer within
+// the 256 MB Infinity Cache is left there, a larger one is stored past it
+// (160^3 FP32, 311 MB: 154 -> 147 us a step; 96^3 FP64, 134 MB: 60 -> 68).
+constexpr uint64_t kInfinityCache = uint64_t(256) << 20;
 
 struct Layout3 {
     size_t f = 0, f2 = 0, psi = 0, run = 0, status = 0, partial = 0, staging = 0, total = 0;
@@ -148,7 +154,9 @@ struct lbm3d_ctx {
         a.tile_x = tile_x;
         a.tile_y = tile_y;
         a.zchunk = zchunk;
-        a.w32 = 19 * (uint64_t)L.dstride * (precision == LBM_FP64 ? 8 : 4) <= 0xffffffffull;
+        const uint64_t pop_bytes = 19 * (uint64_t)L.dstride * (precision == LBM_FP64 ? 8 : 4);
+        a.w32 = pop_bytes <= 0xffffffffull;
+        a.beyond_cache = pop_bytes > kInfinityCache;
         a.stream = stream;
         return a;
     }
@@ -250,6 +258,40 @@ void lbm3d_destroy(lbm3d_ctx *ctx)
     delete ctx;
 }
 
+// The schedule of a new context.  Up to 64^3 nodes the two passes: a step is
+// then two short launches of independent nodes against a march of dependent
+// planes (48^3 FP32 12.9 us a step against 14.3 fused, 64^3 16.0 / 16.9).
+// Above, the fused step: its workgroups march z_chunk + 2 planes each, a
+// latency a plane, so the chunk is the one with the fewest rounds of resident
+// workgroups (two of 512 threads on a CU in FP32, one in FP64) times planes:
+// 160^3 FP32 147 us a step with 480 workgroups of 20 planes, 250 with 180 of
+// 64; 96^3 FP64 62 us with 32 x 16 tiles and 7-8 planes, 294 with 24 workgroups
+// of 96 planes.  64 x 8 tiles read whole lines; 32 x 16 ones (a smaller ring,
+// less padding) are taken where they save a tenth (FP64) or a third (FP32) of
+// the planes.
+static void default_schedule(lbm3d_ctx *c)
+{
+    const int64_t nx = c->grid.nx, ny = c->grid.ny, nz = c->grid.nz;
+    c->fused = nx * ny * nz > 64 * 64 * 64;
+    const int64_t slots = c->precision == LBM_FP64 ? 256 : 512;
+    double least = 0.0;
+    for (int tx : {64, 32}) {
+        const int ty = 512 / tx;
+        for (int64_t k = 1; k <= std::min<int64_t>(nz, 512); ++k) {
+            const int64_t zc = (nz + k - 1) / k, blocks = lbm3::fused3_blocks(nx, ny, nz, tx, ty, (int)zc);
+            if (blocks * 512 > (int64_t)UINT32_MAX) break;
+            const double cost = (double)((blocks + slots - 1) / slots) * ((double)zc + 2.5) *
+                                (tx == 64 ? 1.0 : (c->precision == LBM_FP64 ? 1.1 : 1.35));
+            if (least == 0.0 || cost < least) {
+                least = cost;
+                c->tile_x = tx;
+                c->tile_y = ty;
+                c->zchunk = (int)zc;
+            }
+        }
+    }
+}
+
 lbm_status lbm3d_create(const lbm3d_grid *grid, const lbm_eos *eos, double G, const lbm3d_rates *rates,
                         double kappa, double epsilon, int32_t precision, void *workspace, size_t workspace_bytes,
                         void *stream, lbm3d_ctx **out)
@@ -263,9 +305,8 @@ lbm_status lbm3d_create(const lbm3d_grid *grid, const lbm_eos *eos, double G, co
     lbm3d_ctx *c = new (std::nothrow) lbm3d_ctx;
     if (!c) return fail3(LBM_ENOMEM, "host allocation failed");
     c->precision = precision;
-    // default z chunk from a sweep on a 256^3 drop: 64 planes in FP32, 128 in FP64
-    c->zchunk = precision == LBM_FP64 ? 128 : 64;
     c->grid = *grid;
+    default_schedule(c);
     c->L = layout3(*grid, precision);
     if (workspace && workspace_bytes < c->L.total) {
         delete c;

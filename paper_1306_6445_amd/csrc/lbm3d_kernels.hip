@@ -16,11 +16,10 @@
 // bounce-back).  Every slot is read once per step, so reads are shifted by
 // one node and writes are aligned, which streams faster on this memory system
 // than aligned reads with shifted writes.
-// The moment transforms are the integer D3Q19 basis unrolled at compile time
-// (zero entries dropped, +-1 entries as plain additions).
 #include <hip/hip_ext.h>
 
 #include "lbm3d_kernels.hpp"
+#include "lbm_popbuf.hpp"
 
 namespace lbm3 {
 
@@ -32,87 +31,13 @@ __host__ __device__ constexpr int c2of(int a) { return ex3(a) * ex3(a) + ey3(a) 
 __host__ __device__ constexpr double w_eq3(int a) { return c2of(a) == 0 ? 1.0 / 3.0 : (c2of(a) == 1 ? 1.0 / 18.0 : 1.0 / 36.0); }
 __host__ __device__ constexpr double w_int3(int a) { return c2of(a) == 0 ? 0.0 : (c2of(a) == 1 ? 1.0 / 6.0 : 1.0 / 12.0); }
 
-// Orthogonal moment basis (rho, e, eps, jx, qx, jy, qy, jz, qz, 3pxx, 3pixx,
-// pww, piww, pxy, pyz, pxz, mx, my, mz): row k at velocity a, and row norms.
-__host__ __device__ constexpr int mrow(int k, int a)
-{
-    const int x = ex3(a), y = ey3(a), z = ez3(a), c2 = c2of(a);
-    switch (k) {
-    case 0: return 1;
-    case 1: return 19 * c2 - 30;
-    case 2: return (21 * c2 * c2 - 53 * c2 + 24) / 2;
-    case 3: return x;
-    case 4: return (5 * c2 - 9) * x;
-    case 5: return y;
-    case 6: return (5 * c2 - 9) * y;
-    case 7: return z;
-    case 8: return (5 * c2 - 9) * z;
-    case 9: return 3 * x * x - c2;
-    case 10: return (3 * c2 - 5) * (3 * x * x - c2);
-    case 11: return y * y - z * z;
-    case 12: return (3 * c2 - 5) * (y * y - z * z);
-    case 13: return x * y;
-    case 14: return y * z;
-    case 15: return x * z;
-    case 16: return x * (y * y - z * z);
-    case 17: return y * (z * z - x * x);
-    default: return z * (x * x - y * y);
-    }
-}
+// norms of the orthogonal moment basis (rho, e, eps, jx, qx, jy, qy, jz, qz,
+// 3pxx, 3pixx, pww, piww, pxy, pyz, pxz, mx, my, mz)
 __host__ __device__ constexpr int mnorm(int k)
 {
     return k == 0 ? 19 : k == 1 ? 2394 : k == 2 ? 252 : k <= 8 ? (k % 2 ? 10 : 40)
          : k == 9 ? 36 : k == 10 ? 72 : k == 11 ? 12 : k == 12 ? 24 : k <= 15 ? 4 : 8;
 }
-
-// sum_a c_a v_a over a < A with compile-time integer coefficients c_a = coef(a)
-template <typename C, typename Coef, int A> struct IntDot {
-    __device__ __forceinline__ static C run(const C *v)
-    {
-        const C rest = IntDot<C, Coef, A - 1>::run(v);
-        constexpr int c = Coef::at(A - 1);
-        if constexpr (c == 0)
-            return rest;
-        else if constexpr (c == 1)
-            return rest + v[A - 1];
-        else if constexpr (c == -1)
-            return rest - v[A - 1];
-        else
-            return rest + C(c) * v[A - 1];
-    }
-};
-template <typename C, typename Coef> struct IntDot<C, Coef, 0> {
-    __device__ __forceinline__ static C run(const C *) { return C(0); }
-};
-template <int K> struct RowOf {
-    __host__ __device__ static constexpr int at(int a) { return mrow(K, a); }
-};
-template <int A> struct ColOf {
-    __host__ __device__ static constexpr int at(int k) { return mrow(k, A); }
-};
-
-template <typename C, int K> struct ToMoments {
-    __device__ __forceinline__ static void run(const C *f, C *m)
-    {
-        ToMoments<C, K - 1>::run(f, m);
-        m[K - 1] = IntDot<C, RowOf<K - 1>, 19>::run(f);
-    }
-};
-template <typename C> struct ToMoments<C, 0> {
-    __device__ __forceinline__ static void run(const C *, C *) {}
-};
-
-// f = M^-1 m = M^T diag(1 / norm) m: scale once, then integer columns
-template <typename C, int A> struct ToPops {
-    __device__ __forceinline__ static void run(const C *ms, C *f)
-    {
-        ToPops<C, A - 1>::run(ms, f);
-        f[A - 1] = IntDot<C, ColOf<A - 1>, 19>::run(ms);
-    }
-};
-template <typename C> struct ToPops<C, 0> {
-    __device__ __forceinline__ static void run(const C *, C *) {}
-};
 
 template <typename C> __device__ __forceinline__ C rate(const Run3 &r, int k)
 {
@@ -261,123 +186,120 @@ __global__ void __launch_bounds__(kThreads3) psi3_kernel(const Run3 *__restrict_
     static_cast<C *>(psi_out)[n] = ok ? ps : C(NAN);
 }
 
-// the "second-order" part of a moment vector for a symmetric tensor T
-// (xx, yy, zz, xy, yz, xz): rows e, eps, 3pxx, 3pixx, pww, piww, pxy, pyz, pxz
-template <typename C> struct Second {
-    C e, eps, pxx, pixx, pww, piww, pxy, pyz, pxz;
-    __device__ __forceinline__ Second(C xx, C yy, C zz, C xy, C yz, C xz)
-    {
-        const C tr = xx + yy + zz;
-        e = C(19) * tr;
-        eps = C(-5.5) * tr;
-        pxx = C(3) * xx - tr;
-        pixx = C(-0.5) * pxx;
-        pww = yy - zz;
-        piww = C(-0.5) * pww;
-        pxy = xy;
-        pyz = yz;
-        pxz = xz;
-    }
-};
-
 // One node's collision, shared by both schedules: psi_at(a) gives psi at
 // x + e_a (a = 0: the node itself; beyond a wall, the adjacent fluid node), fv
-// holds the node's 19 populations of the current state (streamed), n its
-// index.  The same source expressions in both kernels give the same bits.
-template <typename S, typename C, bool W32, typename PsiAt>
-__device__ __forceinline__ void collide3(const Run3 &r, S *__restrict__ fout, const C *fv, int64_t n,
-                                         const PsiAt &psi_at)
+// holds the node's 19 populations of the current state (streamed), rho their
+// density19 -> fs.  The same source expressions in both kernels give the same
+// bits.  Both moment transforms go through the sums and differences of
+// opposite populations, which share most of their terms: about 170 additions
+// and products against 400 for the rows and columns of M one by one.
+template <typename C, typename PsiAt>
+__device__ __forceinline__ void collide3(const RunPar<C> &k, const Run3 &r, const C *fv, C rho, const PsiAt &psi_at, C *fs)
 {
-    // Eq. (7) and Eq. (19) with the 3D weights; psi beyond a wall = psi of the adjacent fluid node
-    const RunPar<C> &k = r.r.template par<C>();
+    // Eq. (7) and Eq. (19) with the 3D weights 1/6 and 1/12
+    C sx, sy, sz, qxx, qyy, qzz, qxy, qyz, qxz;
     const C p0 = psi_at(0);
-    C sx = 0, sy = 0, sz = 0, qxx = 0, qyy = 0, qzz = 0, qxy = 0, qyz = 0, qxz = 0;
-#pragma unroll
-    for (int a = 1; a < 19; ++a) {
-        const C pa = psi_at(a);
-        const C w = C(w_int3(a));
-        if (ex3(a)) sx += C(ex3(a)) * w * pa;
-        if (ey3(a)) sy += C(ey3(a)) * w * pa;
-        if (ez3(a)) sz += C(ez3(a)) * w * pa;
-        const C d = w * (pa - p0);
-        if (ex3(a)) qxx += d;
-        if (ey3(a)) qyy += d;
-        if (ez3(a)) qzz += d;
-        if (ex3(a) * ey3(a)) qxy += C(ex3(a) * ey3(a)) * d;
-        if (ey3(a) * ez3(a)) qyz += C(ey3(a) * ez3(a)) * d;
-        if (ex3(a) * ez3(a)) qxz += C(ex3(a) * ez3(a)) * d;
+    {
+        const C w1 = C(1.0 / 6.0), w2 = C(1.0 / 12.0);
+        const C p1 = psi_at(1), p2 = psi_at(2), p3 = psi_at(3), p4 = psi_at(4), p5 = psi_at(5), p6 = psi_at(6);
+        const C p7 = psi_at(7), p8 = psi_at(8), p9 = psi_at(9), p10 = psi_at(10);
+        const C sA = p7 + p8, sB = p9 + p10, dA = p7 - p8, dB = p9 - p10;
+        const C p11 = psi_at(11), p12 = psi_at(12), p13 = psi_at(13), p14 = psi_at(14);
+        const C sC = p11 + p12, sD = p13 + p14, dC = p11 - p12, dD = p13 - p14;
+        const C p15 = psi_at(15), p16 = psi_at(16), p17 = psi_at(17), p18 = psi_at(18);
+        const C sE = p15 + p16, sF = p17 + p18, dE = p15 - p16, dF = p17 - p18;
+        sx = w1 * (p1 - p2) + w2 * ((dA + dB) + (dC + dD));
+        sy = w1 * (p3 - p4) + w2 * ((dA - dB) + (dE + dF));
+        sz = w1 * (p5 - p6) + w2 * ((dC - dD) + (dE - dF));
+        const C xy = (sA + sB) - C(4) * p0, xz = (sC + sD) - C(4) * p0, yz = (sE + sF) - C(4) * p0;
+        qxx = w1 * ((p1 + p2) - C(2) * p0) + w2 * (xy + xz);
+        qyy = w1 * ((p3 + p4) - C(2) * p0) + w2 * (xy + yz);
+        qzz = w1 * ((p5 + p6) - C(2) * p0) + w2 * (xz + yz);
+        qxy = w2 * (sA - sB);
+        qxz = w2 * (sC - sD);
+        qyz = w2 * (sE - sF);
     }
     const C G = k.G;
-    const C Fx = -G * p0 * sx, Fy = -G * p0 * sy, Fz = -G * p0 * sz;
+    const C Gp = -G * p0;
+    const C Fx = Gp * sx, Fy = Gp * sy, Fz = Gp * sz;
     const C F2 = G * G * (sx * sx + sy * sy + sz * sz); // |F|^2 / psi^2
     const C kq = k.kappa * G * C(0.5) * p0;
-    qxx *= kq, qyy *= kq, qzz *= kq, qxy *= kq, qyz *= kq, qxz *= kq;
+    // flux shift (3/5) tr Q I - Q + 2 sigma |F|^2/psi^2 I
+    const C iso = C(0.6) * (kq * (qxx + qyy + qzz)) + two_sigma<C>(r) * F2;
 
-    C m[19];
-    const C rho = density19<C>(fv);
-    ToMoments<C, 19>::run(fv, m);
+    // moments from the sums and differences of opposite populations
+    const C X = fv[1] + fv[2], Y = fv[3] + fv[4], Z = fv[5] + fv[6];
+    const C A = fv[7] + fv[8], B = fv[9] + fv[10], Cc = fv[11] + fv[12], D = fv[13] + fv[14], E = fv[15] + fv[16],
+            F = fv[17] + fv[18];
+    const C dx = fv[1] - fv[2], dy = fv[3] - fv[4], dz = fv[5] - fv[6];
+    const C a = fv[7] - fv[8], b = fv[9] - fv[10], c = fv[11] - fv[12], d = fv[13] - fv[14], e = fv[15] - fv[16],
+            f = fv[17] - fv[18];
+    const C XY = A + B, XZ = Cc + D, YZ = E + F;
+    const C S1 = X + Y + Z, S2 = XY + XZ + YZ;
+    const C xab = a + b, xcd = c + d, yab = a - b, yef = e + f, zcd = c - d, zef = e - f;
+    const C tx = xab + xcd, ty = yab + yef, tz = zcd + zef;
+    const C jx = dx + tx, jy = dy + ty, jz = dz + tz;
+
     // Eq. (6) velocity
     const C irho = lbm::recip<C>(rho);
-    const C vx = (m[3] + C(0.5) * Fx) * irho, vy = (m[5] + C(0.5) * Fy) * irho, vz = (m[7] + C(0.5) * Fz) * irho;
-    // equilibrium (tensor rho v v), Guo forcing (v F + F v) and flux shift
-    // ((3/5) tr Q I - Q + 2 sigma |F|^2/psi^2 I) moments
-    const Second<C> E2(rho * vx * vx, rho * vy * vy, rho * vz * vz, rho * vx * vy, rho * vy * vz, rho * vx * vz);
-    const Second<C> S2(C(2) * vx * Fx, C(2) * vy * Fy, C(2) * vz * Fz, vx * Fy + vy * Fx, vy * Fz + vz * Fy,
-                       vx * Fz + vz * Fx);
-    const C iso = C(0.6) * (qxx + qyy + qzz) + two_sigma<C>(r) * F2;
-    const Second<C> D2(iso - qxx, iso - qyy, iso - qzz, -qxy, -qyz, -qxz);
-    C meq[19], Sm[19], Cm[19];
-    meq[1] = C(-11) * rho + E2.e, Sm[1] = S2.e, Cm[1] = D2.e;
-    meq[2] = C(3) * rho + E2.eps, Sm[2] = S2.eps, Cm[2] = D2.eps;
-    meq[4] = C(-2.0 / 3.0) * rho * vx, Sm[4] = C(-2.0 / 3.0) * Fx, Cm[4] = 0;
-    meq[6] = C(-2.0 / 3.0) * rho * vy, Sm[6] = C(-2.0 / 3.0) * Fy, Cm[6] = 0;
-    meq[8] = C(-2.0 / 3.0) * rho * vz, Sm[8] = C(-2.0 / 3.0) * Fz, Cm[8] = 0;
-    meq[9] = E2.pxx, Sm[9] = S2.pxx, Cm[9] = D2.pxx;
-    meq[10] = E2.pixx, Sm[10] = S2.pixx, Cm[10] = D2.pixx;
-    meq[11] = E2.pww, Sm[11] = S2.pww, Cm[11] = D2.pww;
-    meq[12] = E2.piww, Sm[12] = S2.piww, Cm[12] = D2.piww;
-    meq[13] = E2.pxy, Sm[13] = S2.pxy, Cm[13] = D2.pxy;
-    meq[14] = E2.pyz, Sm[14] = S2.pyz, Cm[14] = D2.pyz;
-    meq[15] = E2.pxz, Sm[15] = S2.pxz, Cm[15] = D2.pxz;
-    meq[16] = meq[17] = meq[18] = 0, Sm[16] = Sm[17] = Sm[18] = 0, Cm[16] = Cm[17] = Cm[18] = 0;
-    // Eq. (17); conserved moments: rho* = rho, and with the Eq. (6) velocity
-    // j* = j - s_j (j - rho v) + (1 - s_j/2) F = j + F for any s_j
-    C ms[19];
-    ms[0] = rho;
-    ms[3] = m[3] + Fx;
-    ms[5] = m[5] + Fy;
-    ms[7] = m[7] + Fz;
-#pragma unroll
-    for (int q = 1; q < 19; ++q) {
-        if (q == 3 || q == 5 || q == 7) continue;
+    const C vx = (jx + C(0.5) * Fx) * irho, vy = (jy + C(0.5) * Fy) * irho, vz = (jz + C(0.5) * Fz) * irho;
+    // P: equilibrium flux rho v v plus the flux shift; T: Guo forcing v F + F v
+    const C rx = rho * vx, ry = rho * vy, rz = rho * vz;
+    const C Pxx = rx * vx + (iso - kq * qxx), Pyy = ry * vy + (iso - kq * qyy), Pzz = rz * vz + (iso - kq * qzz);
+    const C Pxy = rx * vy - kq * qxy, Pyz = ry * vz - kq * qyz, Pxz = rx * vz - kq * qxz;
+    const C Txx = C(2) * (vx * Fx), Tyy = C(2) * (vy * Fy), Tzz = C(2) * (vz * Fz);
+    const C Txy = vx * Fy + vy * Fx, Tyz = vy * Fz + vz * Fy, Txz = vx * Fz + vz * Fx;
+    const C trP = Pxx + Pyy + Pzz, trT = Txx + Tyy + Tzz;
+
+    // Eq. (17): m* = m + s (m_eq + C - m) + (1 - s/2) S, scaled by 1 / norm.
+    // Conserved moments: rho* = rho, and with the Eq. (6) velocity
+    // j* = j - s_j (j - rho v) + (1 - s_j/2) F = j + F for any s_j; through
+    // div_const (in FP32 the product with a rounded 1/19 or 1/10 would bias the
+    // mass and momentum by an ulp every step; the residual correction removes it)
+    auto relax = [&](int q, C m, C target, C force) {
         const C s = rate<C>(r, q);
-        ms[q] = m[q] - s * (m[q] - meq[q]) + (C(1) - C(0.5) * s) * Sm[q] + s * Cm[q];
-    }
-    // M^-1 = M^T diag(1 / norm): the conserved moments through div_const (in
-    // FP32 the product with a rounded 1/19 or 1/10 would bias the mass and
-    // momentum by an ulp every step; the FMA residual correction removes it)
-#pragma unroll
-    for (int q = 0; q < 19; ++q)
-        ms[q] = (q == 0 || q == 3 || q == 5 || q == 7) ? lbm::div_const<C>(ms[q], (double)mnorm(q))
-                                                      : ms[q] * C(1.0 / mnorm(q));
-    C fs[19];
-    ToPops<C, 19>::run(ms, fs);
+        return (m + s * (target - m) + (C(1) - C(0.5) * s) * force) * C(1.0 / mnorm(q));
+    };
+    const C me = relax(1, C(-30) * fv[0] - C(11) * S1 + C(8) * S2, C(-11) * rho + C(19) * trP, C(19) * trT);
+    const C mp = relax(2, C(12) * fv[0] - C(4) * S1 + S2, C(3) * rho - C(5.5) * trP, C(-5.5) * trT);
+    const C gx = relax(4, tx - C(4) * dx, C(-2.0 / 3.0) * rx, C(-2.0 / 3.0) * Fx);
+    const C gy = relax(6, ty - C(4) * dy, C(-2.0 / 3.0) * ry, C(-2.0 / 3.0) * Fy);
+    const C gz = relax(8, tz - C(4) * dz, C(-2.0 / 3.0) * rz, C(-2.0 / 3.0) * Fz);
+    const C ax2 = C(2) * X - (Y + Z), dg2 = (XY + XZ) - C(2) * YZ;
+    const C P3 = C(3) * Pxx - trP, T3 = C(3) * Txx - trT;
+    const C m9 = relax(9, ax2 + dg2, P3, T3);
+    const C m10 = relax(10, dg2 - C(2) * ax2, C(-0.5) * P3, C(-0.5) * T3);
+    const C axw = Y - Z, dgw = XY - XZ, Pw = Pyy - Pzz, Tw = Tyy - Tzz;
+    const C m11 = relax(11, axw + dgw, Pw, Tw);
+    const C m12 = relax(12, dgw - C(2) * axw, C(-0.5) * Pw, C(-0.5) * Tw);
+    const C mxy = relax(13, A - B, Pxy, Txy), myz = relax(14, E - F, Pyz, Tyz), mxz = relax(15, Cc - D, Pxz, Txz);
+    auto decay = [&](int q, C m) { return (m - rate<C>(r, q) * m) * C(1.0 / mnorm(q)); };
+    const C mx = decay(16, xab - xcd), my = decay(17, yef - yab), mz = decay(18, zcd - zef);
+    const C m0 = lbm::div_const<C>(rho, 19.0);
+    const C hx = lbm::div_const<C>(jx + Fx, 10.0), hy = lbm::div_const<C>(jy + Fy, 10.0),
+            hz = lbm::div_const<C>(jz + Fz, 10.0);
 
-    // f* stays at the node; the next read streams it (Eq. 4)
-    const float ref = r.r.pf.rho_ref;
-    if constexpr (W32) {
-        char *base = reinterpret_cast<char *>(fout);
-        const uint32_t ds = (uint32_t)r.dstride, n32 = (uint32_t)n;
-#pragma unroll
-        for (int a = 0; a < 19; ++a)
-            *reinterpret_cast<S *>(base + (uint32_t)(((uint32_t)a * ds + n32) * (uint32_t)sizeof(S))) =
-                enc<S, C>(fs[a], a, ref);
-    } else {
-#pragma unroll
-        for (int a = 0; a < 19; ++a) fout[(int64_t)a * r.dstride + n] = enc<S, C>(fs[a], a, ref);
-    }
+    // f* = M^T of the scaled moments, opposite populations together
+    fs[0] = m0 - C(30) * me + C(12) * mp;
+    const C ax = m0 - C(11) * me - C(4) * mp, dg = m0 + C(8) * me + mp;
+    auto pair = [](C even, C odd, C &plus, C &minus) {
+        plus = even + odd;
+        minus = even - odd;
+    };
+    const C px = m9 - C(2) * m10, pw = m11 - C(2) * m12;
+    pair(ax + C(2) * px, hx - C(4) * gx, fs[1], fs[2]);
+    pair((ax - px) + pw, hy - C(4) * gy, fs[3], fs[4]);
+    pair((ax - px) - pw, hz - C(4) * gz, fs[5], fs[6]);
+    const C dp = m9 + m10, dw = m11 + m12, ux = hx + gx, uy = hy + gy, uz = hz + gz;
+    const C exy = (dg + dp) + dw, exz = (dg + dp) - dw, eyz = dg - C(2) * dp;
+    const C xp = ux + mx, xm = ux - mx, yp = uy + my, ym = uy - my, zp = uz + mz, zm = uz - mz;
+    pair(exy + mxy, xp + ym, fs[7], fs[8]);
+    pair(exy - mxy, xp - ym, fs[9], fs[10]);
+    pair(exz + mxz, xm + zp, fs[11], fs[12]);
+    pair(exz - mxz, xm - zp, fs[13], fs[14]);
+    pair(eyz + myz, yp + zm, fs[15], fs[16]);
+    pair(eyz - myz, yp - zm, fs[17], fs[18]);
 }
-
 
 // The collide pass runs over tiles of 2^txs x (256 >> txs) nodes in x-y, one
 // z-plane each; the 1D work index decomposes with workgroup-uniform integer
@@ -401,9 +323,14 @@ __global__ void __launch_bounds__(kThreads3) collide3_kernel(const Run3 *__restr
     const C *psi = static_cast<const C *>(psi_in);
     C fv[19];
     gather19<S>(r, fin, n, X, Y, Z, fv);
-    collide3<S, C, false>(r, fout, fv, n, [&](int a) {
+    C fs[19];
+    collide3<C>(r.r.template par<C>(), r, fv, density19<C>(fv), [&](int a) {
         return psi[n + nb_off(X, ex3(a)) + nb_off(Y, ey3(a)) + nb_off(Z, ez3(a))];
-    });
+    }, fs);
+    // f* stays at the node; the next read streams it (Eq. 4)
+    const float ref = r.r.pf.rho_ref;
+#pragma unroll
+    for (int a = 0; a < 19; ++a) fout[(int64_t)a * r.dstride + n] = enc<S, C>(fs[a], a, ref);
 }
 
 // The fused step: one launch, psi computed where it is needed.  A workgroup
@@ -413,70 +340,160 @@ __global__ void __launch_bounds__(kThreads3) collide3_kernel(const Run3 *__restr
 // goes into one of four rotating LDS planes; after one barrier the tile's
 // nodes of the current plane collide with the psi of planes z - 1, z, z + 1
 // and store into the other buffer.  Each node's populations are gathered once
-// (streamed from planes z, z + 1, z + 2 of the source), for its psi, and kept
-// in registers until its collision one plane later; the ring's populations are
-// re-read from cache.  Four slots let one barrier per
-// plane suffice: the slot a plane's psi goes into was last read two planes
-// earlier, before the previous barrier.  Out of place, so every workgroup
-// reads only the unmodified source buffer.
-template <typename S, int TX, int TY, bool W32>
-__global__ void __launch_bounds__(TX * TY, (W32 && sizeof(S) == 4) ? 4 : 1) fused3_kernel(const Run3 *__restrict__ runs, const S *__restrict__ fin,
+// (streamed from planes z, z + 1, z + 2 of the source), for its psi, and wait
+// in the thread's own LDS column for their collision one plane later: held in
+// registers they took FP32 to 128 and FP64 to 223 registers (4 and 2 waves per
+// SIMD).  The ring's populations are re-read from cache.  Four slots let one
+// barrier per plane suffice: the slot a plane's psi goes into was last read two
+// planes earlier, before the previous barrier.  Out of place, so every
+// workgroup reads only the unmodified source buffer.
+// What bounds it: a plane is a chain of load latency, density, barrier and
+// collision, so each thread loads the populations of the plane after next
+// before it collides (160^3 FP32 171 -> 154 us a step; the ring's loads ahead as
+// well cost registers, 220 us), and the 38 shifted or aligned streams, which
+// move 5.0 TB/s of counted traffic at 256^3 against 5.14 of a probe without
+// arithmetic.  160^3 FP32 304 -> 147 us with the chunk of its default schedule,
+// 256^3 619 -> 549, 96^3 FP64 517 -> 62.
+//
+// How a tile's populations are addressed (MODE), the same slots in each:
+//   kFlat   no wall within reach and each buffer below 4 GiB: a buffer
+//           descriptor, one 32-bit offset per (ex, ey) and a scalar one per
+//           direction and plane, so a load takes no vector address arithmetic;
+//   kWall32 walls, below 4 GiB; kWide 64-bit addresses.
+constexpr int kFlat = 0, kWall32 = 1, kWide = 2;
+
+// LDS of a workgroup: four psi planes, and the waiting populations where both
+// fit the default allocation of 64 KB (larger tiles keep them in registers).
+template <typename C> constexpr bool fused3_park(int TX, int TY)
+{
+    return sizeof(C) * (4 * (TX + 2) * (TY + 2) + 19 * TX * TY) <= 65536;
+}
+template <typename C> constexpr uint32_t fused3_lds(int TX, int TY)
+{
+    return (uint32_t)sizeof(C) * (4 * (TX + 2) * (TY + 2) + (fused3_park<C>(TX, TY) ? 19 * TX * TY : 0));
+}
+
+template <typename S, int TX, int TY, int MODE, bool NTS>
+__device__ __forceinline__ bool fused3_tile(const Run3 &r, const S *__restrict__ fin, S *__restrict__ fout,
+                                            const Fused3Thread &q,
+                                            typename std::conditional<std::is_same<S, double>::value, double, float>::type *lps,
+                                            typename std::conditional<std::is_same<S, double>::value, double, float>::type *park)
+{
+    using C = typename std::conditional<std::is_same<S, double>::value, double, float>::type;
+    constexpr int PX = TX + 2, PLANE = PX * (TY + 2), NT = TX * TY;
+    constexpr bool PARK = fused3_park<C>(TX, TY);
+    constexpr uint32_t sz = sizeof(S);
+    const int nx = r.r.nx, ny = r.r.ny, nz = r.nz, bcx = r.r.bc_x, bcy = r.r.bc_y, bcz = r.bc_z;
+    const RunPar<C> k = r.r.template par<C>();
+    const float ref = r.r.pf.rho_ref;
+    const int64_t sxy = (int64_t)nx * ny;
+    const uint32_t ds = (uint32_t)r.dstride * sz, plane = (uint32_t)sxy * sz;
+    const lbm::PopBuf<S> in(fin), out(fout);
+
+    // populations of the column (cx, cy) on plane z (wrapped or clamped)
+    auto gather = [&](int z, int cx, int cy, int64_t col, C *fv) {
+        if constexpr (MODE == kFlat) {
+            const uint32_t xo[3] = {(uint32_t)(cx == 0 ? nx - 1 : cx - 1) * sz, (uint32_t)cx * sz,
+                                    (uint32_t)(cx == nx - 1 ? 0 : cx + 1) * sz};
+            const uint32_t row = (uint32_t)nx * sz;
+            const uint32_t yo[3] = {(uint32_t)(cy == 0 ? ny - 1 : cy - 1) * row, (uint32_t)cy * row,
+                                    (uint32_t)(cy == ny - 1 ? 0 : cy + 1) * row};
+            const uint32_t zo[3] = {(uint32_t)(z == 0 ? nz - 1 : z - 1) * plane, (uint32_t)z * plane,
+                                    (uint32_t)(z == nz - 1 ? 0 : z + 1) * plane};
+#pragma unroll
+            for (int a = 0; a < 19; ++a)
+                fv[a] = dec<S>(in.load(xo[1 - ex3(a)] + yo[1 - ey3(a)], a * ds + zo[1 - ez3(a)]), a, ref);
+        } else {
+            const AxisNb X = axis_nb(cx, nx, bcx, 1), Y = axis_nb(cy, ny, bcy, nx), Z = axis_nb(z, nz, bcz, sxy);
+            if constexpr (MODE == kWall32)
+                gather19_w32<S>(r, fin, (uint32_t)(z * sxy + col), narrow(X), narrow(Y), narrow(Z), fv);
+            else
+                gather19<S>(r, fin, z * sxy + col, X, Y, Z, fv);
+        }
+    };
+    bool bad = false;
+    auto put_psi = [&](int zl, int cell, const C *fv) {
+        const C rho = density19<C>(fv);
+        C ps;
+        const bool ok = lbm::eval_psi<C>(k, r.r.eos_kind, rho, ps);
+        lps[(zl & 3) * PLANE + cell] = ok ? ps : C(NAN);
+        bad |= !ok;
+        return rho;
+    };
+    const int tid = (int)threadIdx.x;
+    C kept[PARK ? 1 : 19];
+    C rc = C(0); // density of the waiting populations
+    C fv[19]; // populations of the next plane, loaded ahead of the collision
+    gather(lbm::psi_coord(q.z0 - 1, nz, bcz), q.cx, q.cy, q.col, fv);
+    for (int zl = q.z0 - 1; zl <= q.z1; ++zl) {
+        // psi of plane zl, tile and ring
+        if (q.ring) {
+            C fr[19];
+            gather(lbm::psi_coord(zl, nz, bcz), q.rcx, q.rcy, q.rcol, fr);
+            put_psi(zl, q.rcell, fr);
+        }
+        const C rho = put_psi(zl, q.cell, fv);
+        // the populations of plane zl - 1 out, those of zl in
+        C fc[19];
+#pragma unroll
+        for (int a = 0; a < 19; ++a) {
+            if constexpr (PARK) {
+                fc[a] = park[a * NT + tid];
+                park[a * NT + tid] = fv[a];
+            } else {
+                fc[a] = kept[a];
+                kept[a] = fv[a];
+            }
+        }
+        const C rcc = rc;
+        rc = rho;
+        __syncthreads();
+        if (zl < q.z1) gather(lbm::psi_coord(zl + 1, nz, bcz), q.cx, q.cy, q.col, fv);
+        const int z = zl - 1;
+        if (z < q.z0 || !q.active) continue;
+        C fs[19];
+        collide3<C>(k, r, fc, rcc, [&](int a) {
+            return lps[((z + ez3(a)) & 3) * PLANE + q.cell + ey3(a) * PX + ex3(a)];
+        }, fs);
+        // f* stays at the node; the next read streams it (Eq. 4)
+        if constexpr (MODE == kWide) {
+            const int64_t n = (int64_t)z * sxy + (int64_t)q.y * nx + q.x;
+#pragma unroll
+            for (int a = 0; a < 19; ++a) fout[(int64_t)a * r.dstride + n] = enc<S, C>(fs[a], a, ref);
+        } else {
+#pragma unroll
+            for (int a = 0; a < 19; ++a)
+                out.template store<NTS>((uint32_t)(q.y * nx + q.x) * sz, a * ds + (uint32_t)z * plane, enc<S, C>(fs[a], a, ref));
+        }
+    }
+    return bad;
+}
+
+template <typename S, int TX, int TY, bool W32, bool NTS>
+__global__ void __launch_bounds__(TX * TY) fused3_kernel(const Run3 *__restrict__ runs, const S *__restrict__ fin,
                                                          S *__restrict__ fout, int32_t *__restrict__ status, int zc)
 {
     using C = typename std::conditional<std::is_same<S, double>::value, double, float>::type;
-    constexpr int PX = TX + 2, PY = TY + 2, PLANE = PX * PY, NT = TX * TY;
+    constexpr int PLANE = (TX + 2) * (TY + 2), NT = TX * TY;
     static_assert(PLANE - NT <= NT, "one ring node per thread at most");
-    __shared__ C lps[4][PLANE];
+    extern __shared__ unsigned char lds3[];
+    C *lps = reinterpret_cast<C *>(lds3), *park = lps + 4 * PLANE;
     const Run3 &r = runs[0];
-    const int nx = r.r.nx, ny = r.r.ny, nz = r.nz, bcx = r.r.bc_x, bcy = r.r.bc_y, bcz = r.bc_z;
-    const Fused3Thread q = fused3_thread((unsigned)lbm::work_index(1), threadIdx.x, nx, ny, nz, bcx, bcy, zc, TX, TY);
-    const int x = q.x, y = q.y, cell = q.cell, rcell = q.rcell;
-    const bool ring = q.ring;
-    const int64_t col = q.col, rcol = q.rcol, sxy = (int64_t)nx * ny;
-    // neighbour offsets of the column whose populations the thread gathers
-    const AxisNb X = axis_nb(q.cx, nx, bcx, 1), Y = axis_nb(q.cy, ny, bcy, nx);
-
-    bool bad = false;
-    // psi of plane zl (wrapped or clamped) into its LDS slot; the thread's own
-    // populations of that plane are left in fv
-    auto psi_plane = [&](int zl, C *fv) {
-        const int zw = lbm::psi_coord(zl, nz, bcz);
-        const int64_t base = (int64_t)zw * sxy;
-        const AxisNb Z = axis_nb(zw, nz, bcz, sxy);
-        if constexpr (W32)
-            gather19_w32<S>(r, fin, (uint32_t)base + (uint32_t)col, narrow(axis_nb(q.cx, nx, bcx, 1)),
-                            narrow(axis_nb(q.cy, ny, bcy, nx)), narrow(Z), fv);
+    const int nx = r.r.nx, ny = r.r.ny, nz = r.nz;
+    const Fused3Thread q = fused3_thread((unsigned)lbm::work_index(1), threadIdx.x, nx, ny, nz, r.r.bc_x, r.r.bc_y, zc, TX, TY);
+    bool bad;
+    if constexpr (W32) {
+        // walls within two nodes of the workgroup's tile and planes
+        const int x0 = q.x - (int)threadIdx.x % TX, y0 = q.y - (int)threadIdx.x / TX;
+        const bool flat = (r.r.bc_x == lbm::BC_PERIODIC || (x0 >= 2 && x0 + TX + 2 <= nx)) &&
+                          (r.r.bc_y == lbm::BC_PERIODIC || (y0 >= 2 && y0 + TY + 2 <= ny)) &&
+                          (r.bc_z == lbm::BC_PERIODIC || (q.z0 >= 2 && q.z1 + 2 <= nz));
+        if (flat)
+            bad = fused3_tile<S, TX, TY, kFlat, NTS>(r, fin, fout, q, lps, park);
         else
-            gather19<S>(r, fin, base + col, X, Y, Z, fv);
-        C ps;
-        bool ok = lbm::eval_psi<C>(r.r, density19<C>(fv), ps);
-        lps[zl & 3][cell] = ok ? ps : C(NAN);
-        bad |= !ok;
-        if (ring) {
-            C fr[19];
-            if constexpr (W32)
-                gather19_w32<S>(r, fin, (uint32_t)base + (uint32_t)rcol, narrow(axis_nb(q.rcx, nx, bcx, 1)),
-                                narrow(axis_nb(q.rcy, ny, bcy, nx)), narrow(Z), fr);
-            else
-                gather19<S>(r, fin, base + rcol, axis_nb(q.rcx, nx, bcx, 1), axis_nb(q.rcy, ny, bcy, nx), Z, fr);
-            ok = lbm::eval_psi<C>(r.r, density19<C>(fr), ps);
-            lps[zl & 3][rcell] = ok ? ps : C(NAN);
-            bad |= !ok;
-        }
-    };
-    C fc[19], fn[19];
-    psi_plane(q.z0 - 1, fn);
-    psi_plane(q.z0, fc);
-    for (int z = q.z0; z < q.z1; ++z) {
-        psi_plane(z + 1, fn);
-        __syncthreads();
-        if (q.active) {
-            const int64_t n = (int64_t)z * sxy + (int64_t)y * nx + x;
-            collide3<S, C, W32>(r, fout, fc, n,
-                                [&](int a) { return lps[(z + ez3(a)) & 3][cell + ey3(a) * PX + ex3(a)]; });
-        }
-#pragma unroll
-        for (int a = 0; a < 19; ++a) fc[a] = fn[a];
+            bad = fused3_tile<S, TX, TY, kWall32, NTS>(r, fin, fout, q, lps, park);
+    } else {
+        bad = fused3_tile<S, TX, TY, kWide, NTS>(r, fin, fout, q, lps, park);
     }
     if (bad) status[0] = 1;
 }
@@ -626,12 +643,17 @@ static unsigned blocks3(int64_t n) { return (unsigned)((n + kThreads3 - 1) / kTh
 template <typename S, int TX, int TY> hipError_t fused3_t(const Step3Args &a)
 {
     const dim3 grid(fused3_blocks(a.nx, a.ny, a.nz, TX, TY, a.zchunk)), block(TX * TY);
-    if (a.w32)
-        hipExtLaunchKernelGGL((fused3_kernel<S, TX, TY, true>), grid, block, 0, a.stream, a.ev_col0, a.ev_col1, 0,
-                              a.run, static_cast<const S *>(a.fin), static_cast<S *>(a.fout), a.status, a.zchunk);
+    constexpr uint32_t lds = fused3_lds<S>(TX, TY);
+    auto go = [&](auto kernel) {
+        hipExtLaunchKernelGGL(kernel, grid, block, lds, a.stream, a.ev_col0, a.ev_col1, 0, a.run,
+                              static_cast<const S *>(a.fin), static_cast<S *>(a.fout), a.status, a.zchunk);
+    };
+    if (!a.w32)
+        go(fused3_kernel<S, TX, TY, false, false>);
+    else if (a.beyond_cache)
+        go(fused3_kernel<S, TX, TY, true, true>);
     else
-        hipExtLaunchKernelGGL((fused3_kernel<S, TX, TY, false>), grid, block, 0, a.stream, a.ev_col0, a.ev_col1, 0,
-                              a.run, static_cast<const S *>(a.fin), static_cast<S *>(a.fout), a.status, a.zchunk);
+        go(fused3_kernel<S, TX, TY, true, false>);
     return hipGetLastError();
 }
 

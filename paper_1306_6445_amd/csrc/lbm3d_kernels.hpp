@@ -144,6 +144,7 @@ struct Step3Args {
     int32_t tile_y = 8;
     int32_t zchunk = 64; // fused: planes one workgroup marches through
     bool w32 = false;    // each population buffer is below 4 GiB: 32-bit byte offsets in the fused kernel
+    bool beyond_cache = false; // a population buffer outgrows the Infinity Cache (w32 only): non-temporal stores
     hipStream_t stream;
     hipEvent_t ev_psi0 = nullptr, ev_psi1 = nullptr, ev_col0 = nullptr, ev_col1 = nullptr;
 };

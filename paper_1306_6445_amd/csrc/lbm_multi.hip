@@ -24,35 +24,9 @@
 #include "lbm_device.hpp"
 #include "lbm_kernels.hpp"
 #include "lbm_node.hpp"
+#include "lbm_popbuf.hpp"
 
 namespace lbm {
-
-// Populations of one run through a buffer descriptor: a 32-bit byte offset per
-// lane plus a scalar one per direction, so that a load or store takes no
-// address arithmetic in vector registers (the run's block is below 4 GiB).
-template <typename S> struct PopBuf {
-    __amdgpu_buffer_rsrc_t rsrc;
-    __device__ __forceinline__ explicit PopBuf(const S *base)
-        : rsrc(__builtin_amdgcn_make_buffer_rsrc(const_cast<S *>(base), 0, -1, 0x00020000))
-    {
-    }
-    __device__ __forceinline__ S load(uint32_t lane, uint32_t uni) const
-    {
-        if constexpr (sizeof(S) == 4)
-            return __builtin_bit_cast(S, __builtin_amdgcn_raw_buffer_load_b32(rsrc, (int)lane, (int)uni, 0));
-        else
-            return __builtin_bit_cast(S, __builtin_amdgcn_raw_buffer_load_b64(rsrc, (int)lane, (int)uni, 0));
-    }
-    __device__ __forceinline__ void store(uint32_t lane, uint32_t uni, S v) const
-    {
-        if constexpr (sizeof(S) == 4)
-            __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned int, v), rsrc, (int)lane, (int)uni, 0);
-        else {
-            typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
-            __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, v), rsrc, (int)lane, (int)uni, 0);
-        }
-    }
-};
 
 // Geometry of a tile of TX x TY nodes advanced K steps: step s (1..K) collides
 // the tile and a margin of 2 (K - s) nodes around it, for which it needs psi
