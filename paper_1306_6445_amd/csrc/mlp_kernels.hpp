@@ -23,8 +23,7 @@ struct AdamArgs {
     int update;                          // 0: only reduce the gradient
 };
 
-int chunks(int n); // workgroups (chunks of samples) for a batch of n
-size_t smem_bytes();
+int chunks(int n); // workgroups (and gradient slots) for a batch of n
 hipError_t launch_forward(const float *th, const float *x, int n, float *y, hipStream_t st);
 hipError_t launch_weight_sum(const float *m, int n, float *inv, hipStream_t st);
 hipError_t launch_grad(const float *th, const float *x, const float *tg, const float *mw, int n, const float *inv,
