@@ -304,10 +304,10 @@ lbm_status lbm_set_tile(lbm_ctx *ctx, int32_t tx, int32_t ty);
  * the populations cross HBM once each way per step instead of being read
  * twice (bf16 storage: the writer densities of the previous step are staged
  * with the halo, and the tile writes its own for the next step).  With rows
- * > 0, FP64 or FP32 storage, no multi-range run and every run's populations
- * below 4 GiB, lbm_step advances two or four steps per launch from an even
- * step count while at least as many remain (tiles of the library's choice,
- * the intermediate states in LDS); tx, ty and rows then shape the remaining
+ * > 0, no multi-range run and every run's populations below 4 GiB, lbm_step
+ * advances two or four steps per launch from an even step count while at
+ * least as many remain (tiles of the library's choice, the intermediate
+ * states in LDS); tx, ty and rows then shape the remaining
  * single steps.  Every schedule gives the same bits.  Default: 2.
  * LBM_EINVAL for other values.  Drops any captured graph; synchronises. */
 lbm_status lbm_set_fused(lbm_ctx *ctx, int32_t rows);

@@ -129,7 +129,7 @@ Layout make_layout(int nruns, const lbm_run_desc *runs, int prec)
     L.r1 = off;
     off = align256(off + rbytes);
     L.seed = off;
-    off = align256(off + 2 * sizeof(uint32_t));
+    off = align256(off + 4 * sizeof(uint32_t)); // one pair per population buffer
     L.runs = off;
     off = align256(off + sizeof(lbm::RunDev) * nruns);
     L.tiles = off;
@@ -220,13 +220,17 @@ struct lbm_ctx {
     int fused = 0;         // nodes per thread of the fused kernel (1, 2, 4); 0: psi + collide in place
                            // (2 at creation)
     int halo = 1;          // psi halo of the collide tile: 2 once a run uses the multi-range force
-    int cur = 0;           // population buffer holding the current state (0: L.f, 1: L.f2)
-    hipGraphExec_t graph[2] = {nullptr, nullptr}; // 2k steps from population buffer 0 / 1
-    int graph_swap = 0;    // 1: a replay ends on the other buffer than it started from
+    int cur = 0;           // population buffer holding the current state (0: L.f, 1: L.f2), and its rounding seeds
+    int rflip = 0;         // bf16 storage: 1 when the writer densities R0, R1 have changed places (L.r1, L.r0)
+    hipGraphExec_t graph[4] = {};  // 2k steps from population buffer `cur` with the writer densities `rflip`
+    int graph_cur = 0, graph_rflip = 0; // 1: a replay ends on the other buffer / flip than it started from
     bool graph_failed = false;
 
     template <typename T> T *at(size_t off) { return reinterpret_cast<T *>(ws + off); }
     unsigned char *fbuf(int k) { return ws + (k ? L.f2 : L.f); }
+    float *rbuf(int k) { return at<float>(k ^ rflip ? L.r1 : L.r0); } // writer densities R[k]
+    uint32_t *seeds(int buf) { return at<uint32_t>(L.seed) + 2 * buf; }
+    hipGraphExec_t &exec() { return graph[2 * rflip + cur]; }
 
     lbm::StepArgs step_args()
     {
@@ -252,10 +256,11 @@ struct lbm_ctx {
             a.nmtiles = (int)lbm::multi_tiles(mshape, desc[0].grid.nx, desc[0].grid.ny);
         }
         if (precision == LBM_FP32_BF16STORE) {
-            a.r0 = at<float>(L.r0);
-            a.r1 = at<float>(L.r1);
+            a.r0 = rbuf(0);
+            a.r1 = rbuf(1);
         }
-        a.seed = at<uint32_t>(L.seed);
+        a.seed = seeds(cur);
+        a.seed_alt = seeds(cur ^ 1);
         a.halo = halo;
         return a;
     }
@@ -266,11 +271,11 @@ struct lbm_ctx {
 namespace {
 
 // Variant of the multi-step kernel, -1 for single steps only: it needs the
-// second population buffer (fused schedule), the single-range force, FP64 or
-// FP32 storage, and run blocks that a 32-bit byte offset spans.
+// second population buffer (fused schedule), the single-range force, and run
+// blocks that a 32-bit byte offset spans.
 int multi_variant(const lbm_ctx *c)
 {
-    if (!c->fused || c->single_steps || c->halo != 1 || c->precision == LBM_FP32_BF16STORE) return -1;
+    if (!c->fused || c->single_steps || c->halo != 1) return -1;
     for (const lbm::RunDev &r : c->rdev)
         if ((uint64_t)r.dstride * 9 * pop_bytes(c->precision) >= (uint64_t)1 << 32) return -1;
     return lbm::pick_multi(kernel_precision(c->precision), c->rdev.data(), c->nruns);
@@ -393,8 +398,8 @@ lbm_status util(lbm_ctx *c, int op, int run, double *buf, const double *ux = nul
     u.parity = c->parity();
     u.stream = c->stream;
     if (c->precision == LBM_FP32_BF16STORE) {
-        u.r0 = c->at<float>(c->L.r0);
-        u.r1 = c->at<float>(c->L.r1);
+        u.r0 = c->rbuf(0);
+        u.r1 = c->rbuf(1);
     }
     LBM_HIP(lbm::launch_util(kernel_precision(c->precision), u));
     return LBM_OK;
@@ -408,7 +413,7 @@ lbm_status reset_seed(lbm_ctx *c, int64_t steps)
     uint32_t w[2];
     w[steps & 1] = v[0];       // not read before it is rewritten
     w[(steps & 1) ^ 1] = v[1]; // the last step's seed
-    LBM_HIP(hipMemcpyAsync(c->ws + c->L.seed, w, sizeof(w), hipMemcpyHostToDevice, c->stream));
+    LBM_HIP(hipMemcpyAsync(c->seeds(c->cur), w, sizeof(w), hipMemcpyHostToDevice, c->stream));
     LBM_HIP(hipStreamSynchronize(c->stream));
     return LBM_OK;
 }
@@ -430,8 +435,9 @@ lbm_status read_status(lbm_ctx *c, std::vector<int32_t> &st)
 
 // One launch: the steps of the multi-step kernel from an even step count when
 // at least that many remain, else one step.  A fused or multi-step launch
-// leaves the state in the other buffer (swapped in `a`); `taken` receives the
-// number of steps.
+// leaves the state in the other buffer, a multi-step one of bf16 storage the
+// writer densities in the other array (swapped in `a`; moved() is the same for
+// the context); `taken` receives the number of steps.
 hipError_t launch_some(const lbm_ctx *c, lbm::StepArgs &a, int parity, int64_t left, int64_t *taken)
 {
     const int prec = kernel_precision(c->precision);
@@ -440,8 +446,19 @@ hipError_t launch_some(const lbm_ctx *c, lbm::StepArgs &a, int parity, int64_t l
                          : c->fused ? lbm::launch_fused(prec, a, parity)
                                     : lbm::launch_step(prec, a, parity);
     *taken = multi ? c->mshape.steps : 1;
-    if (c->fused) std::swap(a.f, a.f_alt);
+    if (c->fused) {
+        std::swap(a.f, a.f_alt);
+        std::swap(a.seed, a.seed_alt);
+    }
+    if (multi) std::swap(a.r0, a.r1);
     return e;
+}
+
+void moved(lbm_ctx *c, int64_t taken)
+{
+    if (c->fused) c->cur ^= 1;
+    if (taken > 1 && c->precision == LBM_FP32_BF16STORE) c->rflip ^= 1;
+    c->steps += taken;
 }
 
 lbm_status step_eager(lbm_ctx *c, int64_t n)
@@ -450,16 +467,16 @@ lbm_status step_eager(lbm_ctx *c, int64_t n)
     while (n > 0) {
         int64_t taken = 0;
         LBM_HIP(launch_some(c, a, c->parity(), n, &taken));
-        c->steps += taken;
+        moved(c, taken);
         n -= taken;
-        if (c->fused) c->cur ^= 1;
     }
     return LBM_OK;
 }
 
 lbm_status build_graph(lbm_ctx *c)
 {
-    lbm::StepArgs a = c->step_args();
+    const lbm::StepArgs start = c->step_args();
+    lbm::StepArgs a = start;
     hipGraph_t g = nullptr;
     if (hipStreamBeginCapture(c->stream, hipStreamCaptureModeRelaxed) != hipSuccess) {
         (void)hipGetLastError();
@@ -470,8 +487,9 @@ lbm_status build_graph(lbm_ctx *c)
     hipError_t e = hipSuccess;
     for (int64_t i = 0, taken = 0; i < 2 * (int64_t)c->graph_k && e == hipSuccess; i += taken)
         e = launch_some(c, a, (int)(i & 1), 2 * (int64_t)c->graph_k - i, &taken);
-    c->graph_swap = a.f != c->fbuf(c->cur);
-    hipGraphExec_t &exec = c->graph[c->cur];
+    c->graph_cur = a.f != c->fbuf(c->cur);
+    c->graph_rflip = a.r0 != start.r0;
+    hipGraphExec_t &exec = c->exec();
     hipError_t e2 = hipStreamEndCapture(c->stream, &g);
     if (e != hipSuccess || e2 != hipSuccess || !g) {
         if (g) (void)hipGraphDestroy(g);
@@ -709,12 +727,13 @@ lbm_status lbm_step(lbm_ctx *ctx, int64_t n)
             if (s != LBM_OK) return s;
         }
         while (n >= block && !ctx->graph_failed) {
-            if (!ctx->graph[ctx->cur]) {
+            if (!ctx->exec()) {
                 if ((s = build_graph(ctx)) != LBM_OK) return s;
                 continue;
             }
-            LBM_HIP(hipGraphLaunch(ctx->graph[ctx->cur], ctx->stream));
-            ctx->cur ^= ctx->graph_swap;
+            LBM_HIP(hipGraphLaunch(ctx->exec(), ctx->stream));
+            ctx->cur ^= ctx->graph_cur;
+            ctx->rflip ^= ctx->graph_rflip;
             ctx->steps += block;
             n -= block;
         }
@@ -764,8 +783,8 @@ lbm_status lbm_run_density_column(lbm_ctx *ctx, int32_t run, int32_t x, double *
     u.index = x;
     u.stream = ctx->stream;
     if (ctx->precision == LBM_FP32_BF16STORE) {
-        u.r0 = ctx->at<float>(ctx->L.r0);
-        u.r1 = ctx->at<float>(ctx->L.r1);
+        u.r0 = ctx->rbuf(0);
+        u.r1 = ctx->rbuf(1);
     }
     LBM_HIP(lbm::launch_util(kernel_precision(ctx->precision), u));
     LBM_HIP(hipMemcpyAsync(rho, st, sizeof(double) * ny, hipMemcpyDeviceToHost, ctx->stream));
@@ -810,8 +829,8 @@ lbm_status lbm_run_get_window(lbm_ctx *ctx, int32_t run, int32_t x0, int32_t y0,
     u.wh = h;
     u.stream = ctx->stream;
     if (ctx->precision == LBM_FP32_BF16STORE) {
-        u.r0 = ctx->at<float>(ctx->L.r0);
-        u.r1 = ctx->at<float>(ctx->L.r1);
+        u.r0 = ctx->rbuf(0);
+        u.r1 = ctx->rbuf(1);
     }
     LBM_HIP(lbm::launch_util(kernel_precision(ctx->precision), u));
     LBM_HIP(hipMemcpyAsync(f, st, sizeof(double) * 9 * (size_t)w * h, hipMemcpyDeviceToHost, ctx->stream));
@@ -1051,10 +1070,9 @@ lbm_status lbm_save_state(lbm_ctx *ctx, void *host_buf, size_t bytes)
         // the current state decodes with R[parity ^ 1]; the last seed sits in slot parity ^ 1
         const int last = ctx->parity() ^ 1;
         const size_t rb = sizeof(float) * (size_t)ctx->L.total_nodes;
-        LBM_HIP(hipMemcpyAsync(q + pb, ctx->ws + (last ? ctx->L.r1 : ctx->L.r0), rb, hipMemcpyDeviceToHost,
+        LBM_HIP(hipMemcpyAsync(q + pb, ctx->rbuf(last), rb, hipMemcpyDeviceToHost, ctx->stream));
+        LBM_HIP(hipMemcpyAsync(q + pb + rb, ctx->seeds(ctx->cur) + last, sizeof(uint32_t), hipMemcpyDeviceToHost,
                                ctx->stream));
-        LBM_HIP(hipMemcpyAsync(q + pb + rb, ctx->ws + ctx->L.seed + sizeof(uint32_t) * last, sizeof(uint32_t),
-                               hipMemcpyDeviceToHost, ctx->stream));
     }
     LBM_HIP(hipStreamSynchronize(ctx->stream));
     return LBM_OK;
@@ -1091,10 +1109,9 @@ lbm_status lbm_load_state(lbm_ctx *ctx, const void *host_buf, size_t bytes)
         // the writer densities decode the current state; the last seed sits in slot parity ^ 1
         const int last = ctx->parity() ^ 1;
         const size_t rb = sizeof(float) * (size_t)ctx->L.total_nodes;
-        LBM_HIP(hipMemcpyAsync(ctx->ws + (last ? ctx->L.r1 : ctx->L.r0), q + pb, rb, hipMemcpyHostToDevice,
+        LBM_HIP(hipMemcpyAsync(ctx->rbuf(last), q + pb, rb, hipMemcpyHostToDevice, ctx->stream));
+        LBM_HIP(hipMemcpyAsync(ctx->seeds(ctx->cur) + last, q + pb + rb, sizeof(uint32_t), hipMemcpyHostToDevice,
                                ctx->stream));
-        LBM_HIP(hipMemcpyAsync(ctx->ws + ctx->L.seed + sizeof(uint32_t) * last, q + pb + rb, sizeof(uint32_t),
-                               hipMemcpyHostToDevice, ctx->stream));
     }
     LBM_HIP(hipMemsetAsync(ctx->ws + ctx->L.status, 0, sizeof(int32_t) * ctx->nruns, ctx->stream));
     LBM_HIP(hipStreamSynchronize(ctx->stream));
@@ -1164,7 +1181,6 @@ lbm_status lbm_time_kernels(lbm_ctx *ctx, int64_t n, double *psi_ms, double *col
                 a.ev_start = ev[4 * i + 2];
                 a.ev_stop = ev[4 * i + 3];
                 if (e == hipSuccess) e = launch_some(ctx, a, par, left, &taken);
-                if (e == hipSuccess) ctx->cur ^= 1;
             } else {
                 a.ev_start = ev[4 * i];
                 a.ev_stop = ev[4 * i + 1];
@@ -1173,7 +1189,7 @@ lbm_status lbm_time_kernels(lbm_ctx *ctx, int64_t n, double *psi_ms, double *col
                 a.ev_stop = ev[4 * i + 3];
                 if (e == hipSuccess) e = lbm::launch_collide(prec, a, par);
             }
-            if (e == hipSuccess) ctx->steps += taken;
+            if (e == hipSuccess) moved(ctx, taken);
             left -= taken;
         }
         if (e == hipSuccess) e = hipStreamSynchronize(ctx->stream);

@@ -161,6 +161,17 @@ template <> struct Store<bf16_t> {
     {
         p[i].bits = float_to_bf16_sr(v - (float)rest_weight(A) * ref, r16);
     }
+    // The same bits with gfx950's stochastic-rounding conversion, which adds
+    // the top 16 bits of its random operand below the kept ones.  In kernels
+    // with registers to spare: 50 fewer instructions a node in the single-step
+    // kernel, but five more registers and a wave per SIMD less there.
+    template <int A> __device__ static __forceinline__ bf16_t encode_sr_hw(float v, float ref, uint32_t r)
+    {
+        typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+        const bf16x2 zero = {0, 0};
+        const bf16x2 q = __builtin_amdgcn_cvt_sr_bf16_f32(zero, v - (float)rest_weight(A) * ref, r, false);
+        return bf16_t{(uint16_t)__builtin_bit_cast(uint32_t, q)};
+    }
 };
 
 // Storage whose base density is the writer's density (one FP32 density array

@@ -467,7 +467,8 @@ __global__ void __launch_bounds__(kMaxTileThreads) fused_kernel(const RunDev *__
                                                     const S *__restrict__ src, S *__restrict__ dst,
                                                     int32_t *__restrict__ status, int xcd,
                                                     const float *__restrict__ rprev, float *__restrict__ rcur,
-                                                    uint32_t *__restrict__ seed)
+                                                    const uint32_t *__restrict__ seed,
+                                                    uint32_t *__restrict__ seed_out)
 {
     using C = typename Store<S>::C;
     extern __shared__ unsigned char lds_raw[];
@@ -484,9 +485,9 @@ __global__ void __launch_bounds__(kMaxTileThreads) fused_kernel(const RunDev *__
     uint32_t sd = 0;
     if constexpr (kWriterRef<S>) {
         // rounding seed of this step: one more than the last step's (the
-        // value psi_kernel would write; no workgroup reads slot PARITY here)
+        // value psi_kernel would write), to the pair of the next state
         sd = seed[PARITY ^ 1] + 1u;
-        if (blockIdx.x == 0 && threadIdx.x == 0 && threadIdx.y == 0) seed[PARITY] = sd;
+        if (blockIdx.x == 0 && threadIdx.x == 0 && threadIdx.y == 0) seed_out[PARITY] = sd;
         stage_tile<float>(rtile, rprev + r.n_off, t.x0, t.y0, TX, TYR, H + 1, r);
         __syncthreads();
     }
@@ -898,10 +899,12 @@ hipError_t launch_fused_hr(const StepArgs &a, int parity)
     float *rcur = parity ? a.r1 : a.r0;
     if (parity == 0)
         hipExtLaunchKernelGGL(fused_kernel<S, 0, H, R>, dim3(a.nftiles), block, lds, a.stream, a.ev_start,
-                              a.ev_stop, 0, a.runs, a.ftiles, src, dst, a.status, a.xcd, rprev, rcur, a.seed);
+                              a.ev_stop, 0, a.runs, a.ftiles, src, dst, a.status, a.xcd, rprev, rcur, a.seed,
+                              a.seed_alt);
     else
         hipExtLaunchKernelGGL(fused_kernel<S, 1, H, R>, dim3(a.nftiles), block, lds, a.stream, a.ev_start,
-                              a.ev_stop, 0, a.runs, a.ftiles, src, dst, a.status, a.xcd, rprev, rcur, a.seed);
+                              a.ev_stop, 0, a.runs, a.ftiles, src, dst, a.status, a.xcd, rprev, rcur, a.seed,
+                              a.seed_alt);
     return hipGetLastError();
 }
 
@@ -919,7 +922,7 @@ hipError_t launch_fused_h(const StepArgs &a, int parity)
 template <typename S>
 hipError_t launch_fused_t(const StepArgs &a, int parity)
 {
-    if (!a.f_alt || !a.ftiles || (kWriterRef<S> && (!a.r0 || !a.r1 || !a.seed))) return hipErrorInvalidValue;
+    if (!a.f_alt || !a.ftiles || (kWriterRef<S> && (!a.r0 || !a.r1 || !a.seed || !a.seed_alt))) return hipErrorInvalidValue;
     return a.halo == 1 ? launch_fused_h<S, 1>(a, parity) : launch_fused_h<S, 2>(a, parity);
 }
 

@@ -36,7 +36,9 @@ struct StepArgs {
     int mntx = 0;                   // > 0: one run, its tiles in row-major order, mntx to a row (no list read)
     float *r0 = nullptr;            // writer densities of bf16 storage: a step of parity p
     float *r1 = nullptr;            // reads R[p ^ 1] and writes R[p] (r0 = R[0], r1 = R[1])
-    uint32_t *seed = nullptr;       // rounding-seed counter pair, slot p written by step p
+    uint32_t *seed = nullptr;       // rounding-seed counter pair of the current state, slot p of the last step
+                                    // of parity p; a fused or multi-step launch writes the pair seed_alt
+    uint32_t *seed_alt = nullptr;
     int halo = 1;                   // psi halo of the collide tile: 2 when a run uses Eq. (9)
     hipEvent_t ev_start = nullptr;  // optional events around a single launch
     hipEvent_t ev_stop = nullptr;
@@ -79,7 +81,8 @@ inline int64_t multi_tiles(const MultiShape &s, int nx, int ny)
 bool multi_shape(int precision, int v, MultiShape &s);
 // The variant for these runs; -1 when the precision has none.
 int pick_multi(int precision, const RunDev *runs, int nruns);
-// From an even step count: f -> f_alt, shape.steps steps later.
+// From an even step count: f -> f_alt, shape.steps steps later (bf16 storage:
+// r1 -> r0 and seed -> seed_alt, whose roles the caller then swaps).
 hipError_t launch_multi(int precision, int v, const StepArgs &a);
 hipError_t launch_copy(void *dst, const void *src, size_t bytes, hipStream_t stream);
 hipError_t launch_psi(int precision, const StepArgs &a, int parity);

@@ -1,4 +1,4 @@
-// Several D2Q9 steps in one launch (FP64 and FP32 storage, single-range force):
+// Several D2Q9 steps in one launch (every storage, single-range force):
 // multi_kernel reads the populations of an even step count, advances its tile
 // K steps with the intermediate states in LDS and writes the state K steps
 // later, in the same layout, to the other buffer.
@@ -13,12 +13,14 @@
 // (82 B per node and 2 steps in FP32 by the counters) and the kernel is bound by
 // vector instruction issue: 380 a node and step, the vector units 93% busy.
 // The intermediate state passes through LDS in its storage form (FP32
-// deviations), so that K steps in one launch and K launches give the same bits.
+// deviations; bf16 with its writer densities and rounding bits), so that K steps
+// in one launch and K launches give the same bits.
 //
 // Measured against one step per launch (us per step): 4096 x 2048 FP32 142 ->
 // 88, FP64 261 -> 172; 40 x 256^2 FP32 32.7 -> 25.1, FP64 87 -> 57; 64 uneven
 // drops FP32 128 -> 77; 2048 x 1024 with walls FP32 27.8 -> 21; 100^2 FP64 6.0 ->
-// 2.2; 256 grids of 4 x 256 FP32 38 -> 5.9.
+// 2.2; 256 grids of 4 x 256 FP32 38 -> 5.9; 40 x 256^2 bf16 40.9 -> 32.1, 64
+// uneven drops bf16 125 -> 93.
 #include <hip/hip_ext.h>
 
 #include "lbm_device.hpp"
@@ -35,6 +37,7 @@ template <int K, int TX, int TY> struct MultiGeom {
     static constexpr int M = 2 * (K - 1);                       // margin of the first step
     static constexpr int FX = TX + 2 * M, FY = TY + 2 * M, FN = FX * FY; // LDS populations
     static constexpr int PX = FX + 2, PN = PX * (FY + 2);       // LDS psi
+    static constexpr int RX = FX + 4, RN = RX * (FY + 4);       // LDS writer densities (bf16 storage)
     static constexpr int w(int s) { return TX + 4 * (K - s); }
     static constexpr int h(int s) { return TY + 4 * (K - s); }
     static constexpr int cells(int s) { return w(s) * h(s); }
@@ -73,15 +76,45 @@ struct MultiTile {
     const PopBuf<S> in, out;
     C *psi;
     S *pop;
+    // bf16 storage: the writer densities that decode the current state (of the
+    // previous step's nodes; a colliding node replaces its own), the array of
+    // the last step's densities, the first step's rounding seed, the run's
+    // first node (for the rounding hash)
+    float *wr;
+    float *rlast;
+    uint32_t seed;
+    int64_t n_off;
     bool bad = false;
 
-    template <int A> __device__ __forceinline__ C decode(S v) const { return Store<S>::template load<A>(&v, 0, k.rho_ref); }
-    template <int A> __device__ __forceinline__ S encode(C v) const
+    template <int A> __device__ __forceinline__ C decode(S v, C base) const { return Store<S>::template load<A>(&v, 0, base); }
+    // hb: the node's rounding bits, advanced once per population
+    template <int A> __device__ __forceinline__ S encode(C v, C base, uint32_t &hb) const
     {
-        S r;
-        Store<S>::template store<A>(&r, 0, v, k.rho_ref);
-        return r;
+        if constexpr (kWriterRef<S>) {
+            hb = hb * 747796405u + 2891336453u;
+            return Store<S>::template encode_sr_hw<A>(v, base, hb);
+        } else {
+            S r;
+            Store<S>::template store<A>(&r, 0, v, base);
+            return r;
+        }
     }
+    __device__ __forceinline__ static int wcell(int dx, int dy) { return (dy + Gm::M + 2) * Gm::RX + dx + Gm::M + 2; }
+    // base density of f_a of the item's node: its writer's (x - e_a, or x across a wall), or the run's constant
+    template <int A> __device__ __forceinline__ C base_of(int wc, bool wall) const
+    {
+        if constexpr (kWriterRef<S>)
+            return C(wr[wall ? wc : wc - (ey_of(A) * Gm::RX + ex_of(A))]);
+        else
+            return k.rho_ref;
+    }
+    template <int A> struct Up {
+        static __device__ __forceinline__ bool wall(const bool *w) // wxm, wxp, wym, wyp
+        {
+            constexpr int ex = ex_of(A), ey = ey_of(A);
+            return (ex > 0 && w[0]) || (ex < 0 && w[1]) || (ey > 0 && w[2]) || (ey < 0 && w[3]);
+        }
+    };
     // the node an item stands for: wrapped on periodic axes (global), clamped across walls
     __device__ __forceinline__ int wrap_x(int x) const { return MODE == kMInner ? x : psi_coord(x, nx, MODE == kMPeriodic ? BC_PERIODIC : bcx); }
     __device__ __forceinline__ int wrap_y(int y) const { return MODE == kMInner ? y : psi_coord(y, ny, MODE == kMPeriodic ? BC_PERIODIC : bcy); }
@@ -89,31 +122,39 @@ struct MultiTile {
     struct LoadG {
         const MultiTile &t;
         uint32_t off;
+        int wc;
+        bool w[4];
         C *f;
-        template <int A> __device__ __forceinline__ void operator()() { f[A] = t.template decode<A>(t.in.load(off, A * t.ds)); }
+        template <int A> __device__ __forceinline__ void operator()()
+        {
+            const bool wall = MODE == kMGeneral && kWriterRef<S> && Up<A>::wall(w);
+            f[A] = t.template decode<A>(t.in.load(off, A * t.ds), t.template base_of<A>(wc, wall));
+        }
     };
     // f_a(x) of an intermediate state: f*_a(x - e_a), or f*_opp(a)(x) across a wall
     struct LoadL {
         const MultiTile &t;
-        int cell; // of the item's node
-        bool wxm, wxp, wym, wyp;
+        int cell, wc; // of the item's node
+        bool w[4];
         C *f;
         template <int A> __device__ __forceinline__ void operator()()
         {
             constexpr int ex = ex_of(A), ey = ey_of(A);
-            int i = A * Gm::FN + cell - (ey * Gm::FX + ex);
-            if constexpr (MODE == kMGeneral && A > 0) {
-                const bool wall = (ex > 0 && wxm) || (ex < 0 && wxp) || (ey > 0 && wym) || (ey < 0 && wyp);
-                i = wall ? opp_of(A) * Gm::FN + cell : i;
-            }
-            f[A] = t.template decode<A>(t.pop[i]);
+            const bool wall = MODE == kMGeneral && Up<A>::wall(w);
+            const int i = wall ? opp_of(A) * Gm::FN + cell : A * Gm::FN + cell - (ey * Gm::FX + ex);
+            f[A] = t.template decode<A>(t.pop[i], t.template base_of<A>(wc, wall));
         }
     };
     struct StoreL {
         const MultiTile &t;
         int cell;
         const C *f;
-        template <int A> __device__ __forceinline__ void operator()() { t.pop[A * Gm::FN + cell] = t.template encode<A>(f[A]); }
+        C base;
+        uint32_t hb;
+        template <int A> __device__ __forceinline__ void operator()()
+        {
+            t.pop[A * Gm::FN + cell] = t.template encode<A>(f[A], base, hb);
+        }
     };
     // f*_a(x) to slot a of x + e_a, or slot opp(a) of x across a wall (the even-state layout)
     struct StoreG {
@@ -121,10 +162,12 @@ struct MultiTile {
         uint32_t xo[3], yo[3]; // byte offsets of x - 1, x, x + 1 and of rows y - 1, y, y + 1
         bool wxm, wxp, wym, wyp;
         const C *f;
+        C base;
+        uint32_t hb;
         template <int A> __device__ __forceinline__ void operator()()
         {
             constexpr int ex = ex_of(A), ey = ey_of(A);
-            const S v = t.template encode<A>(f[A]);
+            const S v = t.template encode<A>(f[A], base, hb);
             if constexpr (MODE == kMInner) {
                 t.out.store(xo[1], A * t.ds + (uint32_t)((ey * t.ld + ex) * (int)sizeof(S)), v);
             } else if constexpr (MODE == kMPeriodic || A == 0) {
@@ -139,18 +182,19 @@ struct MultiTile {
     template <int s> __device__ __forceinline__ void load(int dx, int dy, C *f) const
     {
         const int gx = wrap_x(x0 + dx), gy = wrap_y(y0 + dy);
+        // LDS cell: unwrapped on a periodic axis, the clamped node's across a wall
+        int cx = dx, cy = dy;
+        bool w[4] = {false, false, false, false};
+        if constexpr (MODE == kMGeneral) {
+            if (bcx == BC_WALL) cx = gx - x0, w[0] = gx == 0, w[1] = gx == nx - 1;
+            if (bcy == BC_WALL) cy = gy - y0, w[2] = gy == 0, w[3] = gy == ny - 1;
+        }
+        const int wc = wcell(cx, cy);
         if constexpr (s == 1) {
-            LoadG op{*this, (uint32_t)(gy * ld + gx) * (uint32_t)sizeof(S), f};
+            LoadG op{*this, (uint32_t)(gy * ld + gx) * (uint32_t)sizeof(S), wc, {w[0], w[1], w[2], w[3]}, f};
             for9(op);
         } else {
-            // LDS cell: unwrapped on a periodic axis, the clamped node's across a wall
-            int cx = dx, cy = dy;
-            bool wxm = false, wxp = false, wym = false, wyp = false;
-            if constexpr (MODE == kMGeneral) {
-                if (bcx == BC_WALL) cx = gx - x0, wxm = gx == 0, wxp = gx == nx - 1;
-                if (bcy == BC_WALL) cy = gy - y0, wym = gy == 0, wyp = gy == ny - 1;
-            }
-            LoadL op{*this, (cy + Gm::M) * Gm::FX + cx + Gm::M, wxm, wxp, wym, wyp, f};
+            LoadL op{*this, (cy + Gm::M) * Gm::FX + cx + Gm::M, wc, {w[0], w[1], w[2], w[3]}, f};
             for9(op);
         }
     }
@@ -193,14 +237,25 @@ struct MultiTile {
                 const int dx = lx - 2 * (K - s), dy = ly - 2 * (K - s);
                 C fs[9];
                 collide_node<C>(k, fv[j], rho[j], psi + (dy + Gm::M + 1) * Gm::PX + dx + Gm::M + 1, Gm::PX, fs);
+                // bf16 storage: this node's density is the base of what it writes, rounded stochastically
+                C base = k.rho_ref;
+                uint32_t hb = 0;
+                int64_t gi = 0;
+                if constexpr (kWriterRef<S>) {
+                    base = rho[j];
+                    gi = n_off + (int64_t)wrap_y(y0 + dy) * ld + wrap_x(x0 + dx);
+                    hb = fmix32((uint32_t)gi ^ fmix32(seed + (s - 1)));
+                }
                 if constexpr (s < K) {
-                    StoreL op{*this, (dy + Gm::M) * Gm::FX + dx + Gm::M, fs};
+                    if constexpr (kWriterRef<S>) wr[wcell(dx, dy)] = (float)rho[j];
+                    StoreL op{*this, (dy + Gm::M) * Gm::FX + dx + Gm::M, fs, base, hb};
                     for9(op);
                 } else {
                     const int x = x0 + dx, y = y0 + dy;
                     if (MODE == kMInner || (x < nx && y < ny)) {
                         constexpr uint32_t z = sizeof(S);
-                        StoreG op{*this, {}, {}, false, false, false, false, fs};
+                        if constexpr (kWriterRef<S>) rlast[gi] = (float)rho[j];
+                        StoreG op{*this, {}, {}, false, false, false, false, fs, base, hb};
                         if constexpr (MODE == kMInner) {
                             op.xo[1] = (uint32_t)(y * ld + x) * z;
                         } else {
@@ -222,41 +277,71 @@ struct MultiTile {
     }
 };
 
-template <typename S, int K, int TX, int TY, int NT, int MODE>
-__device__ __forceinline__ bool multi_tile(const RunDev &r, const Tile &t, const S *src, S *dst, unsigned char *lds)
-{
-    using C = typename Store<S>::C;
+// LDS of a tile: psi, the intermediate populations, the writer densities.
+template <typename S, int K, int TX, int TY> struct MultiLds {
     using Gm = MultiGeom<K, TX, TY>;
-    MultiTile<S, K, TX, TY, NT, MODE> m{r.template par<C>(), r.eos_kind, r.nx, r.ny, r.pitch, r.bc_x, r.bc_y, t.x0, t.y0,
-                                       (uint32_t)r.dstride * (uint32_t)sizeof(S), PopBuf<S>(src), PopBuf<S>(dst),
-                                       reinterpret_cast<C *>(lds), reinterpret_cast<S *>(lds + sizeof(C) * Gm::PN)};
+    typename Store<S>::C psi[Gm::PN];
+    float wr[kWriterRef<S> ? Gm::RN : 1];
+    S pop[9 * Gm::FN];
+};
+
+template <typename S, int K, int TX, int TY, int NT, int MODE>
+__device__ __forceinline__ bool multi_tile(const RunDev &r, const Tile &t, const S *src, S *dst,
+                                           MultiLds<S, K, TX, TY> &lds, float *rlast, uint32_t seed)
+{
+    MultiTile<S, K, TX, TY, NT, MODE> m{r.template par<typename Store<S>::C>(), r.eos_kind, r.nx, r.ny, r.pitch, r.bc_x,
+                                       r.bc_y, t.x0, t.y0, (uint32_t)r.dstride * (uint32_t)sizeof(S), PopBuf<S>(src),
+                                       PopBuf<S>(dst), lds.psi, lds.pop, lds.wr, rlast, seed, r.n_off};
     m.template step<1>((int)threadIdx.x);
     return m.bad;
 }
 
-// Grid: one workgroup per tile of the list, or of the one run (ntx tiles to a row).
+// Grid: one workgroup per tile of the list, or of the one run (ntx tiles to a
+// row).  bf16 storage: rprev holds the densities of the last step, rlast
+// receives those of this launch's last step; seeds holds the rounding seeds
+// of the last even and odd step, seeds_out receives this launch's (other
+// arrays, because every workgroup reads the old ones).
 template <typename S, int K, int TX, int TY, int NT>
 __global__ void __launch_bounds__(NT) multi_kernel(const RunDev *__restrict__ runs, const Tile *__restrict__ tiles, int ntx,
                                               const S *__restrict__ src, S *__restrict__ dst,
-                                              int32_t *__restrict__ status, int xcd)
+                                              int32_t *__restrict__ status, int xcd, const float *__restrict__ rprev,
+                                              float *__restrict__ rlast, const uint32_t *__restrict__ seeds,
+                                              uint32_t *__restrict__ seeds_out)
 {
     static_assert(K % 2 == 0, "the state returns to the layout of an even step count");
-    using C = typename Store<S>::C;
     using Gm = MultiGeom<K, TX, TY>;
-    __shared__ __align__(16) unsigned char lds[sizeof(C) * Gm::PN + sizeof(S) * 9 * Gm::FN];
+    __shared__ __align__(16) MultiLds<S, K, TX, TY> lds;
     const int wi = work_index(xcd);
     // one run: the tile follows from the work index (no dependent load of the list)
     const Tile t = ntx > 0 ? Tile{0, wi % ntx * TX, wi / ntx * TY, 0} : tiles[wi];
     const RunDev &r = runs[t.run];
+    uint32_t seed = 0;
+    if constexpr (kWriterRef<S>) {
+        seed = seeds[1] + 1u;
+        if (blockIdx.x == 0 && threadIdx.x == 0) {
+            seeds_out[0] = seed + (K - 2);
+            seeds_out[1] = seed + (K - 1);
+        }
+        const float *rp = rprev + r.n_off;
+        for (int i = threadIdx.x; i < Gm::RN; i += NT) {
+            const int ly = (unsigned)i / (unsigned)Gm::RX, lx = i - ly * Gm::RX;
+            const int gx = psi_coord(t.x0 + lx - (Gm::M + 2), r.nx, r.bc_x);
+            const int gy = psi_coord(t.y0 + ly - (Gm::M + 2), r.ny, r.bc_y);
+            lds.wr[i] = rp[(int64_t)gy * r.pitch + gx];
+        }
+        __syncthreads();
+    }
     constexpr int E = Gm::M + 2; // reach of the first step's loads and of the last step's stores
     const bool inner = t.x0 - E >= 0 && t.x0 + TX + E <= r.nx && t.y0 - E >= 0 && t.y0 + TY + E <= r.ny;
+    const S *in = src + r.f_off;
+    S *out = dst + r.f_off;
     bool bad;
     if (inner)
-        bad = multi_tile<S, K, TX, TY, NT, kMInner>(r, t, src + r.f_off, dst + r.f_off, lds);
+        bad = multi_tile<S, K, TX, TY, NT, kMInner>(r, t, in, out, lds, rlast, seed);
     else if (r.bc_x == BC_PERIODIC && r.bc_y == BC_PERIODIC)
-        bad = multi_tile<S, K, TX, TY, NT, kMPeriodic>(r, t, src + r.f_off, dst + r.f_off, lds);
+        bad = multi_tile<S, K, TX, TY, NT, kMPeriodic>(r, t, in, out, lds, rlast, seed);
     else
-        bad = multi_tile<S, K, TX, TY, NT, kMGeneral>(r, t, src + r.f_off, dst + r.f_off, lds);
+        bad = multi_tile<S, K, TX, TY, NT, kMGeneral>(r, t, in, out, lds, rlast, seed);
     if (bad) status[t.run] = 1;
 }
 
@@ -271,7 +356,7 @@ template <typename S, int K, int TX, int TY, int NT> hipError_t launch_multi_t(c
 {
     hipExtLaunchKernelGGL((multi_kernel<S, K, TX, TY, NT>), dim3(a.nmtiles), dim3(NT), 0, a.stream, a.ev_start, a.ev_stop,
                           0, a.runs, a.mtiles, a.mntx, static_cast<const S *>(a.f), static_cast<S *>(a.f_alt), a.status,
-                          a.xcd);
+                          a.xcd, a.r1, a.r0, a.seed, a.seed_alt);
     return hipGetLastError();
 }
 
@@ -315,10 +400,20 @@ const Variant kF64[] = {
     make_variant<double, 2, 28, 20, 768>(0), make_variant<double, 2, 4, 60, 512>(0),
 };
 
+// bf16 storage spends its time on decoding and rounding (480 instructions a node
+// and step): 512 threads for 64 x 16 tiles measured 32.1 us on 40 x 256^2 drops
+// against 32.5 with 768 and 34.9 with 64 x 12 tiles.
+const Variant kBf16[] = {
+    make_variant<bf16_t, 4, 8, 8, 512>(256),   make_variant<bf16_t, 4, 20, 20, 1024>(256),
+    make_variant<bf16_t, 2, 28, 12, 512>(768), make_variant<bf16_t, 2, 64, 16, 512>(0),
+    make_variant<bf16_t, 2, 60, 12, 512>(0),   make_variant<bf16_t, 2, 4, 60, 512>(0),
+};
+
 const Variant *variant(int precision, int v)
 {
     if (precision == PREC_FP32) return v >= 0 && v < (int)(sizeof(kF32) / sizeof(kF32[0])) ? &kF32[v] : nullptr;
     if (precision == PREC_FP64) return v >= 0 && v < (int)(sizeof(kF64) / sizeof(kF64[0])) ? &kF64[v] : nullptr;
+    if (precision == PREC_BF16) return v >= 0 && v < (int)(sizeof(kBf16) / sizeof(kBf16[0])) ? &kBf16[v] : nullptr;
     return nullptr;
 }
 

@@ -21,7 +21,9 @@ template <typename S> struct PopBuf {
     __device__ __forceinline__ S load(uint32_t lane, uint32_t uni) const
     {
         uni = __builtin_amdgcn_readfirstlane(uni);
-        if constexpr (sizeof(S) == 4)
+        if constexpr (sizeof(S) == 2)
+            return __builtin_bit_cast(S, __builtin_amdgcn_raw_buffer_load_b16(rsrc, (int)lane, (int)uni, 0));
+        else if constexpr (sizeof(S) == 4)
             return __builtin_bit_cast(S, __builtin_amdgcn_raw_buffer_load_b32(rsrc, (int)lane, (int)uni, 0));
         else
             return __builtin_bit_cast(S, __builtin_amdgcn_raw_buffer_load_b64(rsrc, (int)lane, (int)uni, 0));
@@ -31,7 +33,9 @@ template <typename S> struct PopBuf {
     {
         constexpr int kAux = NT ? 2 : 0;
         uni = __builtin_amdgcn_readfirstlane(uni);
-        if constexpr (sizeof(S) == 4)
+        if constexpr (sizeof(S) == 2)
+            __builtin_amdgcn_raw_buffer_store_b16(__builtin_bit_cast(unsigned short, v), rsrc, (int)lane, (int)uni, kAux);
+        else if constexpr (sizeof(S) == 4)
             __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned int, v), rsrc, (int)lane, (int)uni, kAux);
         else {
             typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));

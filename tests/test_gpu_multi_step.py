@@ -2,10 +2,11 @@
 an MI355X).
 
 The multi-step kernel runs the collision of the single-step kernels on the same
-rounded states, so every population is equal.  The grids sit at the edges of its
+rounded states (bf16 storage: the same writer densities and rounding bits), so
+every population is equal.  The grids sit at the edges of its
 tiles: smaller than a tile's margin, one short of and one past a tile, several
 tiles of each variant (four steps of 8 x 8, 12 x 12 and 20 x 20 nodes; two of
-28 x 12, 64 x 16, 60 x 20, 4 x 60 and 8 x 60), walls on either axis, batches of
+28 x 12, 64 x 16, 60 x 12, 60 x 20, 4 x 60 and 8 x 60), walls on either axis, batches of
 uneven runs; step counts leave remainders and start at odd counts.
 """
 import dataclasses
@@ -57,14 +58,14 @@ SMALL = [(1, 1), (2, 3), (5, 1), (7, 9), (8, 8), (16, 17), (33, 25), (100, 61)]
 LARGE = [(240, 200), (257, 241), (640, 33), (1200, 500), (700, 641)]
 
 
-@pytest.mark.parametrize("precision", ["fp64", "fp32"])
+@pytest.mark.parametrize("precision", ["fp64", "fp32", "bf16"])
 @pytest.mark.parametrize("walls", [(0, 0), (1, 0), (0, 1), (1, 1)])
 @pytest.mark.parametrize("shape", SMALL + LARGE)
 def test_single_runs(shape, walls, precision):
     same([run(*shape, *walls)], precision, [1, 4, 9, 2])
 
 
-@pytest.mark.parametrize("precision", ["fp64", "fp32"])
+@pytest.mark.parametrize("precision", ["fp64", "fp32", "bf16"])
 @pytest.mark.parametrize("shapes", [[(9, 8), (64, 65), (20, 41)],
                                     [(256, 256)] * 20,
                                     [(4, 256)] * 150 + [(3, 61)],
@@ -75,18 +76,19 @@ def test_batches(shapes, precision):
     same(runs, precision, [2, 3, 4])
 
 
-@pytest.mark.parametrize("precision", ["fp64", "fp32"])
+@pytest.mark.parametrize("precision", ["fp64", "fp32", "bf16"])
 @pytest.mark.parametrize("eos", ["pw", "exp"])
 def test_other_equations_of_state(eos, precision):
     same([run(50, 40, 0, 1, eos), run(23, 60, 0, 0, eos)], precision, [4, 3])
 
 
 @pytest.mark.parametrize("graph_steps", [1, 3, 16])
+@pytest.mark.parametrize("precision", ["fp32", "bf16"])
 @pytest.mark.parametrize("shape", [(90, 70), (300, 520)])
-def test_graphs_from_either_buffer(shape, graph_steps):
+def test_graphs_from_either_buffer(shape, precision, graph_steps):
     """Replays whose number of launches is odd end on the other buffer; single
     steps between the replays change parity and buffer."""
-    same([run(*shape)], "fp32", [35, 1, 64, 7, 33], graph_steps)
+    same([run(*shape)], precision, [35, 1, 64, 7, 33], graph_steps)
 
 
 def test_divergence_inside_a_launch_is_flagged():
