@@ -76,9 +76,11 @@ lbm_status lbm_mc_create(const lbm_grid *grid, const lbm_mc_params *p, int32_t p
 lbm_status lbm_mc_init_density(lbm_mc_ctx *ctx, const double *rhoA, const double *rhoB, const double *ux,
                                const double *uy);
 
-/* Advance n >= 0 steps (one fused launch each), enqueued on the stream
- * (graph replays of 2k steps while at least 2k remain, see
- * lbm_mc_set_graph_steps; single launches for the rest). */
+/* Advance n >= 0 steps, enqueued on the stream (graph replays of 2k steps
+ * while at least 2k remain, see lbm_mc_set_graph_steps; launches for the
+ * rest).  Where each population buffer is below 4 GiB a launch advances two or
+ * four steps while at least as many remain (tiles of the library's choice, the
+ * intermediate states in LDS), otherwise one. */
 lbm_status lbm_mc_step(lbm_mc_ctx *ctx, int64_t n);
 
 /* Steps per HIP graph: lbm_mc_step replays a captured graph of 2k steps (k
@@ -114,7 +116,7 @@ lbm_status lbm_mc_load_state(lbm_mc_ctx *ctx, const void *host_buf, size_t bytes
 /* Diagnostics of a drop of A about (cx, cy) (see lbm_mc_diag).  Synchronises. */
 lbm_status lbm_mc_diagnostics(lbm_mc_ctx *ctx, double cx, double cy, double r_in, double r_out, lbm_mc_diag *out);
 
-/* Tile of the fused step: tx x ty threads (tx in {32, 64, 128, 256}, ty in
+/* Tile of the single fused step (see lbm_mc_step): tx x ty threads (tx in {32, 64, 128, 256}, ty in
  * {1, 2, 4, 8}, 64 <= tx ty <= 512), each with `rows` nodes (1, 2 or 4) ty
  * rows apart.  Every shape gives the same bits.  Default one row of 128 x 4
  * threads for FP32, of 64 x 8 for FP64. */
@@ -122,13 +124,13 @@ lbm_status lbm_mc_set_tile(lbm_mc_ctx *ctx, int32_t tx, int32_t ty, int32_t rows
 
 /* Tile autotuner: times `steps` (>= 1) steps of each of ten candidate tiles
  * (128 x 4, 64 x 8, 256 x 2, 64 x 4 with one row; 128 x 4, 64 x 4, 128 x 2,
- * 256 x 2, 64 x 8, 32 x 8 with two) on the context's own state, which
- * advances by (steps + 1) per candidate, and sets the fastest; the choice goes
+ * 256 x 2, 64 x 8, 32 x 8 with two), one step per launch, on the context's
+ * own state, which advances by (steps + 1) per candidate, and sets the fastest; the choice goes
  * to the non-NULL outputs.  Every tile gives the same bits.  Synchronises. */
 lbm_status lbm_mc_autotune(lbm_mc_ctx *ctx, int32_t steps, int32_t *tx, int32_t *ty, int32_t *rows);
 
 /* Advance n >= 1 steps with HIP events around each launch; mean milliseconds
- * per step kernel.  Synchronises. */
+ * of kernel time per step.  Synchronises. */
 lbm_status lbm_mc_time_kernels(lbm_mc_ctx *ctx, int64_t n, double *step_ms);
 
 int64_t lbm_mc_steps_taken(const lbm_mc_ctx *ctx);

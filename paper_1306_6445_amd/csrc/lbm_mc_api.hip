@@ -101,9 +101,12 @@ struct lbm_mc_ctx {
     int64_t steps = 0;
     int tx = 64, ty = 4, rows = 2;
     int graph_k = 8;                  // lbm_mc_step replays HIP graphs of 2 graph_k steps (0: eager)
-    int graph_cur = 0;                // buffer the captured graph starts from
-    hipGraphExec_t graph = nullptr;
+    hipGraphExec_t graph[2] = {};     // 2 graph_k steps from population buffer 0 / 1
+    int graph_swap = 0;               // 1: a replay ends on the other buffer than it started from
     bool graph_failed = false;
+    int multi = -1;                   // variant of the multi-step kernel; -1: single steps
+    lbm::MultiShape mshape{0, 0, 0};
+    bool single_steps = false;        // set while the autotuner times the single-step tiles
     int64_t nodes() const { return run.nodes; }
     unsigned char *fbuf(int k) { return ws + (k ? L.f2 : L.f); }
     lbmmc::RunMC *drun() { return reinterpret_cast<lbmmc::RunMC *>(ws + L.run); }
@@ -175,15 +178,29 @@ namespace {
 
 void drop_graph_mc(lbm_mc_ctx *c)
 {
-    if (c->graph) {
-        (void)hipGraphExecDestroy(c->graph);
-        c->graph = nullptr;
-    }
+    for (hipGraphExec_t &g : c->graph)
+        if (g) {
+            (void)hipGraphExecDestroy(g);
+            g = nullptr;
+        }
 }
 
-// Captures 2 graph_k steps with the current tile from the current buffer
-// (an even number, so the replay ends on the buffer it started from).  A
-// failed capture leaves eager stepping in place.
+// One launch of the multi-step kernel when at least its steps remain, else one
+// step; the buffers change places in `a`, `taken` receives the steps.
+hipError_t launch_some_mc(const lbm_mc_ctx *c, lbmmc::StepMCArgs &a, int64_t left, int64_t *taken)
+{
+    const bool multi = c->multi >= 0 && !c->single_steps && left >= c->mshape.steps;
+    const hipError_t e = multi ? lbmmc::launch_multi_mc(kprec(c->precision), c->multi, a)
+                               : lbmmc::launch_step_mc(kprec(c->precision), a);
+    *taken = multi ? c->mshape.steps : 1;
+    void *next_in = a.fout;
+    a.fout = const_cast<void *>(a.fin);
+    a.fin = next_in;
+    return e;
+}
+
+// Captures 2 graph_k steps from the current buffer.  A failed capture leaves
+// eager stepping in place.
 void build_graph_mc(lbm_mc_ctx *c)
 {
     hipGraph_t g = nullptr;
@@ -194,12 +211,10 @@ void build_graph_mc(lbm_mc_ctx *c)
     }
     lbmmc::StepMCArgs a = c->args();
     hipError_t e = hipSuccess;
-    for (int i = 0; i < 2 * c->graph_k && e == hipSuccess; ++i) {
-        e = lbmmc::launch_step_mc(kprec(c->precision), a);
-        void *next_in = a.fout; // the buffers alternate
-        a.fout = const_cast<void *>(a.fin);
-        a.fin = next_in;
-    }
+    for (int64_t left = 2 * (int64_t)c->graph_k, taken = 0; left > 0 && e == hipSuccess; left -= taken)
+        e = launch_some_mc(c, a, left, &taken);
+    c->graph_swap = a.fin != c->fbuf(c->cur);
+    hipGraphExec_t &exec = c->graph[c->cur];
     hipError_t e2 = hipStreamEndCapture(c->stream, &g);
     if (e != hipSuccess || e2 != hipSuccess || !g) {
         if (g) (void)hipGraphDestroy(g);
@@ -207,15 +222,13 @@ void build_graph_mc(lbm_mc_ctx *c)
         c->graph_failed = true;
         return;
     }
-    hipError_t e3 = hipGraphInstantiate(&c->graph, g, nullptr, nullptr, 0);
+    hipError_t e3 = hipGraphInstantiate(&exec, g, nullptr, nullptr, 0);
     (void)hipGraphDestroy(g);
     if (e3 != hipSuccess) {
-        c->graph = nullptr;
+        exec = nullptr;
         (void)hipGetLastError();
         c->graph_failed = true;
-        return;
     }
-    c->graph_cur = c->cur;
 }
 
 } // namespace
@@ -245,13 +258,12 @@ lbm_status lbm_mc_create(const lbm_grid *grid, const lbm_mc_params *p, int32_t p
     c->precision = precision;
     c->grid = *grid;
     c->L = layout_mc(*grid, precision);
-    // fastest shapes of a sweep on a 2048^2 mixture: FP32 128 x 4 threads, one
-    // node each; FP64 128 x 2 threads, two nodes each
-    // default tiles from a sweep on the 2048^2 mixture: 128 x 4 threads for
+    // single-step tiles from a sweep on the 2048^2 mixture: 128 x 4 threads for
     // FP32 and 64 x 8 for FP64, one node each
     c->tx = precision == LBM_FP32 ? 128 : 64;
     c->ty = precision == LBM_FP32 ? 4 : 8;
     c->rows = 1;
+    if (c->args().w32) c->multi = lbmmc::pick_multi_mc(kprec(precision), grid->nx, grid->ny, c->mshape);
     if (workspace && workspace_bytes < c->L.total) {
         delete c;
         return failmc(LBM_ENOMEM, "workspace smaller than lbm_mc_workspace_bytes()");
@@ -350,21 +362,23 @@ lbm_status lbm_mc_step(lbm_mc_ctx *ctx, int64_t n)
     if (n < 0) return failmc(LBM_EINVAL, "negative step count");
     LBMMC_HIP(hipSetDevice(ctx->device));
     const int64_t block = 2 * (int64_t)ctx->graph_k;
-    if (ctx->graph_k > 0 && !ctx->graph_failed && n >= block) {
-        if (ctx->graph && ctx->graph_cur != ctx->cur) drop_graph_mc(ctx); // captured from the other buffer
-        if (!ctx->graph) build_graph_mc(ctx);
-        if (ctx->graph) {
-            while (n >= block) {
-                LBMMC_HIP(hipGraphLaunch(ctx->graph, ctx->stream));
-                ctx->steps += block;
-                n -= block;
-            }
+    while (ctx->graph_k > 0 && !ctx->graph_failed && n >= block) {
+        if (!ctx->graph[ctx->cur]) {
+            build_graph_mc(ctx);
+            continue;
         }
+        LBMMC_HIP(hipGraphLaunch(ctx->graph[ctx->cur], ctx->stream));
+        ctx->cur ^= ctx->graph_swap;
+        ctx->steps += block;
+        n -= block;
     }
-    for (int64_t i = 0; i < n; ++i) {
-        LBMMC_HIP(lbmmc::launch_step_mc(kprec(ctx->precision), ctx->args()));
+    lbmmc::StepMCArgs a = ctx->args();
+    while (n > 0) {
+        int64_t taken = 0;
+        LBMMC_HIP(launch_some_mc(ctx, a, n, &taken));
         ctx->cur ^= 1;
-        ++ctx->steps;
+        ctx->steps += taken;
+        n -= taken;
     }
     return LBM_OK;
 }
@@ -423,6 +437,7 @@ lbm_status lbm_mc_autotune(lbm_mc_ctx *ctx, int32_t steps, int32_t *tx, int32_t 
     Cand pick = keep;
     float best = 0.f;
     lbm_status rc = LBM_OK;
+    ctx->single_steps = true; // the tiles are those of the single steps
     for (const Cand &c : cands) {
         if (lbm_mc_set_tile(ctx, c.tx, c.ty, c.rows) != LBM_OK) continue;
         if ((rc = lbm_mc_step(ctx, 1)) != LBM_OK) break; // warm-up
@@ -443,6 +458,7 @@ lbm_status lbm_mc_autotune(lbm_mc_ctx *ctx, int32_t steps, int32_t *tx, int32_t 
     }
     (void)hipEventDestroy(e0);
     (void)hipEventDestroy(e1);
+    ctx->single_steps = false;
     if (rc != LBM_OK) {
         (void)lbm_mc_set_tile(ctx, keep.tx, keep.ty, keep.rows);
         return rc;
@@ -620,18 +636,19 @@ lbm_status lbm_mc_time_kernels(lbm_mc_ctx *ctx, int64_t n, double *step_ms)
         }
     double t = 0.0;
     hipError_t e = hipSuccess;
-    for (int64_t i = 0; i < n && rc == LBM_OK && e == hipSuccess; ++i) {
+    int64_t launches = 0;
+    for (int64_t left = n, taken = 0; left > 0 && rc == LBM_OK && e == hipSuccess; ++launches, left -= taken) {
         lbmmc::StepMCArgs a = ctx->args();
-        a.ev0 = ev[2 * i];
-        a.ev1 = ev[2 * i + 1];
-        e = lbmmc::launch_step_mc(kprec(ctx->precision), a);
+        a.ev0 = ev[2 * launches];
+        a.ev1 = ev[2 * launches + 1];
+        e = launch_some_mc(ctx, a, left, &taken);
         if (e == hipSuccess) {
             ctx->cur ^= 1;
-            ++ctx->steps;
+            ctx->steps += taken;
         }
     }
     if (rc == LBM_OK && e == hipSuccess) e = hipStreamSynchronize(ctx->stream);
-    for (int64_t i = 0; i < n && rc == LBM_OK && e == hipSuccess; ++i) {
+    for (int64_t i = 0; i < launches && rc == LBM_OK && e == hipSuccess; ++i) {
         float a1 = 0.f;
         e = hipEventElapsedTime(&a1, ev[2 * i], ev[2 * i + 1]);
         t += a1;

@@ -2,7 +2,7 @@
 // pseudopotential MRT step with the surface-tension source term (Li & Luo,
 // arXiv:1306.6445, Section VI names multicomponent models as future work; the
 // two-component form follows the derivation in the design notes).  One step
-// is one launch of mc_fused_kernel:
+// is one launch of mc_fused_kernel, or several are one of mc_multi_kernel:
 //   each workgroup loads the populations of both components for its tile
 //   (rows nodes per thread, ty rows apart) and a one-node ring around it,
 //   sums the densities (psi_s = rho_s) into LDS, and after one barrier
@@ -20,6 +20,8 @@
 
 #include "lbm3d_kernels.hpp"
 #include "lbm_mc_kernels.hpp"
+#include "lbm_multi.hpp"
+#include "lbm_popbuf.hpp"
 
 namespace lbmmc {
 
@@ -141,6 +143,30 @@ __device__ __forceinline__ void collide_mc(const RunMC &r, const C *fv, C rs, C 
     mc_moments_to_pops<C>(ms, fs);
 }
 
+// Both components of one node: populations fA, fB with densities rA, rB, the
+// densities pA, pB of the node and its neighbours -> post-collision sa, sb.
+template <typename C>
+__device__ __forceinline__ void collide_both(const RunMC &r, C G, C kappa, const C *fA, const C *fB, C rA, C rB,
+                                             const C *pA, const C *pB, C *sa, C *sb)
+{
+    // psi_s = rho_s: A feels B's psi and B feels A's
+    C FAx, FAy, QAxx, QAyy, QAxy, FBx, FBy, QBxx, QByy, QBxy;
+    force_q<C>(G, kappa, rA, pB, FAx, FAy, QAxx, QAyy, QAxy);
+    force_q<C>(G, kappa, rB, pA, FBx, FBy, QBxx, QByy, QBxy);
+    // Eq. (6) for the mixture
+    C jx = C(0), jy = C(0);
+#pragma unroll
+    for (int a = 1; a < 9; ++a) {
+        const C v = fA[a] + fB[a];
+        if (ex_of(a)) jx += C(ex_of(a)) * v;
+        if (ey_of(a)) jy += C(ey_of(a)) * v;
+    }
+    const C irho = lbm::recip<C>(rA + rB);
+    const C ux = (jx + C(0.5) * (FAx + FBx)) * irho, uy = (jy + C(0.5) * (FAy + FBy)) * irho;
+    collide_mc<C>(r, fA, rA, ux, uy, FAx, FAy, QAxx, QAyy, QAxy, sa);
+    collide_mc<C>(r, fB, rB, ux, uy, FBx, FBy, QBxx, QByy, QBxy, sb);
+}
+
 // streamed populations of both components of node n (host-order index
 // y nx + x, neighbour offsets X, Y)
 template <typename S, typename C>
@@ -250,23 +276,8 @@ __global__ void __launch_bounds__(512) mc_fused_kernel(const RunMC *__restrict__
             pA[a] = la[cell + ey_of(a) * LX + ex_of(a)];
             pB[a] = lb[cell + ey_of(a) * LX + ex_of(a)];
         }
-        // psi_s = rho_s: A feels B's psi and B feels A's
-        C FAx, FAy, QAxx, QAyy, QAxy, FBx, FBy, QBxx, QByy, QBxy;
-        force_q<C>(G, kappa, rA[j], pB, FAx, FAy, QAxx, QAyy, QAxy);
-        force_q<C>(G, kappa, rB[j], pA, FBx, FBy, QBxx, QByy, QBxy);
-        // Eq. (6) for the mixture
-        C jx = C(0), jy = C(0);
-#pragma unroll
-        for (int a = 1; a < 9; ++a) {
-            const C v = fA[j][a] + fB[j][a];
-            if (ex_of(a)) jx += C(ex_of(a)) * v;
-            if (ey_of(a)) jy += C(ey_of(a)) * v;
-        }
-        const C irho = lbm::recip<C>(rA[j] + rB[j]);
-        const C ux = (jx + C(0.5) * (FAx + FBx)) * irho, uy = (jy + C(0.5) * (FAy + FBy)) * irho;
         C sa[9], sb[9];
-        collide_mc<C>(r, fA[j], rA[j], ux, uy, FAx, FAy, QAxx, QAyy, QAxy, sa);
-        collide_mc<C>(r, fB[j], rB[j], ux, uy, FBx, FBy, QBxx, QByy, QBxy, sb);
+        collide_both<C>(r, G, kappa, fA[j], fB[j], rA[j], rB[j], pA, pB, sa, sb);
         // f* stays at the node; the next read streams it (Eq. 4)
         const int64_t n = (int64_t)y * nx + x;
         if constexpr (W32) {
@@ -287,6 +298,173 @@ __global__ void __launch_bounds__(512) mc_fused_kernel(const RunMC *__restrict__
             }
         }
     }
+}
+
+// Several steps in one launch, the intermediate states in LDS (see
+// lbm_multi.hpp): step s of K collides the tile and a margin of 2 (K - s) nodes.
+// The state is f*_a at the node, streamed on the read, so the first step gathers
+// from the source buffer, the later ones from LDS and the last stores at the
+// node.  The intermediate state passes through LDS in its storage form: the same
+// bits as single steps.
+//
+// What bounds it: the single step moved 149 B of counted traffic a node and step
+// (FP32) at 4.4-4.9 TB/s; two steps a launch halve that, and vector issue, with
+// the margins done again by the neighbours, bounds the rest.  us per step, one ->
+// several a launch: 2048^2 FP32 127 -> 101, FP64 244 -> 200; 800^2 FP32 20.8 -> 15.7;
+// 100^2 FP32 5.1 -> 2.9, FP64 6.4 -> 3.2.
+template <typename S, int K, int TX, int TY, int NT, bool WALLS> struct MultiMC {
+    using C = ArithOf<S>;
+    using Gm = lbm::MultiGeom<K, TX, TY>;
+    const RunMC &r;
+    const int nx, ny, bcx, bcy, x0, y0;
+    const uint32_t ds; // bytes from one direction's array to the next
+    const C refA, refB, G, kappa;
+    const lbm::PopBuf<S> in, out;
+    C *la, *lb; // densities
+    S *pop;     // component A's nine planes of FN cells, then component B's
+    bool bad = false;
+
+    template <int s> __device__ __forceinline__ void load(int dx, int dy, C *fa, C *fb) const
+    {
+        const int gx = lbm::psi_coord(x0 + dx, nx, WALLS ? bcx : lbm::BC_PERIODIC);
+        const int gy = lbm::psi_coord(y0 + dy, ny, WALLS ? bcy : lbm::BC_PERIODIC);
+        const lbm::Nbr n = lbm::neighbours(gx, gy, nx, ny, WALLS ? bcx : lbm::BC_PERIODIC, WALLS ? bcy : lbm::BC_PERIODIC);
+        auto wall = [&](int a) {
+            const int ex = ex_of(a), ey = ey_of(a);
+            return WALLS && ((ex > 0 && n.wxm) || (ex < 0 && n.wxp) || (ey > 0 && n.wym) || (ey < 0 && n.wyp));
+        };
+        if constexpr (s == 1) {
+            constexpr uint32_t z = sizeof(S);
+            const uint32_t xo[3] = {n.xm * z, gx * z, n.xp * z};
+            const uint32_t yo[3] = {n.ym * nx * z, gy * nx * z, n.yp * nx * z};
+#pragma unroll
+            for (int a = 0; a < 9; ++a) {
+                const uint32_t up = xo[1 - ex_of(a)] + yo[1 - ey_of(a)];
+                if constexpr (WALLS) {
+                    const uint32_t i = wall(a) ? opp_of(a) * ds + xo[1] + yo[1] : a * ds + up;
+                    fa[a] = dec<S, C>(in.load(i, 0), a, refA);
+                    fb[a] = dec<S, C>(in.load(i, 9 * ds), a, refB);
+                } else {
+                    fa[a] = dec<S, C>(in.load(up, a * ds), a, refA);
+                    fb[a] = dec<S, C>(in.load(up, (9 + a) * ds), a, refB);
+                }
+            }
+        } else {
+            // LDS cell: unwrapped on a periodic axis, the clamped node's across a wall
+            const int cx = WALLS && bcx == lbm::BC_WALL ? gx - x0 : dx, cy = WALLS && bcy == lbm::BC_WALL ? gy - y0 : dy;
+            const int cell = (cy + Gm::M) * Gm::FX + cx + Gm::M;
+#pragma unroll
+            for (int a = 0; a < 9; ++a) {
+                const int i = wall(a) ? opp_of(a) * Gm::FN + cell : a * Gm::FN + cell - (ey_of(a) * Gm::FX + ex_of(a));
+                fa[a] = dec<S, C>(pop[i], a, refA);
+                fb[a] = dec<S, C>(pop[9 * Gm::FN + i], a, refB);
+            }
+        }
+    }
+
+    __device__ __forceinline__ void put(int dx, int dy, const C *fa, const C *fb, C &da, C &db)
+    {
+        da = lbm::node_density<C>(fa);
+        db = lbm::node_density<C>(fb);
+        bad |= !(da + db > C(0)) || !(da - da == C(0)) || !(db - db == C(0));
+        const int cell = (dy + Gm::M + 1) * Gm::PX + dx + Gm::M + 1;
+        la[cell] = da;
+        lb[cell] = db;
+    }
+
+    template <int s> __device__ __forceinline__ void step(int tid)
+    {
+        constexpr int N = Gm::cells(s), NI = N + Gm::ring(s), R = (N + NT - 1) / NT;
+        C fA[R][9], fB[R][9], rA[R], rB[R];
+#pragma unroll
+        for (int j = 0; j < R; ++j) {
+            const int i = tid + j * NT;
+            if (i < NI) {
+                int dx, dy;
+                lbm::multi_item<Gm, s, K>(i, dx, dy);
+                load<s>(dx, dy, fA[j], fB[j]);
+                put(dx, dy, fA[j], fB[j], rA[j], rB[j]);
+            }
+        }
+        for (int i = tid + R * NT; i < NI; i += NT) {
+            int dx, dy;
+            lbm::multi_item<Gm, s, K>(i, dx, dy);
+            C ha[9], hb[9], da, db;
+            load<s>(dx, dy, ha, hb);
+            put(dx, dy, ha, hb, da, db);
+        }
+        __syncthreads();
+#pragma unroll
+        for (int j = 0; j < R; ++j) {
+            const int i = tid + j * NT;
+            if (i < N) {
+                const int ly = (unsigned)i / (unsigned)Gm::w(s), lx = i - ly * Gm::w(s);
+                const int dx = lx - 2 * (K - s), dy = ly - 2 * (K - s);
+                const int cell = (dy + Gm::M + 1) * Gm::PX + dx + Gm::M + 1;
+                C pA[9], pB[9], sa[9], sb[9];
+#pragma unroll
+                for (int a = 0; a < 9; ++a) {
+                    pA[a] = la[cell + ey_of(a) * Gm::PX + ex_of(a)];
+                    pB[a] = lb[cell + ey_of(a) * Gm::PX + ex_of(a)];
+                }
+                collide_both<C>(r, G, kappa, fA[j], fB[j], rA[j], rB[j], pA, pB, sa, sb);
+                if constexpr (s < K) {
+                    const int q = (dy + Gm::M) * Gm::FX + dx + Gm::M;
+#pragma unroll
+                    for (int a = 0; a < 9; ++a) {
+                        pop[a * Gm::FN + q] = enc<S, C>(sa[a], a, refA);
+                        pop[(9 + a) * Gm::FN + q] = enc<S, C>(sb[a], a, refB);
+                    }
+                } else {
+                    const int x = x0 + dx, y = y0 + dy;
+                    if (x < nx && y < ny) {
+                        const uint32_t off = (uint32_t)(y * nx + x) * (uint32_t)sizeof(S);
+#pragma unroll
+                        for (int a = 0; a < 9; ++a) {
+                            out.store(off, a * ds, enc<S, C>(sa[a], a, refA));
+                            out.store(off, (9 + a) * ds, enc<S, C>(sb[a], a, refB));
+                        }
+                    }
+                }
+            }
+        }
+        if constexpr (s < K) {
+            __syncthreads();
+            step<s + 1>(tid);
+        }
+    }
+};
+
+template <typename S, int K, int TX, int TY, int NT>
+__global__ void __launch_bounds__(NT) mc_multi_kernel(const RunMC *__restrict__ runs, const S *__restrict__ fin,
+                                                      S *__restrict__ fout, int32_t *__restrict__ status)
+{
+    using C = ArithOf<S>;
+    using Gm = lbm::MultiGeom<K, TX, TY>;
+    __shared__ C la[Gm::PN], lb[Gm::PN];
+    __shared__ S pop[18 * Gm::FN];
+    const RunMC &r = runs[0];
+    const int ntx = (r.nx + TX - 1) / TX, wi = lbm::work_index(1), x0 = wi % ntx * TX, y0 = wi / ntx * TY;
+    const uint32_t ds = (uint32_t)r.dstride * (uint32_t)sizeof(S);
+    const C G = std::is_same<C, float>::value ? C(r.Gf) : C(r.G);
+    const C kappa = std::is_same<C, float>::value ? C(r.kappaf) : C(r.kappa);
+    // reach of the first step's reads beyond the tile
+    constexpr int E = Gm::M + 2;
+    const bool free_x = r.bc_x == lbm::BC_PERIODIC || (x0 >= E && x0 + TX + E <= r.nx);
+    const bool free_y = r.bc_y == lbm::BC_PERIODIC || (y0 >= E && y0 + TY + E <= r.ny);
+    bool bad;
+    if (free_x && free_y) {
+        MultiMC<S, K, TX, TY, NT, false> m{r, r.nx, r.ny, r.bc_x, r.bc_y, x0, y0, ds, ref_of<C>(r, 0), ref_of<C>(r, 1), G,
+                                          kappa, lbm::PopBuf<S>(fin), lbm::PopBuf<S>(fout), la, lb, pop};
+        m.template step<1>((int)threadIdx.x);
+        bad = m.bad;
+    } else {
+        MultiMC<S, K, TX, TY, NT, true> m{r, r.nx, r.ny, r.bc_x, r.bc_y, x0, y0, ds, ref_of<C>(r, 0), ref_of<C>(r, 1), G,
+                                         kappa, lbm::PopBuf<S>(fin), lbm::PopBuf<S>(fout), la, lb, pop};
+        m.template step<1>((int)threadIdx.x);
+        bad = m.bad;
+    }
+    if (bad) status[0] = 1;
 }
 
 // ------------------------------------------------------------- utilities
@@ -440,6 +618,80 @@ hipError_t launch_step_mc(int precision, const StepMCArgs &a)
 {
     if (!mc_shape_ok(a.tx, a.ty, a.rows)) return hipErrorInvalidValue;
     return precision == PRECMC_FP64 ? step_mc_t<double>(a) : step_mc_t<float>(a);
+}
+
+namespace {
+
+template <typename S, int K, int TX, int TY, int NT> hipError_t launch_multi_mc_t(const StepMCArgs &a)
+{
+    const lbm::MultiShape shape{K, TX, TY};
+    const dim3 grid((unsigned)lbm::multi_tiles(shape, a.nx, a.ny));
+    hipExtLaunchKernelGGL((mc_multi_kernel<S, K, TX, TY, NT>), grid, dim3(NT), 0, a.stream, a.ev0, a.ev1, 0, a.run,
+                          static_cast<const S *>(a.fin), static_cast<S *>(a.fout), a.status);
+    return hipGetLastError();
+}
+
+struct VariantMC {
+    lbm::MultiShape shape;
+    double work;       // relative vector work of a tile: 130 a cell's densities, 440 a collision
+    int64_t max_tiles; // small tiles: taken when the grid has no more of them than this
+    hipError_t (*launch)(const StepMCArgs &);
+};
+
+template <typename S, int K, int TX, int TY, int NT> constexpr VariantMC variant_of(int64_t max_tiles, double factor = 1.0)
+{
+    using Gm = lbm::MultiGeom<K, TX, TY>;
+    double work = 0.0;
+    for (int s = 1; s <= K; ++s) work += 130.0 * (Gm::cells(s) + Gm::ring(s)) + 440.0 * Gm::cells(s);
+    return {{K, TX, TY}, work * factor, max_tiles, launch_multi_mc_t<S, K, TX, TY, NT>};
+}
+
+// 72 (FP32) or 144 bytes of LDS a cell keep the tiles small: about 500 (220)
+// nodes for two workgroups a CU.  Small grids take the tile with the shortest
+// chain (us a step, FP32: 100^2 2.9 with 8 x 8 and K = 4 against 4.0 with 28 x 12
+// and 5.1 one step at a time; 400^2 6.2 with 28 x 12 against 6.7 with 32 x 16), the
+// others the least work over whole tiles, 32 x 16 ones charged a tenth more for
+// their short rows (2048^2 100.6 with 64 x 8 against 107.7; 800^2 18.5 against 15.7).
+const VariantMC kMc32[] = {
+    variant_of<float, 4, 8, 8, 512>(256),
+    variant_of<float, 2, 28, 12, 512>(768),
+    variant_of<float, 2, 64, 8, 512>(0),
+    variant_of<float, 2, 32, 16, 768>(0, 1.1),
+};
+const VariantMC kMc64[] = {
+    variant_of<double, 4, 8, 8, 512>(256),
+    variant_of<double, 2, 28, 8, 512>(0),
+};
+
+const VariantMC *variant_mc(int precision, int v)
+{
+    if (precision == PRECMC_FP32) return v >= 0 && v < (int)(sizeof(kMc32) / sizeof(kMc32[0])) ? &kMc32[v] : nullptr;
+    return v >= 0 && v < (int)(sizeof(kMc64) / sizeof(kMc64[0])) ? &kMc64[v] : nullptr;
+}
+
+} // namespace
+
+int pick_multi_mc(int precision, int nx, int ny, lbm::MultiShape &shape)
+{
+    int best = -1;
+    double least = 0.0;
+    for (int v = 0; const VariantMC *p = variant_mc(precision, v); ++v) {
+        const int64_t tiles = lbm::multi_tiles(p->shape, nx, ny);
+        if (p->max_tiles > 0 && tiles > p->max_tiles) continue;
+        if (p->max_tiles > 0 || best < 0 || (double)tiles * p->work < least) {
+            best = v;
+            least = (double)tiles * p->work;
+            shape = p->shape;
+        }
+        if (p->max_tiles > 0) break;
+    }
+    return best;
+}
+
+hipError_t launch_multi_mc(int precision, int v, const StepMCArgs &a)
+{
+    const VariantMC *p = variant_mc(precision, v);
+    return p && a.w32 ? p->launch(a) : hipErrorInvalidValue;
 }
 
 static unsigned blocks_mc(int64_t n) { return (unsigned)((n + kThreadsMC - 1) / kThreadsMC); }

@@ -7,6 +7,7 @@
 
 #include "lbm3d_kernels.hpp"
 #include "lbm_device.hpp"
+#include "lbm_kernels.hpp"
 
 namespace lbmmc {
 
@@ -89,6 +90,10 @@ __host__ __device__ inline void mc_ring_cell(int k, int LX, int LY, int &lx, int
 }
 
 hipError_t launch_step_mc(int precision, const StepMCArgs &a);
+// Several steps fin -> fout in one launch (w32 buffers): the variant for a
+// grid and its shape, -1 when there is none; and its launch.
+int pick_multi_mc(int precision, int nx, int ny, lbm::MultiShape &shape);
+hipError_t launch_multi_mc(int precision, int v, const StepMCArgs &a);
 
 // Utility launches over the nodes of the run: op 0 = populations [2][9][N]
 // into buf (FP64, host order), op 1 = populations from buf into fout, op 2 =
