@@ -213,6 +213,7 @@ struct lbm_ctx {
     bool own_ws = false;
     hipStream_t stream = nullptr;
     bool own_stream = false;
+    unsigned char *pinned = nullptr; // host memory that small read-outs are written to (kSmallRead; see small_read)
     int tx = 64, ty = 4;
     int64_t steps = 0;
     int graph_k = 16;
@@ -422,6 +423,24 @@ lbm_status refresh_psi(lbm_ctx *c)
 {
     LBM_HIP(lbm::launch_psi(kernel_precision(c->precision), c->step_args(), c->parity()));
     return LBM_OK;
+}
+
+// Read-outs of up to 2 MB: the kernel writes them straight to pinned host
+// memory of the context, and one synchronisation later they are copied to the
+// caller's arrays.  A copy command into pageable memory costs about 15 us before
+// its bytes count: 256 columns of 4 x 256 slabs 6.3 -> 3.9 ms, the moments of 40
+// drops of 256^2 7.0 -> 5.5, of one 100^2 run 0.23 -> 0.04.  Larger read-outs gain
+// nothing, the page faults of the caller's fresh arrays bound them.  nullptr: no
+// pinned memory, the caller takes copies from the staging area.
+constexpr size_t kSmallRead = size_t(2) << 20;
+double *small_read(lbm_ctx *c, size_t bytes)
+{
+    if (bytes > kSmallRead) return nullptr;
+    if (!c->pinned && hipHostMalloc(reinterpret_cast<void **>(&c->pinned), kSmallRead, hipHostMallocDefault) != hipSuccess) {
+        (void)hipGetLastError();
+        c->pinned = nullptr;
+    }
+    return reinterpret_cast<double *>(c->pinned);
 }
 
 lbm_status read_status(lbm_ctx *c, std::vector<int32_t> &st)
@@ -661,6 +680,7 @@ void lbm_destroy(lbm_ctx *ctx)
     if (ctx->stream) (void)hipStreamSynchronize(ctx->stream);
     drop_graph(ctx);
     if (ctx->own_ws && ctx->ws) (void)hipFree(ctx->ws);
+    if (ctx->pinned) (void)hipHostFree(ctx->pinned);
     if (ctx->own_stream && ctx->stream) (void)hipStreamDestroy(ctx->stream);
     delete ctx;
 }
@@ -749,14 +769,18 @@ lbm_status lbm_run_moments(lbm_ctx *ctx, int32_t run, double *rho, double *ux, d
     if (!rho) return fail(LBM_EINVAL, "null density output");
     LBM_HIP(hipSetDevice(ctx->device));
     const int64_t N = run_nodes(ctx, run);
-    double *st = ctx->at<double>(ctx->L.staging);
+    double *const small = small_read(ctx, 3 * sizeof(double) * (size_t)N);
+    double *st = small ? small : ctx->at<double>(ctx->L.staging);
+    double *const outs[3] = {rho, ux, uy};
     if ((s = refresh_psi(ctx)) != LBM_OK) return s;
     if ((s = util(ctx, lbm::UTIL_MOMENTS, run, st)) != LBM_OK) return s;
-    LBM_HIP(hipMemcpyAsync(rho, st, sizeof(double) * N, hipMemcpyDeviceToHost, ctx->stream));
-    if (ux) LBM_HIP(hipMemcpyAsync(ux, st + N, sizeof(double) * N, hipMemcpyDeviceToHost, ctx->stream));
-    if (uy) LBM_HIP(hipMemcpyAsync(uy, st + 2 * N, sizeof(double) * N, hipMemcpyDeviceToHost, ctx->stream));
+    for (int i = 0; i < 3 && !small; ++i)
+        if (outs[i])
+            LBM_HIP(hipMemcpyAsync(outs[i], st + i * N, sizeof(double) * N, hipMemcpyDeviceToHost, ctx->stream));
     std::vector<int32_t> stt;
     if ((s = read_status(ctx, stt)) != LBM_OK) return s;
+    for (int i = 0; i < 3 && small; ++i)
+        if (outs[i]) std::memcpy(outs[i], st + i * N, sizeof(double) * (size_t)N);
     return stt[run] ? fail(LBM_EDIVERGED, "run " + std::to_string(run) + " has diverged") : LBM_OK;
 }
 
@@ -769,7 +793,8 @@ lbm_status lbm_run_density_column(lbm_ctx *ctx, int32_t run, int32_t x, double *
     if (x < 0 || x >= ctx->desc[run].grid.nx) return fail(LBM_EINVAL, "column index out of range");
     LBM_HIP(hipSetDevice(ctx->device));
     const int ny = ctx->desc[run].grid.ny;
-    double *st = ctx->at<double>(ctx->L.staging);
+    double *const small = small_read(ctx, sizeof(double) * (size_t)ny);
+    double *st = small ? small : ctx->at<double>(ctx->L.staging);
     lbm::UtilArgs u;
     u.op = lbm::UTIL_COLUMN;
     u.runs = ctx->at<lbm::RunDev>(ctx->L.runs);
@@ -787,8 +812,9 @@ lbm_status lbm_run_density_column(lbm_ctx *ctx, int32_t run, int32_t x, double *
         u.r1 = ctx->rbuf(1);
     }
     LBM_HIP(lbm::launch_util(kernel_precision(ctx->precision), u));
-    LBM_HIP(hipMemcpyAsync(rho, st, sizeof(double) * ny, hipMemcpyDeviceToHost, ctx->stream));
+    if (!small) LBM_HIP(hipMemcpyAsync(rho, st, sizeof(double) * ny, hipMemcpyDeviceToHost, ctx->stream));
     LBM_HIP(hipStreamSynchronize(ctx->stream));
+    if (small) std::memcpy(rho, st, sizeof(double) * (size_t)ny);
     return LBM_OK;
 }
 
