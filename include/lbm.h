@@ -316,9 +316,11 @@ lbm_status lbm_set_fused(lbm_ctx *ctx, int32_t rows);
  * candidate schedule and tile shape (two-kernel 64x4, 128x2, 32x8, 256x1, 64x2,
  * 32x4; fused, as tx x ty threads / rows: 64x4 / 1, 64x4 / 2, 64x4 / 4,
  * 128x2 / 2, 128x2 / 4, 256x1 / 4, 32x8 / 2, 64x2 / 4, 256x2 / 4, 128x4 / 2),
- * graph replay included, one step per launch, and keeps the fastest.  The
- * candidates compute the same step, so the timed steps are real work: the
- * state advances by about 16 * (steps + 2 * graph steps).  The chosen shape is
+ * graph replay included, one step per launch, and keeps the fastest; where
+ * that is a two-kernel shape, the fastest fused one is timed once more with
+ * several steps per launch and kept if it is faster.  The candidates compute
+ * the same step, so the timed steps are real work: the state advances by
+ * about 16 * (steps + 2 * graph steps).  The chosen shape is
  * written to tx, ty, fused (each may be NULL).  Synchronises. */
 lbm_status lbm_autotune(lbm_ctx *ctx, int32_t steps, int32_t *tx, int32_t *ty, int32_t *fused);
 

@@ -1269,35 +1269,45 @@ lbm_status lbm_autotune(lbm_ctx *ctx, int32_t steps, int32_t *tx, int32_t *ty, i
         (void)hipEventDestroy(e0);
         return fail(LBM_EDEVICE, std::string("hipEventCreate: ") + hipGetErrorString(he));
     }
-    float best = 0.f;
-    Cand pick = {ctx->tx, ctx->ty, ctx->fused};
-    lbm_status rc = LBM_OK;
     const int64_t n = steps + (steps & 1);
-    // the shapes are those of the single steps; lbm_set_fused below restores the multi-step kernel
+    auto timed = [&](const Cand &c, float &ms) -> lbm_status {
+        lbm_status r = lbm_set_tile(ctx, c.tx, c.ty);
+        if (r == LBM_OK) r = lbm_set_fused(ctx, c.fused);
+        // one untimed replay builds the graph
+        if (r == LBM_OK) r = lbm_step(ctx, 2 * (int64_t)std::max(ctx->graph_k, 1));
+        if (r != LBM_OK) return r;
+        hipError_t e = hipEventRecord(e0, ctx->stream);
+        if (e == hipSuccess && (r = lbm_step(ctx, n)) != LBM_OK) return r;
+        if (e == hipSuccess) e = hipEventRecord(e1, ctx->stream);
+        if (e == hipSuccess) e = hipEventSynchronize(e1);
+        if (e == hipSuccess) e = hipEventElapsedTime(&ms, e0, e1);
+        return e == hipSuccess ? LBM_OK : fail(LBM_EDEVICE, std::string("autotune timing: ") + hipGetErrorString(e));
+    };
+    // the shapes are those of the single steps: the multi-step kernel is off while they are timed
+    float best = 0.f, best_fused = 0.f;
+    Cand pick = {ctx->tx, ctx->ty, ctx->fused}, pick_fused = pick;
+    lbm_status rc = LBM_OK;
     ctx->single_steps = true;
     for (const Cand &c : cands) {
-        if ((rc = lbm_set_tile(ctx, c.tx, c.ty)) != LBM_OK) break;
-        if ((rc = lbm_set_fused(ctx, c.fused)) != LBM_OK) break;
-        // one untimed replay builds the graph
-        if ((rc = lbm_step(ctx, 2 * (int64_t)std::max(ctx->graph_k, 1))) != LBM_OK) break;
-        he = hipEventRecord(e0, ctx->stream);
-        if (he == hipSuccess && (rc = lbm_step(ctx, n)) != LBM_OK) break;
-        if (he == hipSuccess) he = hipEventRecord(e1, ctx->stream);
-        if (he == hipSuccess) he = hipEventSynchronize(e1);
         float ms = 0.f;
-        if (he == hipSuccess) he = hipEventElapsedTime(&ms, e0, e1);
-        if (he != hipSuccess) {
-            rc = fail(LBM_EDEVICE, std::string("autotune timing: ") + hipGetErrorString(he));
-            break;
-        }
+        if ((rc = timed(c, ms)) != LBM_OK) break;
         if (best == 0.f || ms < best) {
             best = ms;
             pick = c;
         }
+        if (c.fused && (best_fused == 0.f || ms < best_fused)) {
+            best_fused = ms;
+            pick_fused = c;
+        }
+    }
+    ctx->single_steps = false;
+    // where two kernels a step win among single steps, the fused shape is timed again with several steps a launch
+    if (rc == LBM_OK && pick.fused == 0) {
+        float ms = 0.f;
+        if ((rc = timed(pick_fused, ms)) == LBM_OK && ms < best) pick = pick_fused;
     }
     (void)hipEventDestroy(e0);
     (void)hipEventDestroy(e1);
-    ctx->single_steps = false;
     if (rc != LBM_OK) {
         // keep the failure's message; the tables go back to the multi-step kernel
         const std::string msg = g_error;
