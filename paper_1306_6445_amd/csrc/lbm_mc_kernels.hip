@@ -310,7 +310,7 @@ __global__ void __launch_bounds__(512) mc_fused_kernel(const RunMC *__restrict__
 // What bounds it: the single step moved 149 B of counted traffic a node and step
 // (FP32) at 4.4-4.9 TB/s; two steps a launch halve that, and vector issue, with
 // the margins done again by the neighbours, bounds the rest.  us per step, one ->
-// several a launch: 2048^2 FP32 127 -> 101, FP64 244 -> 200; 800^2 FP32 20.8 -> 15.7;
+// several a launch: 2048^2 FP32 127 -> 100, FP64 244 -> 194; 1300^2 FP32 34.7, FP64 81.3;
 // 100^2 FP32 5.1 -> 2.9, FP64 6.4 -> 3.2.
 template <typename S, int K, int TX, int TY, int NT, bool WALLS> struct MultiMC {
     using C = ArithOf<S>;
@@ -638,29 +638,30 @@ struct VariantMC {
     hipError_t (*launch)(const StepMCArgs &);
 };
 
-template <typename S, int K, int TX, int TY, int NT> constexpr VariantMC variant_of(int64_t max_tiles, double factor = 1.0)
+template <typename S, int K, int TX, int TY, int NT> constexpr VariantMC variant_of(int64_t max_tiles)
 {
     using Gm = lbm::MultiGeom<K, TX, TY>;
     double work = 0.0;
     for (int s = 1; s <= K; ++s) work += 130.0 * (Gm::cells(s) + Gm::ring(s)) + 440.0 * Gm::cells(s);
-    return {{K, TX, TY}, work * factor, max_tiles, launch_multi_mc_t<S, K, TX, TY, NT>};
+    return {{K, TX, TY}, work, max_tiles, launch_multi_mc_t<S, K, TX, TY, NT>};
 }
 
-// 72 (FP32) or 144 bytes of LDS a cell keep the tiles small: about 500 (220)
-// nodes for two workgroups a CU.  Small grids take the tile with the shortest
-// chain (us a step, FP32: 100^2 2.9 with 8 x 8 and K = 4 against 4.0 with 28 x 12
-// and 5.1 one step at a time; 400^2 6.2 with 28 x 12 against 6.7 with 32 x 16), the
-// others the least work over whole tiles, 32 x 16 ones charged a tenth more for
-// their short rows (2048^2 100.6 with 64 x 8 against 107.7; 800^2 18.5 against 15.7).
+// 72 (FP32) or 144 bytes of LDS a cell keep the tiles small.  Small grids take
+// the tile with the shortest chain (us a step, FP32: 100^2 2.9 with 8 x 8 and K =
+// 4 against 4.0 with 28 x 12 and 5.1 one step at a time; 400^2 6.2 with 28 x 12
+// against 6.7 with 32 x 16), the others the largest tile that leaves two
+// workgroups a CU and fills the rounds of its threads, with rows that start on
+// 128 bytes (FP32, us a step: 1300^2 34.9 with 32 x 24 against 38.2 with 64 x 8 and
+// 37.3 with 28 x 24, 2048^2 101.7 / 102.0 / 99.7; FP64 1300^2 82.0 with 32 x 8
+// against 86.4 with 28 x 8, 2048^2 195 / 201).
 const VariantMC kMc32[] = {
     variant_of<float, 4, 8, 8, 512>(256),
     variant_of<float, 2, 28, 12, 512>(768),
-    variant_of<float, 2, 64, 8, 512>(0),
-    variant_of<float, 2, 32, 16, 768>(0, 1.1),
+    variant_of<float, 2, 32, 24, 768>(0),
 };
 const VariantMC kMc64[] = {
     variant_of<double, 4, 8, 8, 512>(256),
-    variant_of<double, 2, 28, 8, 512>(0),
+    variant_of<double, 2, 32, 8, 512>(0),
 };
 
 const VariantMC *variant_mc(int precision, int v)

@@ -17,7 +17,7 @@
 // in one launch and K launches give the same bits.
 //
 // Measured against one step per launch (us per step): 4096 x 2048 FP32 142 ->
-// 88, FP64 261 -> 172; 40 x 256^2 FP32 32.7 -> 25.1, FP64 87 -> 57; 64 uneven
+// 88, FP64 261 -> 163; 40 x 256^2 FP32 32.7 -> 25.1, FP64 87 -> 57; 64 uneven
 // drops FP32 128 -> 77; 2048 x 1024 with walls FP32 27.8 -> 21; 100^2 FP64 6.0 ->
 // 2.2; 256 grids of 4 x 256 FP32 38 -> 5.9; 40 x 256^2 bf16 40.9 -> 32.1, 64
 // uneven drops bf16 125 -> 93.
@@ -327,19 +327,19 @@ template <typename S, int K, int TX, int TY, int NT> hipError_t launch_multi_t(c
 
 struct Variant {
     MultiShape shape;
-    // vector instructions of a tile, about 93 per density and 200 per collision
+    // vector instructions of a tile, about 93 per density and 200 per collision, times what it loses otherwise
     int64_t work;
     // small tiles of several steps: taken when the work list has no more of them than this
     int64_t max_tiles;
     hipError_t (*launch)(const StepArgs &);
 };
 
-template <typename S, int K, int TX, int TY, int NT> constexpr Variant make_variant(int64_t max_tiles)
+template <typename S, int K, int TX, int TY, int NT> constexpr Variant make_variant(int64_t max_tiles, int percent = 100)
 {
     using Gm = MultiGeom<K, TX, TY>;
     int64_t work = 0;
     for (int s = 1; s <= K; ++s) work += 93 * (Gm::cells(s) + Gm::ring(s)) + 200 * Gm::cells(s);
-    return {{K, TX, TY}, work, max_tiles, launch_multi_t<S, K, TX, TY, NT>};
+    return {{K, TX, TY}, work * percent / 100, max_tiles, launch_multi_t<S, K, TX, TY, NT>};
 }
 
 // The variants of one precision, the latency-bound ones (max_tiles > 0) first.
@@ -349,20 +349,29 @@ template <typename S, int K, int TX, int TY, int NT> constexpr Variant make_vari
 //    latencies: the smaller the tile the shorter the chain, as long as each
 //    tile has a CU of its own (FP64: 100^2 2.2 us a step with 8 x 8 against 2.5
 //    with 12 x 12; 256^2 4.3 / 3.8 / 3.7 with 8 x 8, 12 x 12 and 28 x 12, K = 2);
-//  - otherwise the shape with the least work, counting whole tiles: 60 x 20 has
-//    the smallest margins (64 uneven drops 76 against 80 us with 64 x 16),
-//    64 x 16 fits widths of 64 k (256^2 drops 25.1 against 27.7), 4 x 60 and
-//    8 x 60 grids a few nodes wide (256 of 4 x 256: 5.9 us against 12 with
-//    16 x 16 tiles and 32 with 60 x 20).
+//  - otherwise the shape with the least work, counting whole tiles: 60 x 24 has
+//    the smallest margins that leave two workgroups a CU (72 KB of LDS; 4096 x
+//    2048 87.7 us against 89.0 with 60 x 20, 2048 x 1024 20.4 against 21.4; 60 x
+//    44, one workgroup a CU, 113.6), 60 x 20 and 64 x 16 fit some heights and widths
+//    better (40 x 100^2 7.3 against 8.2, 40 x 256^2 25.5 against 27.3; 1280 x 1024
+//    15.0 against 15.4 at equal work, hence the charge of 1), 4 x 60 and
+//    8 x 60 grids a few nodes wide (256 of 4 x 256: 5.9 us against 12 with 16 x 16
+//    tiles and 32 with 60 x 20).  FP64 takes 32 x 24: 1008 cells in two rounds of
+//    512 threads, rows that start on 256 bytes, two workgroups in the 160 KB (4096
+//    x 2048 163 us against 182 with 28 x 20 and 176 with 32 x 16, more than their
+//    work explains: the charges; 768 threads 232), and those two where they fit
+//    better (40 x 100^2 12.3 against 13.6).
 const Variant kF32[] = {
     make_variant<float, 4, 8, 8, 512>(512),  make_variant<float, 4, 20, 20, 1024>(512),
-    make_variant<float, 2, 64, 16, 768>(0),  make_variant<float, 2, 60, 20, 768>(0),
+    make_variant<float, 2, 64, 16, 768>(0),  make_variant<float, 2, 60, 24, 768>(0, 101),
+    make_variant<float, 2, 60, 20, 768>(0),
     make_variant<float, 2, 4, 60, 512>(0),   make_variant<float, 2, 8, 60, 768>(0),
 };
 const Variant kF64[] = {
     make_variant<double, 4, 8, 8, 512>(256), make_variant<double, 4, 12, 12, 768>(256),
-    make_variant<double, 2, 28, 12, 512>(768), make_variant<double, 2, 32, 16, 512>(0),
-    make_variant<double, 2, 28, 20, 768>(0), make_variant<double, 2, 4, 60, 512>(0),
+    make_variant<double, 2, 28, 12, 512>(768), make_variant<double, 2, 32, 24, 512>(0),
+    make_variant<double, 2, 32, 16, 512>(0, 105), make_variant<double, 2, 28, 20, 768>(0, 108),
+    make_variant<double, 2, 4, 60, 512>(0),
 };
 
 // bf16 storage spends its time on decoding and rounding (480 instructions a node
