@@ -19,7 +19,7 @@
 // Measured against one step per launch (us per step): 4096 x 2048 FP32 142 ->
 // 88, FP64 261 -> 163; 40 x 256^2 FP32 32.7 -> 25.1, FP64 87 -> 57; 64 uneven
 // drops FP32 128 -> 77; 2048 x 1024 with walls FP32 27.8 -> 21; 100^2 FP64 6.0 ->
-// 2.2; 256 grids of 4 x 256 FP32 38 -> 5.9; 40 x 256^2 bf16 40.9 -> 32.1, 64
+// 2.2; 256 grids of 4 x 256 FP32 38 -> 3.75 (strips); 40 x 256^2 bf16 40.9 -> 32.1, 64
 // uneven drops bf16 125 -> 93.
 #include <hip/hip_ext.h>
 
@@ -310,6 +310,162 @@ __global__ void __launch_bounds__(NT) multi_kernel(const RunDev *__restrict__ ru
     if (bad) status[t.run] = 1;
 }
 
+// Grids of at most W nodes along a periodic x (flat slabs).  A tile of the
+// kernel above repeats such a grid in its margins: 12 columns of collisions for
+// 4 nodes.  Here a tile is the whole width by TY rows, x wraps in LDS, and only
+// the rows have a margin.
+//  - LDS: the populations W columns a row, psi with a copied column either side.
+//  - An item is a node of a row (W = 4 or 8: shifts; columns past nx idle), then
+//    the 2 W nodes of the rows above and below that need only psi.
+// 256 grids of 4 x 256, us a step: FP32 3.75 against 6.2 with 4 x 60 tiles of the
+// kernel above (which collides 1.6 cells a node and step; here 1.13), FP64 5.8
+// against 9.6; 16 of them 1.9 / 2.4.  Vector issue bounds many grids, the chain of
+// four steps a few.
+template <typename S, int K, int W, int TY, int NT> struct StripTile {
+    using C = typename Store<S>::C;
+    static constexpr int M = 2 * (K - 1), FN = W * (TY + 2 * M);  // LDS populations
+    static constexpr int PX = W + 2, PN = PX * (TY + 2 * M + 2);  // LDS psi
+    static constexpr int cells(int s) { return W * (TY + 4 * (K - s)); }
+    const RunPar<C> k;
+    const int eos, nx, ny, ld, bcy, y0;
+    const uint32_t ds; // bytes from one direction's array to the next
+    const PopBuf<S> in, out;
+    C *psi;
+    S *pop;
+    bool bad = false;
+
+    static __device__ __forceinline__ int pcell(int x, int dy) { return (dy + M + 1) * PX + x + 1; }
+
+    template <int A> __device__ __forceinline__ C decode(S v) const { return Store<S>::template load<A>(&v, 0, k.rho_ref); }
+
+    struct LoadG {
+        const StripTile &t;
+        uint32_t off;
+        C *f;
+        template <int A> __device__ __forceinline__ void operator()() { f[A] = t.template decode<A>(t.in.load(off, A * t.ds)); }
+    };
+    // f_a(x) of an intermediate state: f*_a(x - e_a), or f*_opp(a)(x) across a wall
+    struct LoadL {
+        const StripTile &t;
+        int row, xs[3]; // first cell of the node's row; x - 1, x, x + 1
+        bool wym, wyp;
+        C *f;
+        template <int A> __device__ __forceinline__ void operator()()
+        {
+            constexpr int ex = ex_of(A), ey = ey_of(A);
+            const bool wall = (ey > 0 && wym) || (ey < 0 && wyp);
+            const int i = wall ? opp_of(A) * FN + row + xs[1] : A * FN + row - ey * W + xs[1 - ex];
+            f[A] = t.template decode<A>(t.pop[i]);
+        }
+    };
+    struct StoreL {
+        const StripTile &t;
+        int cell;
+        const C *f;
+        template <int A> __device__ __forceinline__ void operator()()
+        {
+            Store<S>::template store<A>(t.pop, A * FN + cell, f[A], t.k.rho_ref);
+        }
+    };
+    // f*_a(x) to slot a of x + e_a, or slot opp(a) of x across a wall (the even-state layout)
+    struct StoreG {
+        const StripTile &t;
+        uint32_t xo[3], yo[3]; // byte offsets of x - 1, x, x + 1 and of rows y - 1, y, y + 1
+        bool wym, wyp;
+        const C *f;
+        template <int A> __device__ __forceinline__ void operator()()
+        {
+            constexpr int ex = ex_of(A), ey = ey_of(A);
+            S v;
+            Store<S>::template store<A>(&v, 0, f[A], t.k.rho_ref);
+            const bool wall = (ey > 0 && wyp) || (ey < 0 && wym);
+            t.out.store(wall ? opp_of(A) * t.ds + xo[1] + yo[1] : A * t.ds + xo[1 + ex] + yo[1 + ey], 0, v);
+        }
+    };
+
+    template <int s> __device__ __forceinline__ C density(int x, int dy, C *f)
+    {
+        const int gy = psi_coord(y0 + dy, ny, bcy);
+        if constexpr (s == 1) {
+            LoadG op{*this, (uint32_t)(gy * ld + x) * (uint32_t)sizeof(S), f};
+            for9(op);
+        } else {
+            // LDS row: unwrapped on a periodic axis, the clamped node's across a wall
+            const bool wall = bcy == BC_WALL;
+            const int cy = wall ? gy - y0 : dy;
+            LoadL op{*this, (cy + M) * W, {x == 0 ? nx - 1 : x - 1, x, x == nx - 1 ? 0 : x + 1},
+                     wall && gy == 0, wall && gy == ny - 1, f};
+            for9(op);
+        }
+        C ps, rho;
+        bad |= !node_psi<C>(k, eos, f, ps, rho);
+        psi[pcell(x, dy)] = ps;
+        if (x == 0) psi[pcell(nx, dy)] = ps;
+        if (x == nx - 1) psi[pcell(-1, dy)] = ps;
+        return rho;
+    }
+
+    template <int s> __device__ __forceinline__ void step(int tid)
+    {
+        constexpr int N = cells(s), NI = N + 2 * W, R = (N + NT - 1) / NT, m = 2 * (K - s);
+        C fv[R][9], rho[R];
+#pragma unroll
+        for (int j = 0; j < R; ++j) {
+            const int i = tid + j * NT, x = i % W;
+            // past the cells come the ring rows; an item of them needs no populations later
+            const int dy = i < N ? i / W - m : (i < N + W ? -1 - m : TY + m);
+            if (i < NI && x < nx) rho[j] = density<s>(x, dy, fv[j]);
+        }
+        for (int i = tid + R * NT; i < NI; i += NT) {
+            C fr[9];
+            if (i % W < nx) density<s>(i % W, i < N + W ? -1 - m : TY + m, fr);
+        }
+        __syncthreads();
+#pragma unroll
+        for (int j = 0; j < R; ++j) {
+            const int i = tid + j * NT, x = i % W, dy = i / W - m;
+            if (i < N && x < nx) {
+                C fs[9];
+                collide_node<C>(k, fv[j], rho[j], psi + pcell(x, dy), PX, fs);
+                if constexpr (s < K) {
+                    StoreL op{*this, (dy + M) * W + x, fs};
+                    for9(op);
+                } else if (y0 + dy < ny) {
+                    constexpr uint32_t z = sizeof(S);
+                    const Nbr n = neighbours(x, y0 + dy, nx, ny, BC_PERIODIC, bcy);
+                    StoreG op{*this, {n.xm * z, x * z, n.xp * z}, {n.ym * ld * z, (y0 + dy) * ld * z, n.yp * ld * z},
+                              n.wym, n.wyp, fs};
+                    for9(op);
+                }
+            }
+        }
+        if constexpr (s < K) {
+            __syncthreads();
+            step<s + 1>(tid);
+        }
+    }
+};
+
+template <typename S, int K, int W, int TY, int NT>
+__global__ void __launch_bounds__(NT) strip_kernel(const RunDev *__restrict__ runs, const Tile *__restrict__ tiles, int ntx,
+                                              const S *__restrict__ src, S *__restrict__ dst,
+                                              int32_t *__restrict__ status, int xcd)
+{
+    static_assert(K % 2 == 0, "the state returns to the layout of an even step count");
+    static_assert(!kWriterRef<S>, "FP64 and FP32 storage");
+    using C = typename Store<S>::C;
+    using T = StripTile<S, K, W, TY, NT>;
+    __shared__ C psi[T::PN];
+    __shared__ S pop[9 * T::FN];
+    const int wi = work_index(xcd);
+    const Tile t = ntx > 0 ? Tile{0, 0, wi * TY, 0} : tiles[wi];
+    const RunDev &r = runs[t.run];
+    T m{r.template par<C>(), r.eos_kind, r.nx, r.ny, r.pitch, r.bc_y, t.y0, (uint32_t)r.dstride * (uint32_t)sizeof(S),
+        PopBuf<S>(src + r.f_off), PopBuf<S>(dst + r.f_off), psi, pop};
+    m.template step<1>((int)threadIdx.x);
+    if (m.bad) status[t.run] = 1;
+}
+
 } // namespace lbm
 
 // ------------------------------------------------------------ launchers
@@ -325,6 +481,14 @@ template <typename S, int K, int TX, int TY, int NT> hipError_t launch_multi_t(c
     return hipGetLastError();
 }
 
+template <typename S, int K, int W, int TY, int NT> hipError_t launch_strip_t(const StepArgs &a)
+{
+    hipExtLaunchKernelGGL((strip_kernel<S, K, W, TY, NT>), dim3(a.nmtiles), dim3(NT), 0, a.stream, a.ev_start, a.ev_stop,
+                          0, a.runs, a.mtiles, a.mntx, static_cast<const S *>(a.f), static_cast<S *>(a.f_alt), a.status,
+                          a.xcd);
+    return hipGetLastError();
+}
+
 struct Variant {
     MultiShape shape;
     // vector instructions of a tile, about 93 per density and 200 per collision, times what it loses otherwise
@@ -332,6 +496,7 @@ struct Variant {
     // small tiles of several steps: taken when the work list has no more of them than this
     int64_t max_tiles;
     hipError_t (*launch)(const StepArgs &);
+    bool strip; // grids of at most tile-width nodes along a periodic x; taken where every run is one
 };
 
 template <typename S, int K, int TX, int TY, int NT> constexpr Variant make_variant(int64_t max_tiles, int percent = 100)
@@ -339,10 +504,19 @@ template <typename S, int K, int TX, int TY, int NT> constexpr Variant make_vari
     using Gm = MultiGeom<K, TX, TY>;
     int64_t work = 0;
     for (int s = 1; s <= K; ++s) work += 93 * (Gm::cells(s) + Gm::ring(s)) + 200 * Gm::cells(s);
-    return {{K, TX, TY}, work * percent / 100, max_tiles, launch_multi_t<S, K, TX, TY, NT>};
+    return {{K, TX, TY}, work * percent / 100, max_tiles, launch_multi_t<S, K, TX, TY, NT>, false};
 }
 
-// The variants of one precision, the latency-bound ones (max_tiles > 0) first.
+template <typename S, int K, int W, int TY, int NT> constexpr Variant make_strip()
+{
+    return {{K, W, TY}, 0, INT64_MAX, launch_strip_t<S, K, W, TY, NT>, true};
+}
+
+// The variants of one precision: strips, then the latency-bound ones (max_tiles >
+// 0).  The threads of a strip hold the first step's cells and its two ring rows in
+// one round (256 threads for 4 x 52: 2.0 us instead of 1.9 for one 4 x 256 grid;
+// K = 2 4.6 instead of 3.75 for 256; 4 x 64 and 8 x 64 lose 10-25% on heights
+// that they do not divide).
 // Threads are a multiple of 256 (four waves, one per SIMD: 576 threads ran 20%
 // slower than 512), and the first step's cells fill them in one or two rounds.
 //  - K = 4 tiles for few nodes, where a step is the launch and one chain of
@@ -355,19 +529,21 @@ template <typename S, int K, int TX, int TY, int NT> constexpr Variant make_vari
 //    44, one workgroup a CU, 113.6), 60 x 20 and 64 x 16 fit some heights and widths
 //    better (40 x 100^2 7.3 against 8.2, 40 x 256^2 25.5 against 27.3; 1280 x 1024
 //    15.0 against 15.4 at equal work, hence the charge of 1), 4 x 60 and
-//    8 x 60 grids a few nodes wide (256 of 4 x 256: 5.9 us against 12 with 16 x 16
-//    tiles and 32 with 60 x 20).  FP64 takes 32 x 24: 1008 cells in two rounds of
+//    8 x 60 grids a few nodes wide that no strip takes (256 of 4 x 256: 5.9 us against
+//    12 with 16 x 16 tiles and 32 with 60 x 20).  FP64 takes 32 x 24: 1008 cells in two rounds of
 //    512 threads, rows that start on 256 bytes, two workgroups in the 160 KB (4096
 //    x 2048 163 us against 182 with 28 x 20 and 176 with 32 x 16, more than their
 //    work explains: the charges; 768 threads 232), and those two where they fit
 //    better (40 x 100^2 12.3 against 13.6).
 const Variant kF32[] = {
+    make_strip<float, 4, 4, 52, 320>(), make_strip<float, 4, 8, 50, 512>(),
     make_variant<float, 4, 8, 8, 512>(512),  make_variant<float, 4, 20, 20, 1024>(512),
     make_variant<float, 2, 64, 16, 768>(0),  make_variant<float, 2, 60, 24, 768>(0, 101),
     make_variant<float, 2, 60, 20, 768>(0),
     make_variant<float, 2, 4, 60, 512>(0),   make_variant<float, 2, 8, 60, 768>(0),
 };
 const Variant kF64[] = {
+    make_strip<double, 4, 4, 52, 320>(), make_strip<double, 4, 8, 50, 512>(),
     make_variant<double, 4, 8, 8, 512>(256), make_variant<double, 4, 12, 12, 768>(256),
     make_variant<double, 2, 28, 12, 512>(768), make_variant<double, 2, 32, 24, 512>(0),
     make_variant<double, 2, 32, 16, 512>(0, 105), make_variant<double, 2, 28, 20, 768>(0, 108),
@@ -406,7 +582,12 @@ int pick_multi(int precision, const RunDev *runs, int nruns)
     int64_t least = 0;
     for (int v = 0; const Variant *p = variant(precision, v); ++v) {
         int64_t tiles = 0;
-        for (int i = 0; i < nruns; ++i) tiles += multi_tiles(p->shape, runs[i].nx, runs[i].ny);
+        bool fits = true;
+        for (int i = 0; i < nruns; ++i) {
+            tiles += multi_tiles(p->shape, runs[i].nx, runs[i].ny);
+            fits &= !p->strip || (runs[i].nx <= p->shape.tx && runs[i].bc_x == BC_PERIODIC);
+        }
+        if (!fits) continue;
         if (p->max_tiles > 0) {
             if (tiles <= p->max_tiles) return v;
         } else if (best < 0 || tiles * p->work < least) {

@@ -7,7 +7,7 @@ every population is equal.  The grids sit at the edges of its
 tiles: smaller than a tile's margin, one short of and one past a tile, several
 tiles of each variant (four steps of 8 x 8, 12 x 12 and 20 x 20 nodes; two of
 28 x 12, 28 x 20, 32 x 16, 32 x 24, 64 x 16, 60 x 12, 60 x 20, 60 x 24, 4 x 60 and
-8 x 60), walls on either axis, batches of
+8 x 60; strips of 4 x 52 and 8 x 50), walls on either axis, batches of
 uneven runs; step counts leave remainders and start at odd counts.
 """
 import dataclasses
@@ -75,6 +75,16 @@ def test_single_runs(shape, walls, precision):
 def test_batches(shapes, precision):
     runs = [run(nx, ny, (i // 2) % 2, i % 2, seed=i) for i, (nx, ny) in enumerate(shapes)]
     same(runs, precision, [2, 3, 4])
+
+
+@pytest.mark.parametrize("precision", ["fp64", "fp32", "bf16"])
+@pytest.mark.parametrize("shapes", [[(1, 1)], [(1, 300)], [(4, 52)], [(8, 50)], [(6, 49)], [(5, 101)], [(2, 3)],
+                                    [(4, 51), (3, 53), (1, 105), (2, 2)], [(8, 51), (4, 100), (7, 149), (1, 9)]])
+def test_strips(shapes, precision):
+    """Grids of at most 4 or 8 nodes along a periodic x, walls along y on every second run."""
+    for first in (0, 1):
+        runs = [run(nx, ny, 0, (i + first) % 2, seed=i) for i, (nx, ny) in enumerate(shapes)]
+        same(runs, precision, [4, 8, 1, 9, 2])
 
 
 @pytest.mark.parametrize("precision", ["fp64", "fp32", "bf16"])
