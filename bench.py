@@ -6,10 +6,10 @@ sweep of 40 periodic 256x256 droplets (radii 20..60 x 8 kappa values in
 [0, 0.99]), Carnahan-Starling EOS at T/Tc = 0.7, stepped together in one
 batched FP32 context.  Reported next to it:
   * the plain FP64 path (one run per context, 256x256) and FP64 batched;
-  * roofline of the dominant kernel (the fused step kernel in the workload's
-    default shape; the collide-stream kernel when the two-kernel schedule is
-    chosen with --fused 0 or by --tile auto), timed with HIP events on the
-    library's stream, and the two-kernel schedule timed beside it;
+  * roofline of the dominant kernel (the multi-step kernel, two steps per
+    launch; the collide-stream kernel when the two-kernel schedule is chosen
+    with --fused 0 or by --tile auto), timed with HIP events on the library's
+    stream, and the two-kernel schedule timed beside it;
   * accuracy of FP32 vs FP64 after the full 20,000 steps: surface tension from
     the Laplace fit (pressure jump vs 1/R) per kappa, rho_l/rho_v, per-node rho;
   * the FP64 CPU oracle timed on the host cores on a bounded sample.
@@ -29,19 +29,24 @@ sys.path.insert(0, ROOT)
 
 METRIC = "MLUPS and % HBM roofline, FP32/batched vs plain FP64, at sigma err <0.5%"
 HBM_PEAK_GBS = 8000.0
-KERNEL_SRC = os.path.join(ROOT, "paper_1306_6445_amd", "csrc", "lbm_kernels.hip")
+KERNEL_SRC = os.path.join(ROOT, "paper_1306_6445_amd", "csrc", "lbm_multi.hip")
 # HBM traffic per dispatch of the dominant kernel, written from rocprofv3 counter runs
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "traffic_%s_%s_%s.json")
 
-# step schedule per workload (threads per tile, nodes per thread of the fused
-# kernel), the fastest of an FP32 sweep on MI355X: 256-wide tiles (of 512
-# threads) suit the one large grid, 64-wide ones the batches of small runs
+# steps per launch under the fused schedules: every grid here has more tiles
+# than the four-step shapes take.  A launch reads and writes the state once, so
+# its algorithmic bytes are those of one step
+STEPS_PER_LAUNCH = 2
+# shape of the single steps (an odd count's last one) per workload: threads per
+# tile, nodes per thread of the fused kernel, the fastest of an FP32 sweep on
+# MI355X: 256-wide tiles (of 512 threads) suit the one large grid, 64-wide ones
+# the batches of small runs
 DEFAULT_SHAPE = {"config2": ((64, 4), 2), "config3": ((256, 2), 4), "config4": ((128, 2), 4),
                  "config5": ((64, 4), 2)}
 # algorithmic bytes per lattice update of the collide-stream kernel of the
 # two-kernel schedule: every population read and written once plus one psi read
 COLLIDE_BYTES = {"fp64": 9 * 8 * 2 + 8, "fp32": 9 * 4 * 2 + 4, "bf16": 9 * 2 * 2 + 4}
-# ... and of the fused step: every population read once and written once
+# ... and of a launch of the fused schedules: every population read once and written once
 STEP_BYTES_ALG = {"fp64": 9 * 8 * 2, "fp32": 9 * 4 * 2, "bf16": 9 * 2 * 2}
 # bf16 storage also reads and writes one FP32 writer density per node
 WRITER_BYTES = 8
@@ -61,11 +66,15 @@ def ensure_built():
 
 
 def launch_ms(fused, t_region, k, dispatch_ms):
-    """Mean duration of one launch of the step kernel.  The fused schedule is
-    one launch per step, so the timed region (HIP events on the library's
-    stream) over its k launches gives it directly, launch gaps included; the
-    two-kernel schedule needs the per-dispatch events to separate its kernels."""
+    """Mean duration per step of the step kernel.  The fused schedules launch
+    nothing else, so the timed region (HIP events on the library's stream) over
+    its k steps gives it directly, launch gaps included; the two-kernel schedule
+    needs the per-dispatch events to separate its kernels."""
     return 1e3 * t_region / k if fused else dispatch_ms
+
+
+def steps_a_launch(fused):
+    return STEPS_PER_LAUNCH if fused else 1
 
 
 def timed_steps(L, k, torch):
@@ -426,8 +435,8 @@ HBM_LEGS = (("config3", "capillary wave 4096x2048 (lambda 256), FP32"),
 
 def hbm_resident_block(lbm, torch, graph_steps, steps=256, skip=()):
     """FP32 step kernel of each HBM-resident workload in its default shape:
-    graph-replayed steps timed with HIP events on the library's stream (one
-    launch per step), algorithmic 72 B per node over the launch duration;
+    graph-replayed steps timed with HIP events on the library's stream (two
+    steps per launch), algorithmic 72 B per node over the launch duration;
     then plain FP64 on the 4096 x 2048 grid (one run, same steps), so the FP32
     vs FP64 comparison is made on a grid that fills the GPU."""
     from paper_1306_6445_amd import workloads as WL
@@ -449,15 +458,16 @@ def hbm_resident_block(lbm, torch, graph_steps, steps=256, skip=()):
         L.init_all()
         t, _ = timed_steps(L, steps, torch)
         L.close()
-        ms = 1e3 * t / steps
+        ms = STEPS_PER_LAUNCH * 1e3 * t / steps
         ach = STEP_BYTES_ALG["fp32"] * ntot / (ms * 1e-3) / 1e9
         wset = 2 * 9 * 4 * ntot
         leg = {"workload": desc, "nodes": ntot, "mlups": ntot * steps / t / 1e6, "tile": [tx, ty],
                "fused": fused, "steps": steps, "graph_replays": reps, "eager_steps": eager,
-               "kernel": "fused_kernel<float>", "kernel_ms": ms, "achieved": ach, "peak": HBM_PEAK_GBS,
+               "kernel": "multi_kernel<float>", "steps_per_launch": STEPS_PER_LAUNCH, "kernel_ms": ms,
+               "achieved": ach, "peak": HBM_PEAK_GBS,
                "unit": "GB/s", "frac": ach / HBM_PEAK_GBS, "working_set_bytes": wset,
-               "cache_resident": False,
-               "traffic": traffic_from_profile(ntot, "fused", name, "fp32")}
+               "cache_resident": False, "step_alg_frac": STEPS_PER_LAUNCH * ach / HBM_PEAK_GBS,
+               "traffic": traffic_from_profile(ntot, "multi", name, "fp32")}
         if leg["traffic"]:
             leg["traffic_frac"] = leg["traffic"] / (ms * 1e-3) / 1e9 / HBM_PEAK_GBS
         log("hbm-resident %s: %.1f MLUPS, %.4f ms per launch, %.3f of HBM" % (name, leg["mlups"], ms, leg["frac"]))
@@ -473,9 +483,9 @@ def hbm_resident_block(lbm, torch, graph_steps, steps=256, skip=()):
         t, _ = timed_steps(P, steps, torch)
         P.close()
         n = big[0].nodes
-        ms = 1e3 * t / steps
+        ms = STEPS_PER_LAUNCH * 1e3 * t / steps
         fp64 = {"workload": "capillary wave 4096x2048, FP64, one run", "nodes": n, "mlups": n * steps / t / 1e6,
-                "steps": steps, "kernel_ms": ms,
+                "steps": steps, "steps_per_launch": STEPS_PER_LAUNCH, "kernel_ms": ms,
                 "achieved": STEP_BYTES_ALG["fp64"] * n / (ms * 1e-3) / 1e9}
         fp64["frac"] = fp64["achieved"] / HBM_PEAK_GBS
         fp64["fp32_over_fp64_same_grid"] = out[0]["mlups"] / fp64["mlups"]
@@ -487,8 +497,8 @@ def hbm_resident_block(lbm, torch, graph_steps, steps=256, skip=()):
 def d3q19_block(lbm, torch, steps=32, n=256):
     """The D3Q19 extension on an n^3 periodic drop (CS, T/Tc 0.7, kappa 0.5),
     FP32 and FP64.  Main figures: the default fused schedule (one launch per
-    step; 64 x 8 x-y tiles marching along z through 64 planes in FP32, 128 in
-    FP64, psi of each plane in LDS), MLUPS over `steps` steps between stream
+    step; 64 x 8 x-y tiles marching along z in chunks that the library chooses to
+    fill the CUs, psi of each plane in LDS), MLUPS over `steps` steps between stream
     synchronisations (replayed from HIP graphs of 16 steps where `steps`
     allows, as lbm3d_step does by default, after a warm-up that captures the
     graph) and the fused kernel's mean launch duration from per-dispatch HIP
@@ -501,7 +511,7 @@ def d3q19_block(lbm, torch, steps=32, n=256):
 
     run = WL.config3d(n)
     out = {"workload": "D3Q19 drop %d^3 (R %g), periodic, CS EOS T/Tc=0.7, kappa 0.5, epsilon 1.93" % (n, run.R0),
-           "nodes": run.nodes, "schedule": "fused: 64x8 x-y tiles, z chunks of 64 planes (FP32) / 128 (FP64)"}
+           "nodes": run.nodes, "schedule": "fused: x-y tiles marching along z, the library's default tile and z chunk"}
 
     def timed(L):
         L.step(16)  # warm-up: one graph block (2 x 8 steps), so the graph is captured before the timed region
@@ -524,7 +534,7 @@ def d3q19_block(lbm, torch, steps=32, n=256):
             psi_ms, col_ms = L.time_kernels(10)
         step_alg = 2 * 19 * s
         leg = {"mlups": run.nodes * steps / t / 1e6, "steps": steps, "ms_per_step": 1e3 * t / steps,
-               "kernel": "fused3_kernel<%s, 64, 8>" % ("float" if s == 4 else "double"), "kernel_ms": fused_ms,
+               "kernel": "fused3_kernel<%s>" % ("float" if s == 4 else "double"), "kernel_ms": fused_ms,
                "achieved_GBs": step_alg * run.nodes / (fused_ms * 1e-3) / 1e9,
                "two_pass": {"mlups": run.nodes * steps / t2 / 1e6, "psi_ms": psi_ms, "collide_ms": col_ms,
                             "collide_GBs": (2 * 19 * s + s) * run.nodes / (col_ms * 1e-3) / 1e9,
@@ -545,12 +555,12 @@ def d3q19_block(lbm, torch, steps=32, n=256):
 def mc_block(lbm, torch, steps=64, n=2048):
     """The two-component extension: spinodal decomposition of a 50/50 mixture
     in a periodic n x n box (G = 1, total density 1.05, kappa 0.5), FP32 and
-    FP64 in their default tiles, one fused launch per step.  MLUPS over
+    FP64 in their default tiles, two steps per launch.  MLUPS over
     `steps` steps between stream synchronisations (replayed from HIP graphs of
     16 steps, as lbm_mc_step does by default, after a warm-up that captures
-    the graph); the kernel's mean launch
-    duration from per-dispatch HIP events; algorithmic bytes 2 x 18 s per node
-    (both components' populations read and written once; s = 4 FP32, 8 FP64)."""
+    the graph); the kernel's mean launch duration from per-dispatch HIP events;
+    algorithmic bytes of a launch 2 x 18 s per node (both components' populations
+    read and written once; s = 4 FP32, 8 FP64)."""
     from paper_1306_6445_amd import workloads as WL
 
     run = WL.mc_spinodal_run(n)
@@ -568,13 +578,14 @@ def mc_block(lbm, torch, steps=64, n=2048):
             b.record(L.stream)
             L.synchronize()
             t = a.elapsed_time(b) / 1e3
-            k_ms = L.time_kernels(10)
+            k_ms = STEPS_PER_LAUNCH * L.time_kernels(20)
         alg = 36 * s
         leg = {"mlups": run.nodes * steps / t / 1e6, "steps": steps, "ms_per_step": 1e3 * t / steps,
-               "kernel": "mc_fused_kernel<%s>" % ("float" if s == 4 else "double"), "kernel_ms": k_ms,
+               "kernel": "mc_multi_kernel<%s>" % ("float" if s == 4 else "double"),
+               "steps_per_launch": STEPS_PER_LAUNCH, "kernel_ms": k_ms,
                "achieved_GBs": alg * run.nodes / (k_ms * 1e-3) / 1e9}
         leg["frac"] = leg["achieved_GBs"] / HBM_PEAK_GBS
-        leg["traffic"] = traffic_from_profile(run.nodes, "mcfused", "mc", prec,
+        leg["traffic"] = traffic_from_profile(run.nodes, "mcmulti", "mc", prec,
                                               os.path.join(ROOT, "paper_1306_6445_amd", "csrc", "lbm_mc_kernels.hip"))
         if leg["traffic"]:
             leg["traffic_frac"] = leg["traffic"] / (k_ms * 1e-3) / 1e9 / HBM_PEAK_GBS
@@ -831,8 +842,10 @@ def main():
     repeats = {"n": 5, "steps": rep_k, "median": reps[2], "min": reps[0], "max": reps[4]}
     # dominant kernel: the timed region per launch (fused), or per-dispatch HIP
     # events on the same stream and workload (two kernels; also reported beside)
+    spl = steps_a_launch(fused)
     psi_ms, ev_ms = L.time_kernels(args.timing_steps)
-    col_ms = launch_ms(fused, t_gpu, args.steps, ev_ms)
+    ev_ms *= spl
+    col_ms = spl * launch_ms(fused, t_gpu, args.steps, ev_ms / spl)
     st = L.status()
     two = None
     if fused:
@@ -849,18 +862,21 @@ def main():
                / (p2 * 1e-3) / 1e9,
                "step_alg_frac": ntot * k2 / t2 * (STEP_BYTES_ALG[prec] + wbytes) / 1e9 / HBM_PEAK_GBS}
     L.close()
-    # algorithmic bytes of the dominant kernel: collide reads and writes every
-    # population and reads psi once; the fused kernel is the whole step (72 B)
+    # algorithmic bytes of a launch of the dominant kernel: collide reads and
+    # writes every population and reads psi once; the multi-step kernel reads the
+    # state and writes it two steps later (72 B)
     kbytes = (STEP_BYTES_ALG if fused else COLLIDE_BYTES)[prec] + wbytes
     achieved = kbytes * ntot / (col_ms * 1e-3) / 1e9
-    kname = ("fused_kernel<%s>" if fused else "collide_kernel<%s>") % KERNEL_TYPE[prec]
+    kname = ("multi_kernel<%s>" if fused else "collide_kernel<%s>") % KERNEL_TYPE[prec]
     roof = {"bound": "hbm", "kernel": kname, "achieved": achieved, "peak": HBM_PEAK_GBS,
             "unit": "GB/s", "frac": achieved / HBM_PEAK_GBS,
-            "traffic": traffic_from_profile(ntot, "fused" if fused else "collide", args.workload, prec),
+            "traffic": traffic_from_profile(ntot, "multi" if fused else "collide", args.workload, prec),
             "kernel_ms": col_ms, "kernel_ms_source": "timed region / launches" if fused else "per-dispatch events",
+            "steps_per_launch": spl,
             "kernel_ms_dispatch_events": ev_ms, "psi_ms": psi_ms,
             "psi_achieved_GBs": (9 * STORE_BYTES[prec] + STORE_BYTES[prec if prec == "fp64" else "fp32"]) * ntot
             / (psi_ms * 1e-3) / 1e9 if psi_ms > 0 else None,
+            # of the rate at which a launch per step would stream at 8 TB/s
             "step_alg_frac": mlups * 1e6 * (STEP_BYTES_ALG[prec] + wbytes) / 1e9 / HBM_PEAK_GBS,
             # the two population buffers the step streams through
             "working_set_bytes": 2 * 9 * STORE_BYTES[prec] * ntot,
@@ -918,7 +934,7 @@ def main():
         kbf = min(args.steps, 10000)
         tbf = graph_timed(Bf, kbf, args.warmup, args.graph_steps, torch)
         p_ms, c_ms = Bf.time_kernels(100)
-        c_ms = launch_ms(bfch["fused"], tbf, kbf, c_ms)
+        c_ms = steps_a_launch(bfch["fused"]) * launch_ms(bfch["fused"], tbf, kbf, c_ms)
         Bf.close()
         bbytes = (STEP_BYTES_ALG if bfch["fused"] else COLLIDE_BYTES)["bf16"] + WRITER_BYTES
         out["bf16_batched"] = {"value": ntot * kbf / tbf / 1e6, "unit": "MLUPS", "steps": kbf, "schedule": bfch,
@@ -933,7 +949,7 @@ def main():
             k64 = min(args.steps, 5000)
             t64 = graph_timed(P, k64, args.warmup, args.graph_steps, torch)
             p_ms, c_ms = P.time_kernels(100)
-            c_ms = launch_ms(pch["fused"], t64, k64, c_ms)
+            c_ms = steps_a_launch(pch["fused"]) * launch_ms(pch["fused"], t64, k64, c_ms)
             P.close()
             out["fp64_plain"] = {"value": runs[0].nodes * k64 / t64 / 1e6, "unit": "MLUPS", "steps": k64,
                                  "config": "one %dx%d run per context" % (runs[0].nx, runs[0].ny),
@@ -950,7 +966,7 @@ def main():
             kb = min(args.steps, 5000)
             tb = graph_timed(B, kb, args.warmup, args.graph_steps, torch)
             p_ms, c_ms = B.time_kernels(100)
-            c_ms = launch_ms(bch["fused"], tb, kb, c_ms)
+            c_ms = steps_a_launch(bch["fused"]) * launch_ms(bch["fused"], tb, kb, c_ms)
             B.close()
             out["fp64_batched"] = {"value": ntot * kb / tb / 1e6, "unit": "MLUPS", "steps": kb,
                                    "schedule": bch,

@@ -443,9 +443,10 @@ class Lattice:
         return {"tile": (tx.value, ty.value), "fused": fu.value}
 
     def set_fused(self, rows):
-        """One out-of-place fused kernel per step with `rows` nodes per thread
-        (1, 2 or 4; True = 1) or the two in-place kernels (0 / False); every
-        storage precision."""
+        """Out-of-place fused kernels (1, 2 or 4; True = 1): two or four steps
+        per launch from an even step count, the remaining steps one per launch
+        with `rows` nodes per thread; or the two in-place kernels (0 / False);
+        every storage precision."""
         rows = 1 if rows is True else (0 if not rows else int(rows))
         _check(self._lib.lbm_set_fused(self._ctx, rows), "lbm_set_fused")
 
@@ -483,8 +484,8 @@ def run3_args(run):
 
 
 class Lattice3:
-    """One D3Q19 run on the GPU (include/lbm3d.h): FP64 or FP32 storage, two
-    kernels per step.  Arrays are [z][y][x]; populations [19][nz][ny][nx]."""
+    """One D3Q19 run on the GPU (include/lbm3d.h): FP64 or FP32 storage, one
+    fused launch or two kernels per step (two up to 64^3 nodes by default).  Arrays are [z][y][x]; populations [19][nz][ny][nx]."""
 
     def __init__(self, run, precision: str = "fp32", device: str = "cuda"):
         import torch
@@ -620,7 +621,8 @@ def mc_args(run):
 
 class LatticeMC:
     """One two-component (binary mixture) run on the GPU (include/lbm_mc.h):
-    FP64 or FP32 storage, one fused launch per step.  Fields are [ny][nx];
+    FP64 or FP32 storage, two or four steps per launch (one from an odd step
+    count or for a remainder).  Fields are [ny][nx];
     populations [2][9][ny][nx] (component A first)."""
 
     def __init__(self, run, precision: str = "fp32", device: str = "cuda"):
@@ -691,7 +693,7 @@ class LatticeMC:
         _check(self._lib.lbm_mc_set_tile(self._ctx, int(tx), int(ty), int(rows)), "lbm_mc_set_tile")
 
     def set_graph_steps(self, k: int):
-        """step() replays HIP graphs of 2k steps (0: one launch per step)."""
+        """step() replays HIP graphs of 2k steps (0: plain launches)."""
         _check(self._lib.lbm_mc_set_graph_steps(self._ctx, int(k)), "lbm_mc_set_graph_steps")
 
     def autotune(self, steps: int = 20) -> tuple:
