@@ -17,7 +17,7 @@
 // in one launch and K launches give the same bits.
 //
 // Measured against one step per launch (us per step): 4096 x 2048 FP32 142 ->
-// 88, FP64 261 -> 163; 40 x 256^2 FP32 32.7 -> 25.1, FP64 87 -> 57; 64 uneven
+// 88, FP64 261 -> 158; 40 x 256^2 FP32 32.7 -> 25.1, FP64 87 -> 57; 64 uneven
 // drops FP32 128 -> 77; 2048 x 1024 with walls FP32 27.8 -> 21; 100^2 FP64 6.0 ->
 // 2.2; 256 grids of 4 x 256 FP32 38 -> 3.75 (strips); 40 x 256^2 bf16 40.9 -> 32.1, 64
 // uneven drops bf16 125 -> 93.
@@ -517,7 +517,7 @@ template <typename S, int K, int W, int TY, int NT> constexpr Variant make_strip
 // one round (256 threads for 4 x 52: 2.0 us instead of 1.9 for one 4 x 256 grid;
 // K = 2 4.6 instead of 3.75 for 256; 4 x 64 and 8 x 64 lose 10-25% on heights
 // that they do not divide).
-// Threads are a multiple of 256 (four waves, one per SIMD: 576 threads ran 20%
+// Threads of a tile are a multiple of 256 (four waves, one per SIMD: 576 ran 20%
 // slower than 512), and the first step's cells fill them in one or two rounds.
 //  - K = 4 tiles for few nodes, where a step is the launch and one chain of
 //    latencies: the smaller the tile the shorter the chain, as long as each
@@ -528,13 +528,14 @@ template <typename S, int K, int W, int TY, int NT> constexpr Variant make_strip
 //    2048 87.7 us against 89.0 with 60 x 20, 2048 x 1024 20.4 against 21.4; 60 x
 //    44, one workgroup a CU, 113.6), 60 x 20 and 64 x 16 fit some heights and widths
 //    better (40 x 100^2 7.3 against 8.2, 40 x 256^2 25.5 against 27.3; 1280 x 1024
-//    15.0 against 15.4 at equal work, hence the charge of 1), 4 x 60 and
-//    8 x 60 grids a few nodes wide that no strip takes (256 of 4 x 256: 5.9 us against
-//    12 with 16 x 16 tiles and 32 with 60 x 20).  FP64 takes 32 x 24: 1008 cells in two rounds of
-//    512 threads, rows that start on 256 bytes, two workgroups in the 160 KB (4096
-//    x 2048 163 us against 182 with 28 x 20 and 176 with 32 x 16, more than their
-//    work explains: the charges; 768 threads 232), and those two where they fit
-//    better (40 x 100^2 12.3 against 13.6).
+//    15.0 against 15.4 at equal work, hence the charge of 1%), 4 x 60 and 8 x 60
+//    grids a few nodes wide that no strip takes (256 of 4 x 256: 5.9 us against 12
+//    with 16 x 16 tiles and 32 with 60 x 20).
+//  - FP64 takes 32 x 24: 1008 cells in two rounds of 512 threads, rows that start
+//    on 256 bytes, two workgroups in the 160 KB (4096 x 2048 158 us against 181 with
+//    28 x 20 and 176 with 32 x 16, more than their work explains: the charges of 8
+//    and 5%; 768 threads 232), and those two where they fit better (40 x 100^2 12.3
+//    against 13.6).
 const Variant kF32[] = {
     make_strip<float, 4, 4, 52, 320>(), make_strip<float, 4, 8, 50, 512>(),
     make_variant<float, 4, 8, 8, 512>(512),  make_variant<float, 4, 20, 20, 1024>(512),
