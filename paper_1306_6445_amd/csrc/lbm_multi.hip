@@ -521,8 +521,11 @@ template <typename S, int K, int W, int TY, int NT> constexpr Variant make_strip
 // slower than 512), and the first step's cells fill them in one or two rounds.
 //  - K = 4 tiles for few nodes, where a step is the launch and one chain of
 //    latencies: the smaller the tile the shorter the chain, as long as each
-//    tile has a CU of its own (FP64: 100^2 2.2 us a step with 8 x 8 against 2.5
-//    with 12 x 12; 256^2 4.3 / 3.8 / 3.7 with 8 x 8, 12 x 12 and 28 x 12, K = 2);
+//    tile has a CU of its own, 256 of them (FP32, us a step: 180^2 2.23 with 12 x
+//    12 against 2.7 with 529 tiles of 8 x 8, 256^2 2.44 with 16 x 16 against 2.74
+//    with 20 x 20, 300^2 2.85 with 20 x 20 against 3.23; bf16 180^2 2.75 / 3.3,
+//    256^2 2.98 / 3.34), then two to a CU (350^2 3.3 with 16 x 16 against 3.8;
+//    FP64 256^2 3.8 with 12 x 12 against 3.87 with 28 x 12 and K = 2);
 //  - otherwise the shape with the least work, counting whole tiles: 60 x 24 has
 //    the smallest margins that leave two workgroups a CU (72 KB of LDS; 4096 x
 //    2048 87.7 us against 89.0 with 60 x 20, 2048 x 1024 20.4 against 21.4; 60 x
@@ -538,14 +541,16 @@ template <typename S, int K, int W, int TY, int NT> constexpr Variant make_strip
 //    against 13.6).
 const Variant kF32[] = {
     make_strip<float, 4, 4, 52, 320>(), make_strip<float, 4, 8, 50, 512>(),
-    make_variant<float, 4, 8, 8, 512>(512),  make_variant<float, 4, 20, 20, 1024>(512),
+    make_variant<float, 4, 8, 8, 512>(256),  make_variant<float, 4, 12, 12, 768>(256),
+    make_variant<float, 4, 16, 16, 1024>(256), make_variant<float, 4, 20, 20, 1024>(256),
+    make_variant<float, 4, 16, 16, 1024>(512), make_variant<float, 4, 20, 20, 1024>(512),
     make_variant<float, 2, 64, 16, 768>(0),  make_variant<float, 2, 60, 24, 768>(0, 101),
     make_variant<float, 2, 60, 20, 768>(0),
     make_variant<float, 2, 4, 60, 512>(0),   make_variant<float, 2, 8, 60, 768>(0),
 };
 const Variant kF64[] = {
     make_strip<double, 4, 4, 52, 320>(), make_strip<double, 4, 8, 50, 512>(),
-    make_variant<double, 4, 8, 8, 512>(256), make_variant<double, 4, 12, 12, 768>(256),
+    make_variant<double, 4, 8, 8, 512>(256), make_variant<double, 4, 12, 12, 768>(512),
     make_variant<double, 2, 28, 12, 512>(768), make_variant<double, 2, 32, 24, 512>(0),
     make_variant<double, 2, 32, 16, 512>(0, 105), make_variant<double, 2, 28, 20, 768>(0, 108),
     make_variant<double, 2, 4, 60, 512>(0),
@@ -555,7 +560,8 @@ const Variant kF64[] = {
 // and step): 512 threads for 64 x 16 tiles measured 32.1 us on 40 x 256^2 drops
 // against 32.5 with 768 and 34.9 with 64 x 12 tiles.
 const Variant kBf16[] = {
-    make_variant<bf16_t, 4, 8, 8, 512>(256),   make_variant<bf16_t, 4, 20, 20, 1024>(256),
+    make_variant<bf16_t, 4, 8, 8, 512>(256),   make_variant<bf16_t, 4, 12, 12, 768>(256),
+    make_variant<bf16_t, 4, 16, 16, 1024>(256), make_variant<bf16_t, 4, 20, 20, 1024>(256),
     make_variant<bf16_t, 2, 28, 12, 512>(768), make_variant<bf16_t, 2, 64, 16, 512>(0),
     make_variant<bf16_t, 2, 60, 12, 512>(0),   make_variant<bf16_t, 2, 4, 60, 512>(0),
 };

@@ -5,7 +5,8 @@ The multi-step kernel runs the collision of the single-step kernels on the same
 rounded states (bf16 storage: the same writer densities and rounding bits), so
 every population is equal.  The grids sit at the edges of its
 tiles: smaller than a tile's margin, one short of and one past a tile, several
-tiles of each variant (four steps of 8 x 8, 12 x 12 and 20 x 20 nodes; two of
+tiles of each variant (four steps of 8 x 8, 12 x 12, 16 x 16 and 20 x 20
+nodes; two of
 28 x 12, 28 x 20, 32 x 16, 32 x 24, 64 x 16, 60 x 12, 60 x 20, 60 x 24, 4 x 60 and
 8 x 60; strips of 4 x 52 and 8 x 50), walls on either axis, batches of
 uneven runs; step counts leave remainders and start at odd counts.
@@ -56,7 +57,8 @@ def same(runs, precision, steps, graph_steps=None):
 
 
 SMALL = [(1, 1), (2, 3), (5, 1), (7, 9), (8, 8), (16, 17), (33, 25), (100, 61)]
-LARGE = [(240, 200), (257, 241), (640, 33), (1200, 500), (700, 641), (599, 601), (607, 623)]
+LARGE = [(240, 200), (257, 241), (640, 33), (1200, 500), (700, 641), (599, 601), (607, 623),
+         (145, 133), (209, 225), (301, 281), (353, 337), (401, 399)]
 
 
 @pytest.mark.parametrize("precision", ["fp64", "fp32", "bf16"])
