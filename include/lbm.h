@@ -171,7 +171,10 @@ lbm_status lbm_create(const lbm_grid *grid, const lbm_eos *eos, double G,
 lbm_status lbm_init_density(lbm_ctx *ctx, const double *rho, const double *ux,
                             const double *uy);
 
-/* Enqueue n >= 0 time steps of every run in the context (Eqs. 6, 7, 19, 17, 4). */
+/* Enqueue n >= 0 time steps of every run in the context (Eqs. 6, 7, 19, 17, 4).
+ * While the caller captures the stream the steps are recorded, one to a launch,
+ * and the context takes one step to a launch from then on: an even n leaves the
+ * state where the recorded launches start, so each replay advances it by n. */
 lbm_status lbm_step(lbm_ctx *ctx, int64_t n);
 
 /* Density and Eq. (6) velocity of run 0 into host arrays [ny][nx]; ux, uy may

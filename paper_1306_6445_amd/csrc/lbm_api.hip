@@ -208,6 +208,7 @@ struct lbm_ctx {
     int multi = -1;                 // its variant; -1: none (single steps only)
     lbm::MultiShape mshape{0, 0, 0};
     bool single_steps = false;      // set while the autotuner times the single-step shapes
+    bool recorded = false;          // steps were recorded by a capture of the caller's (see caller_captures)
     Layout L;
     unsigned char *ws = nullptr;
     bool own_ws = false;
@@ -224,6 +225,7 @@ struct lbm_ctx {
     int cur = 0;           // population buffer holding the current state (0: L.f, 1: L.f2), and its rounding seeds
     int rflip = 0;         // bf16 storage: 1 when the writer densities R0, R1 have changed places (L.r1, L.r0)
     hipGraphExec_t graph[4] = {};  // 2k steps from population buffer `cur` with the writer densities `rflip`
+    hipGraphExec_t retired[4] = {}; // those of before `recorded`: a replay may still run
     int graph_cur = 0, graph_rflip = 0; // 1: a replay ends on the other buffer / flip than it started from
     bool graph_failed = false;
 
@@ -276,7 +278,7 @@ namespace {
 // blocks that a 32-bit byte offset spans.
 int multi_variant(const lbm_ctx *c)
 {
-    if (!c->fused || c->single_steps || c->halo != 1) return -1;
+    if (!c->fused || c->single_steps || c->recorded || c->halo != 1) return -1;
     for (const lbm::RunDev &r : c->rdev)
         if ((uint64_t)r.dstride * 9 * pop_bytes(c->precision) >= (uint64_t)1 << 32) return -1;
     return lbm::pick_multi(kernel_precision(c->precision), c->rdev.data(), c->nruns);
@@ -334,11 +336,12 @@ lbm_status upload_run(lbm_ctx *c, int run)
 
 void drop_graph(lbm_ctx *c)
 {
-    for (hipGraphExec_t &g : c->graph)
-        if (g) {
-            (void)hipGraphExecDestroy(g);
-            g = nullptr;
-        }
+    for (auto *list : {&c->graph, &c->retired})
+        for (hipGraphExec_t &g : *list)
+            if (g) {
+                (void)hipGraphExecDestroy(g);
+                g = nullptr;
+            }
 }
 
 lbm::RunDev make_rundev(const lbm_run_desc &d)
@@ -514,6 +517,22 @@ void moved(lbm_ctx *c, int64_t taken)
     if (c->fused) c->cur ^= 1;
     if (taken > 1 && c->precision == LBM_FP32_BF16STORE) c->rflip ^= 1;
     c->steps += taken;
+}
+
+// Whether the caller captures the stream.  On such a stream, and from then on, a
+// launch takes one step: the buffers then change places each step, so an even
+// number of steps leaves the state in the buffer that a caller's graph starts
+// from, replay after replay (several steps a launch would leave it in the other
+// one, and each replay would repeat the first).
+bool caller_captures(lbm_ctx *c)
+{
+    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(c->stream, &st) != hipSuccess) (void)hipGetLastError();
+    if (st == hipStreamCaptureStatusNone) return false;
+    if (!c->recorded) std::swap(c->graph, c->retired);
+    c->recorded = true;
+    c->multi = -1;
+    return true;
 }
 
 lbm_status step_eager(lbm_ctx *c, int64_t n)
@@ -775,8 +794,9 @@ lbm_status lbm_step(lbm_ctx *ctx, int64_t n)
     if (n < 0) return fail(LBM_EINVAL, "negative step count");
     if (n == 0) return LBM_OK;
     LBM_HIP(hipSetDevice(ctx->device));
+    const bool captured = caller_captures(ctx);
     const int64_t block = 2 * (int64_t)ctx->graph_k;
-    if (ctx->graph_k > 0 && !ctx->graph_failed && n >= block + ctx->parity()) {
+    if (!captured && ctx->graph_k > 0 && !ctx->graph_failed && n >= block + ctx->parity()) {
         if (ctx->parity()) {
             s = step_eager(ctx, 1);
             --n;

@@ -102,11 +102,13 @@ struct lbm_mc_ctx {
     int tx = 64, ty = 4, rows = 2;
     int graph_k = 8;                  // lbm_mc_step replays HIP graphs of 2 graph_k steps (0: eager)
     hipGraphExec_t graph[2] = {};     // 2 graph_k steps from population buffer 0 / 1
+    hipGraphExec_t retired[2] = {};   // those of before `recorded`: a replay may still run
     int graph_swap = 0;               // 1: a replay ends on the other buffer than it started from
     bool graph_failed = false;
     int multi = -1;                   // variant of the multi-step kernel; -1: single steps
     lbm::MultiShape mshape{0, 0, 0};
     bool single_steps = false;        // set while the autotuner times the single-step tiles
+    bool recorded = false;            // steps were recorded by a capture of the caller's (see caller_captures_mc)
     int64_t nodes() const { return run.nodes; }
     unsigned char *fbuf(int k) { return ws + (k ? L.f2 : L.f); }
     lbmmc::RunMC *drun() { return reinterpret_cast<lbmmc::RunMC *>(ws + L.run); }
@@ -178,18 +180,32 @@ namespace {
 
 void drop_graph_mc(lbm_mc_ctx *c)
 {
-    for (hipGraphExec_t &g : c->graph)
-        if (g) {
-            (void)hipGraphExecDestroy(g);
-            g = nullptr;
-        }
+    for (auto *list : {&c->graph, &c->retired})
+        for (hipGraphExec_t &g : *list)
+            if (g) {
+                (void)hipGraphExecDestroy(g);
+                g = nullptr;
+            }
+}
+
+// Whether the caller captures the stream.  On such a stream, and from then on, a
+// launch takes one step, so that an even number of steps leaves the state in the
+// buffer that a caller's graph starts from and each replay advances it.
+bool caller_captures_mc(lbm_mc_ctx *c)
+{
+    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(c->stream, &st) != hipSuccess) (void)hipGetLastError();
+    if (st == hipStreamCaptureStatusNone) return false;
+    if (!c->recorded) std::swap(c->graph, c->retired);
+    c->recorded = true;
+    return true;
 }
 
 // One launch of the multi-step kernel when at least its steps remain, else one
 // step; the buffers change places in `a`, `taken` receives the steps.
 hipError_t launch_some_mc(const lbm_mc_ctx *c, lbmmc::StepMCArgs &a, int64_t left, int64_t *taken)
 {
-    const bool multi = c->multi >= 0 && !c->single_steps && left >= c->mshape.steps;
+    const bool multi = c->multi >= 0 && !c->single_steps && !c->recorded && left >= c->mshape.steps;
     const hipError_t e = multi ? lbmmc::launch_multi_mc(kprec(c->precision), c->multi, a)
                                : lbmmc::launch_step_mc(kprec(c->precision), a);
     *taken = multi ? c->mshape.steps : 1;
@@ -361,8 +377,9 @@ lbm_status lbm_mc_step(lbm_mc_ctx *ctx, int64_t n)
     if (!ctx) return failmc(LBM_EINVAL, "null context");
     if (n < 0) return failmc(LBM_EINVAL, "negative step count");
     LBMMC_HIP(hipSetDevice(ctx->device));
+    const bool captured = caller_captures_mc(ctx);
     const int64_t block = 2 * (int64_t)ctx->graph_k;
-    while (ctx->graph_k > 0 && !ctx->graph_failed && n >= block) {
+    while (!captured && ctx->graph_k > 0 && !ctx->graph_failed && n >= block) {
         if (!ctx->graph[ctx->cur]) {
             build_graph_mc(ctx);
             continue;
