@@ -47,7 +47,7 @@ Layout layout(int max_batch)
     L.m2 = o, o += align256(pb);
     L.grad = o, o += align256(pb);
     L.partial = o, o += align256(pb * nch);
-    L.ploss = o, o += align256(sizeof(float) * nch);
+    L.ploss = o, o += align256(sizeof(double) * nch);
     L.inv = o, o += align256(sizeof(float));
     L.total = o;
     return L;
@@ -71,6 +71,7 @@ struct lbm_mlp {
     int64_t t = 0; // Adam steps taken
 
     float *f(size_t off) { return reinterpret_cast<float *>(ws + off); }
+    double *ploss() { return reinterpret_cast<double *>(ws + L.ploss); }
 };
 
 namespace {
@@ -97,12 +98,12 @@ lbm_status weight_sum(lbm_mlp *net, const float *m, int32_t n)
 
 lbm_status read_loss(lbm_mlp *net, int nch, double *loss)
 {
-    std::vector<float> pl(nch);
-    MLP_HIP(hipMemcpyAsync(pl.data(), net->f(net->L.ploss), sizeof(float) * nch, hipMemcpyDeviceToHost,
+    std::vector<double> pl(nch);
+    MLP_HIP(hipMemcpyAsync(pl.data(), net->ploss(), sizeof(double) * nch, hipMemcpyDeviceToHost,
                            net->stream));
     MLP_HIP(hipStreamSynchronize(net->stream));
     double s = 0.0;
-    for (float v : pl) s += v;
+    for (double v : pl) s += v;
     *loss = s;
     return LBM_OK;
 }
@@ -193,7 +194,7 @@ lbm_status lbm_mlp_loss_grad(lbm_mlp *net, const float *x, const float *t, const
     if ((s = weight_sum(net, m, n)) != LBM_OK) return s;
     const int nch = M::chunks(n);
     MLP_HIP(M::launch_grad(net->f(net->L.theta), x, t, m, n, net->f(net->L.inv), net->f(net->L.partial),
-                           net->f(net->L.ploss), net->stream));
+                           net->ploss(), net->stream));
     M::AdamArgs a{};
     a.update = 0;
     MLP_HIP(M::launch_adam(net->f(net->L.theta), net->f(net->L.m1), net->f(net->L.m2), net->f(net->L.partial), nch,
@@ -229,7 +230,7 @@ lbm_status lbm_mlp_train(lbm_mlp *net, const float *x, const float *t, const flo
         a.c2 = (float)(1.0 / (1.0 - std::pow((double)beta2, (double)tt)));
         a.update = 1;
         MLP_HIP(M::launch_grad(net->f(net->L.theta), x, t, m, n, net->f(net->L.inv), net->f(net->L.partial),
-                               net->f(net->L.ploss), net->stream));
+                               net->ploss(), net->stream));
         MLP_HIP(M::launch_adam(net->f(net->L.theta), net->f(net->L.m1), net->f(net->L.m2), net->f(net->L.partial),
                                nch, nullptr, a, net->stream));
         net->t = tt;

@@ -41,7 +41,7 @@ struct Smem {
     float W1[H * IN], b1[H], W2[H * LDW], b2[H], W3[OUT * H], b3[4];
     float x[CH * IN];
     float dy[OUT * CH];  // [k][s]
-    float red[NT];
+    double red[H];
 };
 
 __device__ __forceinline__ void load_params(Smem &S, const float *__restrict__ th)
@@ -153,14 +153,16 @@ __global__ void __launch_bounds__(WS) weight_sum_kernel(const float *__restrict_
 __global__ void __launch_bounds__(NT) grad_kernel(const float *__restrict__ th, const float *__restrict__ x,
                                                   const float *__restrict__ tg, const float *__restrict__ mw, int n,
                                                   const float *__restrict__ inv_wsum, float *__restrict__ partial,
-                                                  float *__restrict__ ploss)
+                                                  double *__restrict__ ploss)
 {
     __shared__ __align__(16) Smem S;
     const int t = threadIdx.x, lane = t & (H - 1), w = t >> 6, s = 2 * w;
     const float iw = inv_wsum[0];
     load_params(S, th);
-    // the workgroup's sums: dW2[NW w + i][lane], one entry of dW3 and b3, of dW1 and b1, of b2, the loss
-    float g2[H / NW] = {}, g3 = 0.0f, g1 = 0.0f, gb2 = 0.0f, lsum = 0.0f;
+    // the workgroup's sums: dW2[NW w + i][lane], one entry of dW3 and b3, of dW1 and b1, of b2, the loss (in FP64:
+    // past MAX_SLOTS chunks a thread adds one term of each of its chunks)
+    float g2[H / NW] = {}, g3 = 0.0f, g1 = 0.0f, gb2 = 0.0f;
+    double lsum = 0.0;
     for (int64_t s0 = (int64_t)blockIdx.x * CH; s0 < n; s0 += (int64_t)gridDim.x * CH) {
         load_inputs(S, x, s0, n);
         __syncthreads();
@@ -175,7 +177,8 @@ __global__ void __launch_bounds__(NT) grad_kernel(const float *__restrict__ th, 
                 const float r = output_unit(S, k, q) - tg[e];
                 const float mr = mw[e] * r;
                 d = mr * iw;
-                lsum += 0.5f * iw * (mr * r);
+                const float share = 0.5f * iw * (mr * r);
+                lsum += (double)share;
             }
             S.dy[k * CH + q] = d;
         }
@@ -263,7 +266,7 @@ __global__ void __launch_bounds__(NT) grad_kernel(const float *__restrict__ th, 
     else if (t < IN * H + H)
         g[OFF_B1 + lane] = g1;
     // the loss share (only the first OUT * CH threads hold one)
-    S.red[t] = lsum;
+    if (t < H) S.red[t] = lsum;
     __syncthreads();
     for (int o = H / 2; o > 0; o >>= 1) {
         if (t < o) S.red[t] += S.red[t + o];
@@ -320,7 +323,7 @@ hipError_t launch_weight_sum(const float *m, int n, float *inv, hipStream_t st)
 }
 
 hipError_t launch_grad(const float *th, const float *x, const float *tg, const float *mw, int n, const float *inv,
-                       float *partial, float *ploss, hipStream_t st)
+                       float *partial, double *ploss, hipStream_t st)
 {
     hipLaunchKernelGGL(grad_kernel, dim3(chunks(n)), dim3(NT), 0, st, th, x, tg, mw, n, inv, partial,
                        ploss);

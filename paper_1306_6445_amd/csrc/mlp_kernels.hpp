@@ -27,7 +27,7 @@ int chunks(int n); // workgroups (and gradient slots) for a batch of n
 hipError_t launch_forward(const float *th, const float *x, int n, float *y, hipStream_t st);
 hipError_t launch_weight_sum(const float *m, int n, float *inv, hipStream_t st);
 hipError_t launch_grad(const float *th, const float *x, const float *tg, const float *mw, int n, const float *inv,
-                       float *partial, float *ploss, hipStream_t st);
+                       float *partial, double *ploss, hipStream_t st);
 hipError_t launch_adam(float *th, float *m1, float *m2, const float *partial, int nch, float *grad, const AdamArgs &a,
                        hipStream_t st);
 
