@@ -341,19 +341,19 @@ __global__ void __launch_bounds__(kThreads3) collide3_kernel(const Run3 *__restr
 // nodes of the current plane collide with the psi of planes z - 1, z, z + 1
 // and store into the other buffer.  Each node's populations are gathered once
 // (streamed from planes z, z + 1, z + 2 of the source), for its psi, and wait
-// in the thread's own LDS column for their collision one plane later: held in
-// registers they took FP32 to 128 and FP64 to 223 registers (4 and 2 waves per
-// SIMD).  The ring's populations are re-read from cache.  Four slots let one
-// barrier per plane suffice: the slot a plane's psi goes into was last read two
-// planes earlier, before the previous barrier.  Out of place, so every
-// workgroup reads only the unmodified source buffer.
+// in the thread's own LDS column for their collision one plane later (FP32: all in
+// registers took 128 of them; FP64: see fused3_park).  The ring's populations are
+// re-read from cache.  Four slots let one barrier per plane suffice: the slot a
+// plane's psi goes into was last read two planes earlier, before the previous
+// barrier.  Out of place, so every workgroup reads only the unmodified source
+// buffer.
 // What bounds it: a plane is a chain of load latency, density, barrier and
 // collision, so each thread loads the populations of the plane after next
 // before it collides (160^3 FP32 171 -> 154 us a step; the ring's loads ahead as
 // well cost registers, 220 us), and the 38 shifted or aligned streams, which
 // move 5.0 TB/s of counted traffic at 256^3 against 5.14 of a probe without
 // arithmetic.  160^3 FP32 304 -> 147 us with the chunk of its default schedule,
-// 256^3 619 -> 549, 96^3 FP64 517 -> 62.
+// 256^3 619 -> 549, 96^3 FP64 517 -> 60.
 //
 // How a tile's populations are addressed (MODE), the same slots in each:
 //   kFlat   no wall within reach and each buffer below 4 GiB: a buffer
@@ -362,15 +362,20 @@ __global__ void __launch_bounds__(kThreads3) collide3_kernel(const Run3 *__restr
 //   kWall32 walls, below 4 GiB; kWide 64-bit addresses.
 constexpr int kFlat = 0, kWall32 = 1, kWide = 2;
 
-// LDS of a workgroup: four psi planes, and the waiting populations where both
-// fit the default allocation of 64 KB (larger tiles keep them in registers).
-template <typename C> constexpr bool fused3_park(int TX, int TY)
+// Directions whose waiting populations sit in LDS, beside the four psi planes in
+// the 160 KB of a CU; the others wait in registers.  All 19 where they fit, but
+//  - 12 in FP64 with 512 threads and 32-bit offsets, whose 256 registers hold the
+//    other 7: with all in registers the kernel spilled 104 bytes a lane, with all
+//    in LDS it is slower (160^3 266 us a step spilling, 268 with 12 or 8, 276 with
+//    19; 256^3 1024, 1026, 1055).  With 64-bit addresses 19 are faster (320 x 320 x
+//    328: 2325 us, 2476 with 12, 3418 spilling);
+//  - 15 in FP64 with 1,024 threads, all that fit (128 registers: what is left over
+//    spills, and no loads ahead: 160^3 521 us, 1588 with all in registers).
+template <typename C> constexpr int fused3_park(int TX, int TY, bool w32)
 {
-    return sizeof(C) * (4 * (TX + 2) * (TY + 2) + 19 * TX * TY) <= 65536;
-}
-template <typename C> constexpr uint32_t fused3_lds(int TX, int TY)
-{
-    return (uint32_t)sizeof(C) * (4 * (TX + 2) * (TY + 2) + (fused3_park<C>(TX, TY) ? 19 * TX * TY : 0));
+    const int fit = (163840 / (int)sizeof(C) - 4 * (TX + 2) * (TY + 2)) / (TX * TY);
+    if (sizeof(C) == 8 && TX * TY == 512 && w32) return 12;
+    return fit < 19 ? fit : 19;
 }
 
 template <typename S, int TX, int TY, int MODE, bool NTS>
@@ -381,7 +386,9 @@ __device__ __forceinline__ bool fused3_tile(const Run3 &r, const S *__restrict__
 {
     using C = typename std::conditional<std::is_same<S, double>::value, double, float>::type;
     constexpr int PX = TX + 2, PLANE = PX * (TY + 2), NT = TX * TY;
-    constexpr bool PARK = fused3_park<C>(TX, TY);
+    constexpr int PARK = fused3_park<C>(TX, TY, MODE != kWide);
+    // loads ahead of the collision where the registers hold them
+    constexpr bool AHEAD = sizeof(C) == 4 || NT <= 512;
     constexpr uint32_t sz = sizeof(S);
     const int nx = r.r.nx, ny = r.r.ny, nz = r.nz, bcx = r.r.bc_x, bcy = r.r.bc_y, bcz = r.bc_z;
     const RunPar<C> k = r.r.template par<C>();
@@ -421,10 +428,10 @@ __device__ __forceinline__ bool fused3_tile(const Run3 &r, const S *__restrict__
         return rho;
     };
     const int tid = (int)threadIdx.x;
-    C kept[PARK ? 1 : 19];
+    C kept[PARK < 19 ? 19 - PARK : 1];
     C rc = C(0); // density of the waiting populations
     C fv[19]; // populations of the next plane, loaded ahead of the collision
-    gather(lbm::psi_coord(q.z0 - 1, nz, bcz), q.cx, q.cy, q.col, fv);
+    if (AHEAD) gather(lbm::psi_coord(q.z0 - 1, nz, bcz), q.cx, q.cy, q.col, fv);
     for (int zl = q.z0 - 1; zl <= q.z1; ++zl) {
         // psi of plane zl, tile and ring
         if (q.ring) {
@@ -432,23 +439,24 @@ __device__ __forceinline__ bool fused3_tile(const Run3 &r, const S *__restrict__
             gather(lbm::psi_coord(zl, nz, bcz), q.rcx, q.rcy, q.rcol, fr);
             put_psi(zl, q.rcell, fr);
         }
+        if (!AHEAD) gather(lbm::psi_coord(zl, nz, bcz), q.cx, q.cy, q.col, fv);
         const C rho = put_psi(zl, q.cell, fv);
         // the populations of plane zl - 1 out, those of zl in
         C fc[19];
 #pragma unroll
         for (int a = 0; a < 19; ++a) {
-            if constexpr (PARK) {
+            if (a < PARK) {
                 fc[a] = park[a * NT + tid];
                 park[a * NT + tid] = fv[a];
             } else {
-                fc[a] = kept[a];
-                kept[a] = fv[a];
+                fc[a] = kept[a - PARK];
+                kept[a - PARK] = fv[a];
             }
         }
         const C rcc = rc;
         rc = rho;
         __syncthreads();
-        if (zl < q.z1) gather(lbm::psi_coord(zl + 1, nz, bcz), q.cx, q.cy, q.col, fv);
+        if (AHEAD && zl < q.z1) gather(lbm::psi_coord(zl + 1, nz, bcz), q.cx, q.cy, q.col, fv);
         const int z = zl - 1;
         if (z < q.z0 || !q.active) continue;
         C fs[19];
@@ -476,8 +484,7 @@ __global__ void __launch_bounds__(TX * TY) fused3_kernel(const Run3 *__restrict_
     using C = typename std::conditional<std::is_same<S, double>::value, double, float>::type;
     constexpr int PLANE = (TX + 2) * (TY + 2), NT = TX * TY;
     static_assert(PLANE - NT <= NT, "one ring node per thread at most");
-    extern __shared__ unsigned char lds3[];
-    C *lps = reinterpret_cast<C *>(lds3), *park = lps + 4 * PLANE;
+    __shared__ C lps[4 * PLANE], park[fused3_park<C>(TX, TY, W32) * NT];
     const Run3 &r = runs[0];
     const int nx = r.r.nx, ny = r.r.ny, nz = r.nz;
     const Fused3Thread q = fused3_thread((unsigned)lbm::work_index(1), threadIdx.x, nx, ny, nz, r.r.bc_x, r.r.bc_y, zc, TX, TY);
@@ -643,9 +650,8 @@ static unsigned blocks3(int64_t n) { return (unsigned)((n + kThreads3 - 1) / kTh
 template <typename S, int TX, int TY> hipError_t fused3_t(const Step3Args &a)
 {
     const dim3 grid(fused3_blocks(a.nx, a.ny, a.nz, TX, TY, a.zchunk)), block(TX * TY);
-    constexpr uint32_t lds = fused3_lds<S>(TX, TY);
     auto go = [&](auto kernel) {
-        hipExtLaunchKernelGGL(kernel, grid, block, lds, a.stream, a.ev_col0, a.ev_col1, 0, a.run,
+        hipExtLaunchKernelGGL(kernel, grid, block, 0, a.stream, a.ev_col0, a.ev_col1, 0, a.run,
                               static_cast<const S *>(a.fin), static_cast<S *>(a.fout), a.status, a.zchunk);
     };
     if (!a.w32)
