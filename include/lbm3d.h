@@ -138,9 +138,10 @@ int64_t lbm3d_steps_taken(const lbm3d_ctx *ctx);
  * small that a launch would exceed 2^32 threads. */
 lbm_status lbm3d_set_schedule(lbm3d_ctx *ctx, int32_t fused, int32_t tile_x, int32_t tile_y, int32_t z_chunk);
 
-/* Schedule autotuner: times `steps` (>= 1) steps of each of eight candidate
- * schedules (fused 64 x 8 with z chunks of 32, 64 and 128 planes, 64 x 4,
- * 32 x 8, 32 x 16 and 64 x 16 with 64, and the two-pass schedule) on the
+/* Schedule autotuner: times `steps` (>= 1) steps of each candidate schedule
+ * (fused 64 x 8 with z chunks of 32, 64 and 128 planes, 64 x 4, 32 x 8, 32 x 16
+ * and 64 x 16 with 64, the two-pass schedule, and, where they are fused, the
+ * context's current schedule and that of a new context of this grid) on the
  * context's own state, which advances by (steps + 1) per candidate, and sets
  * the fastest; the choice goes to the non-NULL outputs.  Every schedule gives
  * the same bits.  Synchronises. */

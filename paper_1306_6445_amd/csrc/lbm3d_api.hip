@@ -636,8 +636,15 @@ lbm_status lbm3d_autotune(lbm3d_ctx *ctx, int32_t steps, int32_t *fused, int32_t
     struct Cand {
         int fused, tx, ty, zc;
     };
-    const Cand cands[] = {{1, 64, 8, 64}, {1, 64, 8, 128}, {1, 64, 8, 32}, {1, 64, 4, 64}, {1, 32, 8, 64},
-                          {1, 32, 16, 64}, {1, 64, 16, 64}, {0, 64, 8, 64}};
+    const Cand keep = {ctx->fused, ctx->tile_x, ctx->tile_y, ctx->zchunk};
+    Cand cands[10] = {{1, 64, 8, 64}, {1, 64, 8, 128}, {1, 64, 8, 32}, {1, 64, 4, 64}, {1, 32, 8, 64},
+                      {1, 32, 16, 64}, {1, 64, 16, 64}, {0, 64, 8, 64}};
+    int ncands = 8;
+    // and the schedule in place and that of a new context, whose chunks follow the grid (two passes are in the list)
+    if (keep.fused) cands[ncands++] = keep;
+    default_schedule(ctx);
+    if (ctx->fused) cands[ncands++] = {1, ctx->tile_x, ctx->tile_y, ctx->zchunk};
+    ctx->fused = keep.fused, ctx->tile_x = keep.tx, ctx->tile_y = keep.ty, ctx->zchunk = keep.zc;
     hipEvent_t e0 = nullptr, e1 = nullptr;
     LBM3_HIP(hipEventCreate(&e0));
     hipError_t he = hipEventCreate(&e1);
@@ -645,11 +652,11 @@ lbm_status lbm3d_autotune(lbm3d_ctx *ctx, int32_t steps, int32_t *fused, int32_t
         (void)hipEventDestroy(e0);
         return fail3(LBM_EDEVICE, std::string("hipEventCreate: ") + hipGetErrorString(he));
     }
-    const Cand keep = {ctx->fused, ctx->tile_x, ctx->tile_y, ctx->zchunk};
     Cand pick = keep;
     float best = 0.f;
     lbm_status rc = LBM_OK;
-    for (const Cand &c : cands) {
+    for (int i = 0; i < ncands; ++i) {
+        const Cand &c = cands[i];
         // candidates that do not fit this grid's launch limits are skipped
         if (lbm3d_set_schedule(ctx, c.fused, c.tx, c.ty, c.zc) != LBM_OK) continue;
         if ((rc = lbm3d_step(ctx, 1)) != LBM_OK) break; // warm-up
