@@ -1325,18 +1325,20 @@ lbm_status lbm_autotune(lbm_ctx *ctx, int32_t steps, int32_t *tx, int32_t *ty, i
         (void)hipEventDestroy(e0);
         return fail(LBM_EDEVICE, std::string("hipEventCreate: ") + hipGetErrorString(he));
     }
-    const int64_t n = steps + (steps & 1);
+    // milliseconds a step, over at least `steps` steps and whole launches
     auto timed = [&](const Cand &c, float &ms) -> lbm_status {
         lbm_status r = lbm_set_tile(ctx, c.tx, c.ty);
         if (r == LBM_OK) r = lbm_set_fused(ctx, c.fused);
-        // one untimed replay builds the graph
-        if (r == LBM_OK) r = lbm_step(ctx, 2 * (int64_t)std::max(ctx->graph_k, 1));
+        // one untimed replay builds the graph; launches of several steps start at an even count
+        if (r == LBM_OK) r = lbm_step(ctx, 2 * (int64_t)std::max(ctx->graph_k, 1) + ctx->parity());
         if (r != LBM_OK) return r;
+        const int64_t n = lbm::timed_steps(steps, ctx->multi >= 0 ? ctx->mshape.steps : 2);
         hipError_t e = hipEventRecord(e0, ctx->stream);
         if (e == hipSuccess && (r = lbm_step(ctx, n)) != LBM_OK) return r;
         if (e == hipSuccess) e = hipEventRecord(e1, ctx->stream);
         if (e == hipSuccess) e = hipEventSynchronize(e1);
         if (e == hipSuccess) e = hipEventElapsedTime(&ms, e0, e1);
+        ms /= (float)n;
         return e == hipSuccess ? LBM_OK : fail(LBM_EDEVICE, std::string("autotune timing: ") + hipGetErrorString(e));
     };
     // the shapes are those of the single steps: the multi-step kernel is off while they are timed

@@ -77,6 +77,12 @@ inline int64_t multi_tiles(const MultiShape &s, int nx, int ny)
 {
     return (int64_t)((nx + s.tx - 1) / s.tx) * ((ny + s.ty - 1) / s.ty);
 }
+// Steps, at least n of them, that time a schedule of `per_launch` steps a launch:
+// whole launches, from an even step count.
+inline int64_t timed_steps(int64_t n, int per_launch)
+{
+    return (n + per_launch - 1) / per_launch * per_launch;
+}
 // Shape of variant v of a precision; false when there is none.
 bool multi_shape(int precision, int v, MultiShape &s);
 // The variant for these runs; -1 when the precision has none.
