@@ -33,10 +33,6 @@ KERNEL_SRC = os.path.join(ROOT, "paper_1306_6445_amd", "csrc", "lbm_multi.hip")
 # HBM traffic per dispatch of the dominant kernel, written from rocprofv3 counter runs
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "traffic_%s_%s_%s.json")
 
-# steps per launch under the fused schedules: every grid here has more tiles
-# than the four-step shapes take.  A launch reads and writes the state once, so
-# its algorithmic bytes are those of one step
-STEPS_PER_LAUNCH = 2
 # shape of the single steps (an odd count's last one) per workload: threads per
 # tile, nodes per thread of the fused kernel, the fastest of an FP32 sweep on
 # MI355X: 256-wide tiles (of 512 threads) suit the one large grid, 64-wide ones
@@ -46,7 +42,8 @@ DEFAULT_SHAPE = {"config2": ((64, 4), 2), "config3": ((256, 2), 4), "config4": (
 # algorithmic bytes per lattice update of the collide-stream kernel of the
 # two-kernel schedule: every population read and written once plus one psi read
 COLLIDE_BYTES = {"fp64": 9 * 8 * 2 + 8, "fp32": 9 * 4 * 2 + 4, "bf16": 9 * 2 * 2 + 4}
-# ... and of a launch of the fused schedules: every population read once and written once
+# ... and of a launch of the fused schedules, which takes the context's steps_per_launch
+# steps: every population read once and written once
 STEP_BYTES_ALG = {"fp64": 9 * 8 * 2, "fp32": 9 * 4 * 2, "bf16": 9 * 2 * 2}
 # bf16 storage also reads and writes one FP32 writer density per node
 WRITER_BYTES = 8
@@ -73,8 +70,13 @@ def launch_ms(fused, t_region, k, dispatch_ms):
     return 1e3 * t_region / k if fused else dispatch_ms
 
 
-def steps_a_launch(fused):
-    return STEPS_PER_LAUNCH if fused else 1
+def step_kernel(L, fused, prec, nodes, t_region, k, dispatch_ms):
+    """(milliseconds, algorithmic GB/s) of a launch of a one-component context's
+    step kernel: a fused launch takes L.steps_per_launch steps, the collide
+    kernel one."""
+    ms = L.steps_per_launch * launch_ms(fused, t_region, k, dispatch_ms)
+    nbytes = (STEP_BYTES_ALG if fused else COLLIDE_BYTES)[prec] + (WRITER_BYTES if prec == "bf16" else 0)
+    return ms, nbytes * nodes / (ms * 1e-3) / 1e9
 
 
 def timed_steps(L, k, torch):
@@ -435,8 +437,8 @@ HBM_LEGS = (("config3", "capillary wave 4096x2048 (lambda 256), FP32"),
 
 def hbm_resident_block(lbm, torch, graph_steps, steps=256, skip=()):
     """FP32 step kernel of each HBM-resident workload in its default shape:
-    graph-replayed steps timed with HIP events on the library's stream (two
-    steps per launch), algorithmic 72 B per node over the launch duration;
+    graph-replayed steps timed with HIP events on the library's stream,
+    algorithmic 72 B per node over the launch duration;
     then plain FP64 on the 4096 x 2048 grid (one run, same steps), so the FP32
     vs FP64 comparison is made on a grid that fills the GPU."""
     from paper_1306_6445_amd import workloads as WL
@@ -457,16 +459,16 @@ def hbm_resident_block(lbm, torch, graph_steps, steps=256, skip=()):
         warm_graph(L, 0, k)
         L.init_all()
         t, _ = timed_steps(L, steps, torch)
+        spl = L.steps_per_launch
+        ms, ach = step_kernel(L, fused, "fp32", ntot, t, steps, None)
         L.close()
-        ms = STEPS_PER_LAUNCH * 1e3 * t / steps
-        ach = STEP_BYTES_ALG["fp32"] * ntot / (ms * 1e-3) / 1e9
         wset = 2 * 9 * 4 * ntot
         leg = {"workload": desc, "nodes": ntot, "mlups": ntot * steps / t / 1e6, "tile": [tx, ty],
                "fused": fused, "steps": steps, "graph_replays": reps, "eager_steps": eager,
-               "kernel": "multi_kernel<float>", "steps_per_launch": STEPS_PER_LAUNCH, "kernel_ms": ms,
+               "kernel": "multi_kernel<float>", "steps_per_launch": spl, "kernel_ms": ms,
                "achieved": ach, "peak": HBM_PEAK_GBS,
                "unit": "GB/s", "frac": ach / HBM_PEAK_GBS, "working_set_bytes": wset,
-               "cache_resident": False, "step_alg_frac": STEPS_PER_LAUNCH * ach / HBM_PEAK_GBS,
+               "cache_resident": False, "step_alg_frac": spl * ach / HBM_PEAK_GBS,
                "traffic": traffic_from_profile(ntot, "multi", name, "fp32")}
         if leg["traffic"]:
             leg["traffic_frac"] = leg["traffic"] / (ms * 1e-3) / 1e9 / HBM_PEAK_GBS
@@ -481,12 +483,12 @@ def hbm_resident_block(lbm, torch, graph_steps, steps=256, skip=()):
         warm_graph(P, 0, k)
         P.init_all()
         t, _ = timed_steps(P, steps, torch)
-        P.close()
         n = big[0].nodes
-        ms = STEPS_PER_LAUNCH * 1e3 * t / steps
+        spl = P.steps_per_launch
+        ms, ach = step_kernel(P, True, "fp64", n, t, steps, None)
+        P.close()
         fp64 = {"workload": "capillary wave 4096x2048, FP64, one run", "nodes": n, "mlups": n * steps / t / 1e6,
-                "steps": steps, "steps_per_launch": STEPS_PER_LAUNCH, "kernel_ms": ms,
-                "achieved": STEP_BYTES_ALG["fp64"] * n / (ms * 1e-3) / 1e9}
+                "steps": steps, "steps_per_launch": spl, "kernel_ms": ms, "achieved": ach}
         fp64["frac"] = fp64["achieved"] / HBM_PEAK_GBS
         fp64["fp32_over_fp64_same_grid"] = out[0]["mlups"] / fp64["mlups"]
         log("fp64 plain 4096x2048: %.1f MLUPS" % fp64["mlups"])
@@ -555,7 +557,7 @@ def d3q19_block(lbm, torch, steps=32, n=256):
 def mc_block(lbm, torch, steps=64, n=2048):
     """The two-component extension: spinodal decomposition of a 50/50 mixture
     in a periodic n x n box (G = 1, total density 1.05, kappa 0.5), FP32 and
-    FP64 in their default tiles, two steps per launch.  MLUPS over
+    FP64 in their default tiles, several steps per launch.  MLUPS over
     `steps` steps between stream synchronisations (replayed from HIP graphs of
     16 steps, as lbm_mc_step does by default, after a warm-up that captures
     the graph); the kernel's mean launch duration from per-dispatch HIP events;
@@ -578,11 +580,12 @@ def mc_block(lbm, torch, steps=64, n=2048):
             b.record(L.stream)
             L.synchronize()
             t = a.elapsed_time(b) / 1e3
-            k_ms = STEPS_PER_LAUNCH * L.time_kernels(20)
+            spl = L.steps_per_launch
+            k_ms = spl * L.time_kernels(20)
         alg = 36 * s
         leg = {"mlups": run.nodes * steps / t / 1e6, "steps": steps, "ms_per_step": 1e3 * t / steps,
                "kernel": "mc_multi_kernel<%s>" % ("float" if s == 4 else "double"),
-               "steps_per_launch": STEPS_PER_LAUNCH, "kernel_ms": k_ms,
+               "steps_per_launch": spl, "kernel_ms": k_ms,
                "achieved_GBs": alg * run.nodes / (k_ms * 1e-3) / 1e9}
         leg["frac"] = leg["achieved_GBs"] / HBM_PEAK_GBS
         leg["traffic"] = traffic_from_profile(run.nodes, "mcmulti", "mc", prec,
@@ -842,10 +845,10 @@ def main():
     repeats = {"n": 5, "steps": rep_k, "median": reps[2], "min": reps[0], "max": reps[4]}
     # dominant kernel: the timed region per launch (fused), or per-dispatch HIP
     # events on the same stream and workload (two kernels; also reported beside)
-    spl = steps_a_launch(fused)
+    spl = L.steps_per_launch
     psi_ms, ev_ms = L.time_kernels(args.timing_steps)
+    col_ms, achieved = step_kernel(L, fused, prec, ntot, t_gpu, args.steps, ev_ms)
     ev_ms *= spl
-    col_ms = spl * launch_ms(fused, t_gpu, args.steps, ev_ms / spl)
     st = L.status()
     two = None
     if fused:
@@ -864,13 +867,13 @@ def main():
     L.close()
     # algorithmic bytes of a launch of the dominant kernel: collide reads and
     # writes every population and reads psi once; the multi-step kernel reads the
-    # state and writes it two steps later (72 B)
+    # state and writes it some steps later (72 B in FP32)
     kbytes = (STEP_BYTES_ALG if fused else COLLIDE_BYTES)[prec] + wbytes
-    achieved = kbytes * ntot / (col_ms * 1e-3) / 1e9
-    kname = ("multi_kernel<%s>" if fused else "collide_kernel<%s>") % KERNEL_TYPE[prec]
+    kernel = ("multi" if spl > 1 else "fused") if fused else "collide"
+    kname = "%s_kernel<%s>" % (kernel, KERNEL_TYPE[prec])
     roof = {"bound": "hbm", "kernel": kname, "achieved": achieved, "peak": HBM_PEAK_GBS,
             "unit": "GB/s", "frac": achieved / HBM_PEAK_GBS,
-            "traffic": traffic_from_profile(ntot, "multi" if fused else "collide", args.workload, prec),
+            "traffic": traffic_from_profile(ntot, kernel, args.workload, prec),
             "kernel_ms": col_ms, "kernel_ms_source": "timed region / launches" if fused else "per-dispatch events",
             "steps_per_launch": spl,
             "kernel_ms_dispatch_events": ev_ms, "psi_ms": psi_ms,
@@ -934,11 +937,11 @@ def main():
         kbf = min(args.steps, 10000)
         tbf = graph_timed(Bf, kbf, args.warmup, args.graph_steps, torch)
         p_ms, c_ms = Bf.time_kernels(100)
-        c_ms = steps_a_launch(bfch["fused"]) * launch_ms(bfch["fused"], tbf, kbf, c_ms)
+        spl = Bf.steps_per_launch
+        c_ms, gbs = step_kernel(Bf, bfch["fused"], "bf16", ntot, tbf, kbf, c_ms)
         Bf.close()
-        bbytes = (STEP_BYTES_ALG if bfch["fused"] else COLLIDE_BYTES)["bf16"] + WRITER_BYTES
         out["bf16_batched"] = {"value": ntot * kbf / tbf / 1e6, "unit": "MLUPS", "steps": kbf, "schedule": bfch,
-                               "step_kernel_GBs": bbytes * ntot / (c_ms * 1e-3) / 1e9, "kernel_ms": c_ms,
+                               "steps_per_launch": spl, "step_kernel_GBs": gbs, "kernel_ms": c_ms,
                                "psi_ms": p_ms}
         # ---- plain FP64: one run per context
         if args.workload != "config4":
@@ -949,13 +952,13 @@ def main():
             k64 = min(args.steps, 5000)
             t64 = graph_timed(P, k64, args.warmup, args.graph_steps, torch)
             p_ms, c_ms = P.time_kernels(100)
-            c_ms = steps_a_launch(pch["fused"]) * launch_ms(pch["fused"], t64, k64, c_ms)
+            spl = P.steps_per_launch
+            c_ms, gbs = step_kernel(P, pch["fused"], "fp64", runs[0].nodes, t64, k64, c_ms)
             P.close()
             out["fp64_plain"] = {"value": runs[0].nodes * k64 / t64 / 1e6, "unit": "MLUPS", "steps": k64,
                                  "config": "one %dx%d run per context" % (runs[0].nx, runs[0].ny),
                                  "schedule": pch,
-                                 "step_kernel_GBs": (STEP_BYTES_ALG if pch["fused"] else COLLIDE_BYTES)["fp64"]
-                                 * runs[0].nodes / (c_ms * 1e-3) / 1e9}
+                                 "steps_per_launch": spl, "step_kernel_GBs": gbs}
             out["fp32_batched_over_fp64_plain"] = mlups / out["fp64_plain"]["value"]
         # ---- FP64 batched
         if len(runs) > 1:
@@ -966,12 +969,12 @@ def main():
             kb = min(args.steps, 5000)
             tb = graph_timed(B, kb, args.warmup, args.graph_steps, torch)
             p_ms, c_ms = B.time_kernels(100)
-            c_ms = steps_a_launch(bch["fused"]) * launch_ms(bch["fused"], tb, kb, c_ms)
+            spl = B.steps_per_launch
+            c_ms, gbs = step_kernel(B, bch["fused"], "fp64", ntot, tb, kb, c_ms)
             B.close()
             out["fp64_batched"] = {"value": ntot * kb / tb / 1e6, "unit": "MLUPS", "steps": kb,
                                    "schedule": bch,
-                                   "step_kernel_GBs": (STEP_BYTES_ALG if bch["fused"] else COLLIDE_BYTES)["fp64"]
-                                   * ntot / (c_ms * 1e-3) / 1e9}
+                                   "steps_per_launch": spl, "step_kernel_GBs": gbs}
         if args.accuracy_steps:
             log("accuracy: %d steps" % args.accuracy_steps)
             if args.workload == "config2":

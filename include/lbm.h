@@ -212,6 +212,10 @@ lbm_status lbm_set_populations(lbm_ctx *ctx, const double *f);
 /* Steps taken since the last initialisation. */
 int64_t lbm_steps_taken(const lbm_ctx *ctx);
 
+/* Steps of a launch that lbm_step makes from an even step count while at least
+ * that many remain (1, 2 or 4; see lbm_set_fused); -1 for a null context. */
+int32_t lbm_steps_per_launch(const lbm_ctx *ctx);
+
 /* Checkpoint: the raw population storage of every run, the step counter and
  * (bf16 storage) the writer densities and the rounding seed, so that a
  * restart continues bit for bit.  lbm_state_bytes() gives the size; load

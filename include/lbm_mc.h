@@ -136,6 +136,10 @@ lbm_status lbm_mc_autotune(lbm_mc_ctx *ctx, int32_t steps, int32_t *tx, int32_t 
 lbm_status lbm_mc_time_kernels(lbm_mc_ctx *ctx, int64_t n, double *step_ms);
 
 int64_t lbm_mc_steps_taken(const lbm_mc_ctx *ctx);
+
+/* Steps of a launch that lbm_mc_step makes while at least that many remain (1,
+ * 2 or 4); -1 for a null context. */
+int32_t lbm_mc_steps_per_launch(const lbm_mc_ctx *ctx);
 void lbm_mc_destroy(lbm_mc_ctx *ctx);
 
 #ifdef __cplusplus

@@ -726,6 +726,8 @@ lbm_status lbm_create(const lbm_grid *grid, const lbm_eos *eos, double G, const 
 
 int32_t lbm_num_runs(const lbm_ctx *ctx) { return ctx ? ctx->nruns : 0; }
 
+int32_t lbm_steps_per_launch(const lbm_ctx *ctx) { return !ctx ? -1 : (ctx->multi >= 0 ? ctx->mshape.steps : 1); }
+
 int64_t lbm_steps_taken(const lbm_ctx *ctx) { return ctx ? ctx->steps : -1; }
 
 void lbm_destroy(lbm_ctx *ctx)

@@ -201,11 +201,14 @@ bool caller_captures_mc(lbm_mc_ctx *c)
     return true;
 }
 
+// steps of a launch while at least that many remain
+int launch_steps_mc(const lbm_mc_ctx *c) { return c->multi < 0 || c->single_steps || c->recorded ? 1 : c->mshape.steps; }
+
 // One launch of the multi-step kernel when at least its steps remain, else one
 // step; the buffers change places in `a`, `taken` receives the steps.
 hipError_t launch_some_mc(const lbm_mc_ctx *c, lbmmc::StepMCArgs &a, int64_t left, int64_t *taken)
 {
-    const bool multi = c->multi >= 0 && !c->single_steps && !c->recorded && left >= c->mshape.steps;
+    const bool multi = launch_steps_mc(c) > 1 && left >= c->mshape.steps;
     const hipError_t e = multi ? lbmmc::launch_multi_mc(kprec(c->precision), c->multi, a)
                                : lbmmc::launch_step_mc(kprec(c->precision), a);
     *taken = multi ? c->mshape.steps : 1;
@@ -411,6 +414,8 @@ lbm_status lbm_mc_set_graph_steps(lbm_mc_ctx *ctx, int32_t k)
     ctx->graph_failed = false;
     return LBM_OK;
 }
+
+int32_t lbm_mc_steps_per_launch(const lbm_mc_ctx *ctx) { return ctx ? launch_steps_mc(ctx) : -1; }
 
 int64_t lbm_mc_steps_taken(const lbm_mc_ctx *ctx) { return ctx ? ctx->steps : -1; }
 

@@ -100,6 +100,7 @@ SIGNATURES = {
                                ctypes.c_double, ctypes.POINTER(Diag)]),
     "lbm_get_populations": (_I32, [_P, _D]),
     "lbm_set_populations": (_I32, [_P, _D]),
+    "lbm_steps_per_launch": (_I32, [_P]),
     "lbm_steps_taken": (ctypes.c_int64, [_P]),
     "lbm_state_bytes": (ctypes.c_size_t, [_P]),
     "lbm_save_state": (_I32, [_P, _P, ctypes.c_size_t]),
@@ -168,6 +169,7 @@ SIGNATURES = {
     "lbm_mc_autotune": (_I32, [_P, _I32] + [ctypes.POINTER(_I32)] * 3),
     "lbm_mc_set_graph_steps": (_I32, [_P, _I32]),
     "lbm_mc_time_kernels": (_I32, [_P, ctypes.c_int64, _D]),
+    "lbm_mc_steps_per_launch": (_I32, [_P]),
     "lbm_mc_steps_taken": (ctypes.c_int64, [_P]),
     "lbm_mc_destroy": (None, [_P]),
     "lbm3d_destroy": (None, [_P]),
@@ -314,6 +316,11 @@ class Lattice:
     @property
     def steps_taken(self) -> int:
         return int(self._lib.lbm_steps_taken(self._ctx))
+
+    @property
+    def steps_per_launch(self) -> int:
+        """Steps of a launch of step() from an even step count."""
+        return int(self._lib.lbm_steps_per_launch(self._ctx))
 
     def shape(self, run: int) -> tuple:
         return int(self.runs[run].ny), int(self.runs[run].nx)
@@ -673,6 +680,11 @@ class LatticeMC:
     @property
     def steps_taken(self) -> int:
         return int(self._lib.lbm_mc_steps_taken(self._ctx))
+
+    @property
+    def steps_per_launch(self) -> int:
+        """Steps of a launch of step()."""
+        return int(self._lib.lbm_mc_steps_per_launch(self._ctx))
 
     def init_density(self, rhoA, rhoB, ux=None, uy=None):
         f = lambda a: None if a is None else np.ascontiguousarray(a, dtype=np.float64).reshape(self.shape)
