@@ -314,7 +314,8 @@ lbm_status lbm_set_tile(lbm_ctx *ctx, int32_t tx, int32_t ty);
  * > 0, no multi-range run and every run's populations below 4 GiB, lbm_step
  * advances two or four steps per launch from an even step count while at
  * least as many remain (tiles of the library's choice, the intermediate
- * states in LDS); tx, ty and rows then shape the remaining
+ * states in LDS; not on many flat grids or long ones, a few nodes high, which
+ * such tiles would overhang); tx, ty and rows then shape the remaining
  * single steps.  Every schedule gives the same bits.  Default: 2.
  * LBM_EINVAL for other values.  Drops any captured graph; synchronises. */
 lbm_status lbm_set_fused(lbm_ctx *ctx, int32_t rows);

@@ -274,14 +274,14 @@ struct lbm_ctx {
 namespace {
 
 // Variant of the multi-step kernel, -1 for single steps only: it needs the
-// second population buffer (fused schedule), the single-range force, and run
-// blocks that a 32-bit byte offset spans.
+// second population buffer (fused schedule), the single-range force, run blocks
+// that a 32-bit byte offset spans, and tiles that the grids fill.
 int multi_variant(const lbm_ctx *c)
 {
     if (!c->fused || c->single_steps || c->recorded || c->halo != 1) return -1;
     for (const lbm::RunDev &r : c->rdev)
         if ((uint64_t)r.dstride * 9 * pop_bytes(c->precision) >= (uint64_t)1 << 32) return -1;
-    return lbm::pick_multi(kernel_precision(c->precision), c->rdev.data(), c->nruns);
+    return lbm::pick_multi(kernel_precision(c->precision), c->rdev.data(), c->nruns, c->tx, c->ty, c->fused);
 }
 
 // Work lists: tiles of every run in row-major order, runs one after another.

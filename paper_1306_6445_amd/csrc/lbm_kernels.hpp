@@ -85,8 +85,9 @@ inline int64_t timed_steps(int64_t n, int per_launch)
 }
 // Shape of variant v of a precision; false when there is none.
 bool multi_shape(int precision, int v, MultiShape &s);
-// The variant for these runs; -1 when the precision has none.
-int pick_multi(int precision, const RunDev *runs, int nruns);
+// The variant for these runs; -1 where single steps of tx x ty threads with `rows`
+// nodes each are better.
+int pick_multi(int precision, const RunDev *runs, int nruns, int tx, int ty, int rows);
 // From an even step count: f -> f_alt, shape.steps steps later (bf16 storage:
 // r1 -> r0 and seed -> seed_alt, whose roles the caller then swaps).
 hipError_t launch_multi(int precision, int v, const StepArgs &a);

@@ -583,10 +583,31 @@ bool multi_shape(int precision, int v, MultiShape &s)
     return p != nullptr;
 }
 
-int pick_multi(int precision, const RunDev *runs, int nruns)
+// Vector instructions of a single step with tiles of tx x (rows ty) nodes (93 per
+// density, 200 per collision, as above): waves beyond the grid's last row or
+// column do no work, the ring is whole.
+static int64_t single_work(const RunDev &r, int tx, int ty, int rows)
+{
+    const int wide = tx < 64 ? tx : 64, high = ty * rows;
+    const int64_t tiles = multi_tiles({1, tx, high}, r.nx, r.ny);
+    return (int64_t)((r.nx + wide - 1) / wide * wide) * r.ny * (93 + 200) + tiles * 93 * (2 * (tx + 2) + 2 * high);
+}
+
+// Besides the shapes' own rules, single steps stay where the rows of tiles beyond
+// flat grids cost more than the launches save: when the tiles outnumber the
+// resident workgroups (three a CU in bf16, two otherwise), several steps a launch
+// are taken up to 1.65 times the work of as many single steps.  Measured, us a
+// step, single against several: at 1.5 times the work 200 grids of 64 x 34 FP32 9.5
+// / 8.9, FP64 15.4 / 14.3; at 1.6 100 of 400 x 8 bf16 10.9 / 8.5; at 1.7 200000 x 8
+// bf16 29.3 / 29.5; at 2.2 200000 x 8 FP32 23.7 / 27.4, FP64 39.9 / 49.0, 100 of 400 x
+// 8 8.3 / 8.3 and 13.0 / 13.9; at 4 1000000 x 4 FP32 78 / 113.  With fewer tiles the
+// chain of a launch counts, not the work (at 2.2 20000 x 8 FP32 6.3 / 5.7, at 1.7
+// 40000 x 8 bf16 10.8 / 8.2).
+int pick_multi(int precision, const RunDev *runs, int nruns, int tx, int ty, int rows)
 {
     int best = -1;
-    int64_t least = 0;
+    int64_t least = 0, single = 0, launched = 0;
+    for (int i = 0; i < nruns; ++i) single += single_work(runs[i], tx, ty, rows);
     for (int v = 0; const Variant *p = variant(precision, v); ++v) {
         int64_t tiles = 0;
         bool fits = true;
@@ -600,9 +621,11 @@ int pick_multi(int precision, const RunDev *runs, int nruns)
         } else if (best < 0 || tiles * p->work < least) {
             best = v;
             least = tiles * p->work;
+            launched = tiles;
         }
     }
-    return best;
+    const int64_t resident = precision == PREC_BF16 ? 768 : 512;
+    return best >= 0 && launched > resident && 100 * least > 165 * variant(precision, best)->shape.steps * single ? -1 : best;
 }
 
 hipError_t launch_multi(int precision, int v, const StepArgs &a)
