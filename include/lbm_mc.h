@@ -80,7 +80,8 @@ lbm_status lbm_mc_init_density(lbm_mc_ctx *ctx, const double *rhoA, const double
  * while at least 2k remain, see lbm_mc_set_graph_steps; launches for the
  * rest).  Where each population buffer is below 4 GiB a launch advances two or
  * four steps while at least as many remain (tiles of the library's choice, the
- * intermediate states in LDS), otherwise one.  A launch also takes one step
+ * intermediate states in LDS; not on long grids a few nodes high, which such
+ * tiles would overhang), otherwise one.  A launch also takes one step
  * while the caller captures the stream and from then on: an even n leaves the
  * state where the recorded launches start, so each replay advances it by n. */
 lbm_status lbm_mc_step(lbm_mc_ctx *ctx, int64_t n);

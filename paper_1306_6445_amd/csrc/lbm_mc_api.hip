@@ -201,6 +201,14 @@ bool caller_captures_mc(lbm_mc_ctx *c)
     return true;
 }
 
+// the multi-step variant beside the single-step tile in place
+void pick_shape_mc(lbm_mc_ctx *c)
+{
+    c->multi = !c->args().w32 ? -1
+                              : lbmmc::pick_multi_mc(kprec(c->precision), c->grid.nx, c->grid.ny, c->tx, c->ty, c->rows,
+                                                     c->mshape);
+}
+
 // steps of a launch while at least that many remain
 int launch_steps_mc(const lbm_mc_ctx *c) { return c->multi < 0 || c->single_steps || c->recorded ? 1 : c->mshape.steps; }
 
@@ -282,7 +290,7 @@ lbm_status lbm_mc_create(const lbm_grid *grid, const lbm_mc_params *p, int32_t p
     c->tx = precision == LBM_FP32 ? 128 : 64;
     c->ty = precision == LBM_FP32 ? 4 : 8;
     c->rows = 1;
-    if (c->args().w32) c->multi = lbmmc::pick_multi_mc(kprec(precision), grid->nx, grid->ny, c->mshape);
+    pick_shape_mc(c);
     if (workspace && workspace_bytes < c->L.total) {
         delete c;
         return failmc(LBM_ENOMEM, "workspace smaller than lbm_mc_workspace_bytes()");
@@ -429,6 +437,7 @@ lbm_status lbm_mc_set_tile(lbm_mc_ctx *ctx, int32_t tx, int32_t ty, int32_t rows
     ctx->tx = tx;
     ctx->ty = ty;
     ctx->rows = rows;
+    pick_shape_mc(ctx);
     LBMMC_HIP(hipSetDevice(ctx->device));
     LBMMC_HIP(hipStreamSynchronize(ctx->stream));
     drop_graph_mc(ctx); // the captured launches carry the tile

@@ -672,7 +672,15 @@ const VariantMC *variant_mc(int precision, int v)
 
 } // namespace
 
-int pick_multi_mc(int precision, int nx, int ny, lbm::MultiShape &shape)
+// Besides the shapes' own rules, single steps (of tx x ty threads, `rows` nodes
+// each) stay where the tiles' rows beyond a flat grid cost more than the launches
+// save: when the tiles outnumber the resident workgroups, two a CU, several steps a
+// launch are taken up to 2.6 times the work of as many single steps (waves beyond
+// the grid's last row or column do none).  Measured, us a step, single against
+// several: FP32 at 1.3 times the work 100000 x 20 65.9 / 48.4, at 2.1 100000 x 12 37.9 /
+// 37.0, at 3.2 200000 x 8 47.8 / 60.5, at 6.4 400000 x 4 41.9 / 102; FP64 at 2.5 400000
+// x 4 114 / 93, at 7.5 100000 x 1 17.1 / 22.1.
+int pick_multi_mc(int precision, int nx, int ny, int tx, int ty, int rows, lbm::MultiShape &shape)
 {
     int best = -1;
     double least = 0.0;
@@ -686,7 +694,10 @@ int pick_multi_mc(int precision, int nx, int ny, lbm::MultiShape &shape)
         }
         if (p->max_tiles > 0) break;
     }
-    return best;
+    const int wide = tx < 64 ? tx : 64, high = ty * rows;
+    const double single = (double)((nx + wide - 1) / wide * wide) * ny * (130.0 + 440.0) +
+                          (double)lbm::multi_tiles({1, tx, high}, nx, ny) * 130.0 * (2 * (tx + 2) + 2 * high);
+    return lbm::multi_tiles(shape, nx, ny) > 512 && least > 2.6 * shape.steps * single ? -1 : best;
 }
 
 hipError_t launch_multi_mc(int precision, int v, const StepMCArgs &a)

@@ -91,8 +91,9 @@ __host__ __device__ inline void mc_ring_cell(int k, int LX, int LY, int &lx, int
 
 hipError_t launch_step_mc(int precision, const StepMCArgs &a);
 // Several steps fin -> fout in one launch (w32 buffers): the variant for a
-// grid and its shape, -1 when there is none; and its launch.
-int pick_multi_mc(int precision, int nx, int ny, lbm::MultiShape &shape);
+// grid and its shape, -1 where single steps with tiles of tx x ty threads and
+// `rows` nodes each are better; and its launch.
+int pick_multi_mc(int precision, int nx, int ny, int tx, int ty, int rows, lbm::MultiShape &shape);
 hipError_t launch_multi_mc(int precision, int v, const StepMCArgs &a);
 
 // Utility launches over the nodes of the run: op 0 = populations [2][9][N]
