@@ -30,6 +30,10 @@ sys.path.insert(0, ROOT)
 METRIC = "MLUPS and % HBM roofline, FP32/batched vs plain FP64, at sigma err <0.5%"
 HBM_PEAK_GBS = 8000.0
 KERNEL_SRC = os.path.join(ROOT, "paper_1306_6445_amd", "csrc", "lbm_multi.hip")
+# headers with code of the step kernels
+KERNEL_HEADERS = [os.path.join(ROOT, "paper_1306_6445_amd", "csrc", n) for n in
+                  ("lbm3d_kernels.hpp", "lbm_device.hpp", "lbm_kernels.hpp", "lbm_mc_kernels.hpp", "lbm_multi.hpp",
+                   "lbm_node.hpp", "lbm_popbuf.hpp")]
 # HBM traffic per dispatch of the dominant kernel, written from rocprofv3 counter runs
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "traffic_%s_%s_%s.json")
 
@@ -597,18 +601,33 @@ def mc_block(lbm, torch, steps=64, n=2048):
     return out
 
 
+def headers_sha256():
+    """Digest of the step kernels' headers, in the order of their names."""
+    h = hashlib.sha256()
+    for path in KERNEL_HEADERS:
+        with open(path, "rb") as fh:
+            h.update(fh.read())
+    return h.hexdigest()
+
+
 def traffic_from_profile(ntot, kernel, workload, precision="fp32", src=None):
     """HBM bytes per launch of the dominant kernel from committed rocprofv3
     counter runs, if they were taken on the current kernel source (src: the
-    kernel's source file, the 2D kernels by default)."""
+    kernel's source file; by default that of the several-step kernels, for the
+    two-kernel schedule's collide kernel that of the single steps) and, where the
+    summary names them, the current headers."""
+    if src is None:
+        src = KERNEL_SRC if kernel != "collide" else os.path.join(os.path.dirname(KERNEL_SRC), "lbm_kernels.hip")
     path = TRAFFIC_FILE % (kernel, precision, workload)
     if not os.path.exists(path):
         return None
     try:
         with open(path) as fh:
             t = json.load(fh)
-        sha = hashlib.sha256(open(src or KERNEL_SRC, "rb").read()).hexdigest()
+        sha = hashlib.sha256(open(src, "rb").read()).hexdigest()
         if t.get("kernel_source_sha256") != sha or t.get("nodes") != ntot:
+            return None
+        if t.get("headers_sha256", headers_sha256()) != headers_sha256():
             return None
         return float(t["bytes_per_dispatch"])
     except Exception:
