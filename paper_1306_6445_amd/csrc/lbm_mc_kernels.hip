@@ -352,10 +352,10 @@ template <typename S, int K, int TX, int TY, int NT, bool WALLS> struct MultiMC 
         } else {
             // LDS cell: unwrapped on a periodic axis, the clamped node's across a wall
             const int cx = WALLS && bcx == lbm::BC_WALL ? gx - x0 : dx, cy = WALLS && bcy == lbm::BC_WALL ? gy - y0 : dy;
-            const int cell = (cy + Gm::M) * Gm::FX + cx + Gm::M;
+            const int cell = Gm::pop(cx, cy);
 #pragma unroll
             for (int a = 0; a < 9; ++a) {
-                const int i = wall(a) ? opp_of(a) * Gm::FN + cell : a * Gm::FN + cell - (ey_of(a) * Gm::FX + ex_of(a));
+                const int i = Gm::pull(a, cell, wall(a));
                 fa[a] = dec<S, C>(pop[i], a, refA);
                 fb[a] = dec<S, C>(pop[9 * Gm::FN + i], a, refB);
             }
@@ -367,7 +367,7 @@ template <typename S, int K, int TX, int TY, int NT, bool WALLS> struct MultiMC 
         da = lbm::node_density<C>(fa);
         db = lbm::node_density<C>(fb);
         bad |= !(da + db > C(0)) || !(da - da == C(0)) || !(db - db == C(0));
-        const int cell = (dy + Gm::M + 1) * Gm::PX + dx + Gm::M + 1;
+        const int cell = Gm::psi(dx, dy);
         la[cell] = da;
         lb[cell] = db;
     }

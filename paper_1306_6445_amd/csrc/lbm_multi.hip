@@ -64,22 +64,14 @@ struct MultiTile {
             return r;
         }
     }
-    __device__ __forceinline__ static int wcell(int dx, int dy) { return (dy + Gm::M + 2) * Gm::RX + dx + Gm::M + 2; }
     // base density of f_a of the item's node: its writer's (x - e_a, or x across a wall), or the run's constant
     template <int A> __device__ __forceinline__ C base_of(int wc, bool wall) const
     {
         if constexpr (kWriterRef<S>)
-            return C(wr[wall ? wc : wc - (ey_of(A) * Gm::RX + ex_of(A))]);
+            return C(wr[Gm::writer(A, wc, wall)]);
         else
             return k.rho_ref;
     }
-    template <int A> struct Up {
-        static __device__ __forceinline__ bool wall(const bool *w) // wxm, wxp, wym, wyp
-        {
-            constexpr int ex = ex_of(A), ey = ey_of(A);
-            return (ex > 0 && w[0]) || (ex < 0 && w[1]) || (ey > 0 && w[2]) || (ey < 0 && w[3]);
-        }
-    };
     // the node an item stands for: wrapped on periodic axes (global), clamped across walls
     __device__ __forceinline__ int wrap_x(int x) const { return MODE == kMInner ? x : psi_coord(x, nx, MODE == kMPeriodic ? BC_PERIODIC : bcx); }
     __device__ __forceinline__ int wrap_y(int y) const { return MODE == kMInner ? y : psi_coord(y, ny, MODE == kMPeriodic ? BC_PERIODIC : bcy); }
@@ -92,7 +84,7 @@ struct MultiTile {
         C *f;
         template <int A> __device__ __forceinline__ void operator()()
         {
-            const bool wall = MODE == kMGeneral && kWriterRef<S> && Up<A>::wall(w);
+            const bool wall = MODE == kMGeneral && kWriterRef<S> && multi_wall<A>(w);
             f[A] = t.template decode<A>(t.in.load(off, A * t.ds), t.template base_of<A>(wc, wall));
         }
     };
@@ -104,10 +96,8 @@ struct MultiTile {
         C *f;
         template <int A> __device__ __forceinline__ void operator()()
         {
-            constexpr int ex = ex_of(A), ey = ey_of(A);
-            const bool wall = MODE == kMGeneral && Up<A>::wall(w);
-            const int i = wall ? opp_of(A) * Gm::FN + cell : A * Gm::FN + cell - (ey * Gm::FX + ex);
-            f[A] = t.template decode<A>(t.pop[i], t.template base_of<A>(wc, wall));
+            const bool wall = MODE == kMGeneral && multi_wall<A>(w);
+            f[A] = t.template decode<A>(t.pop[Gm::pull(A, cell, wall)], t.template base_of<A>(wc, wall));
         }
     };
     struct StoreL {
@@ -154,7 +144,7 @@ struct MultiTile {
             if (bcx == BC_WALL) cx = gx - x0, w[0] = gx == 0, w[1] = gx == nx - 1;
             if (bcy == BC_WALL) cy = gy - y0, w[2] = gy == 0, w[3] = gy == ny - 1;
         }
-        const int wc = wcell(cx, cy);
+        const int wc = Gm::wr(cx, cy);
         if constexpr (s == 1) {
             LoadG op{*this, (uint32_t)(gy * ld + gx) * (uint32_t)sizeof(S), wc, {w[0], w[1], w[2], w[3]}, f};
             for9(op);
@@ -168,7 +158,7 @@ struct MultiTile {
     {
         C ps, rho;
         bad |= !node_psi<C>(k, eos, f, ps, rho);
-        psi[(dy + Gm::M + 1) * Gm::PX + dx + Gm::M + 1] = ps;
+        psi[Gm::psi(dx, dy)] = ps;
         return rho;
     }
 
@@ -212,7 +202,7 @@ struct MultiTile {
                     hb = fmix32((uint32_t)gi ^ fmix32(seed + (s - 1)));
                 }
                 if constexpr (s < K) {
-                    if constexpr (kWriterRef<S>) wr[wcell(dx, dy)] = (float)rho[j];
+                    if constexpr (kWriterRef<S>) wr[Gm::wr(dx, dy)] = (float)rho[j];
                     StoreL op{*this, (dy + Gm::M) * Gm::FX + dx + Gm::M, fs, base, hb};
                     for9(op);
                 } else {
@@ -323,9 +313,7 @@ __global__ void __launch_bounds__(NT) multi_kernel(const RunDev *__restrict__ ru
 // four steps a few.
 template <typename S, int K, int W, int TY, int NT> struct StripTile {
     using C = typename Store<S>::C;
-    static constexpr int M = 2 * (K - 1), FN = W * (TY + 2 * M);  // LDS populations
-    static constexpr int PX = W + 2, PN = PX * (TY + 2 * M + 2);  // LDS psi
-    static constexpr int cells(int s) { return W * (TY + 4 * (K - s)); }
+    using Gm = StripGeom<K, W, TY>;
     const RunPar<C> k;
     const int eos, nx, ny, ld, bcy, y0;
     const uint32_t ds; // bytes from one direction's array to the next
@@ -333,8 +321,6 @@ template <typename S, int K, int W, int TY, int NT> struct StripTile {
     C *psi;
     S *pop;
     bool bad = false;
-
-    static __device__ __forceinline__ int pcell(int x, int dy) { return (dy + M + 1) * PX + x + 1; }
 
     template <int A> __device__ __forceinline__ C decode(S v) const { return Store<S>::template load<A>(&v, 0, k.rho_ref); }
 
@@ -352,10 +338,8 @@ template <typename S, int K, int W, int TY, int NT> struct StripTile {
         C *f;
         template <int A> __device__ __forceinline__ void operator()()
         {
-            constexpr int ex = ex_of(A), ey = ey_of(A);
-            const bool wall = (ey > 0 && wym) || (ey < 0 && wyp);
-            const int i = wall ? opp_of(A) * FN + row + xs[1] : A * FN + row - ey * W + xs[1 - ex];
-            f[A] = t.template decode<A>(t.pop[i]);
+            const bool wall = (ey_of(A) > 0 && wym) || (ey_of(A) < 0 && wyp);
+            f[A] = t.template decode<A>(t.pop[Gm::pull(A, xs, row, wall)]);
         }
     };
     struct StoreL {
@@ -364,7 +348,7 @@ template <typename S, int K, int W, int TY, int NT> struct StripTile {
         const C *f;
         template <int A> __device__ __forceinline__ void operator()()
         {
-            Store<S>::template store<A>(t.pop, A * FN + cell, f[A], t.k.rho_ref);
+            Store<S>::template store<A>(t.pop, A * Gm::FN + cell, f[A], t.k.rho_ref);
         }
     };
     // f*_a(x) to slot a of x + e_a, or slot opp(a) of x across a wall (the even-state layout)
@@ -392,43 +376,41 @@ template <typename S, int K, int W, int TY, int NT> struct StripTile {
         } else {
             // LDS row: unwrapped on a periodic axis, the clamped node's across a wall
             const bool wall = bcy == BC_WALL;
-            const int cy = wall ? gy - y0 : dy;
-            LoadL op{*this, (cy + M) * W, {x == 0 ? nx - 1 : x - 1, x, x == nx - 1 ? 0 : x + 1},
+            LoadL op{*this, Gm::pop(0, wall ? gy - y0 : dy), {x == 0 ? nx - 1 : x - 1, x, x == nx - 1 ? 0 : x + 1},
                      wall && gy == 0, wall && gy == ny - 1, f};
             for9(op);
         }
         C ps, rho;
         bad |= !node_psi<C>(k, eos, f, ps, rho);
-        psi[pcell(x, dy)] = ps;
-        if (x == 0) psi[pcell(nx, dy)] = ps;
-        if (x == nx - 1) psi[pcell(-1, dy)] = ps;
+        psi[Gm::psi(x, dy)] = ps;
+        if (x == 0) psi[Gm::psi(nx, dy)] = ps;
+        if (x == nx - 1) psi[Gm::psi(-1, dy)] = ps;
         return rho;
     }
 
     template <int s> __device__ __forceinline__ void step(int tid)
     {
-        constexpr int N = cells(s), NI = N + 2 * W, R = (N + NT - 1) / NT, m = 2 * (K - s);
+        constexpr int N = Gm::cells(s), NI = N + 2 * W, R = (N + NT - 1) / NT;
         C fv[R][9], rho[R];
 #pragma unroll
         for (int j = 0; j < R; ++j) {
             const int i = tid + j * NT, x = i % W;
             // past the cells come the ring rows; an item of them needs no populations later
-            const int dy = i < N ? i / W - m : (i < N + W ? -1 - m : TY + m);
-            if (i < NI && x < nx) rho[j] = density<s>(x, dy, fv[j]);
+            if (i < NI && x < nx) rho[j] = density<s>(x, Gm::item_row(s, i), fv[j]);
         }
         for (int i = tid + R * NT; i < NI; i += NT) {
             C fr[9];
-            if (i % W < nx) density<s>(i % W, i < N + W ? -1 - m : TY + m, fr);
+            if (i % W < nx) density<s>(i % W, Gm::item_row(s, i), fr);
         }
         __syncthreads();
 #pragma unroll
         for (int j = 0; j < R; ++j) {
-            const int i = tid + j * NT, x = i % W, dy = i / W - m;
+            const int i = tid + j * NT, x = i % W, dy = i / W - 2 * (K - s);
             if (i < N && x < nx) {
                 C fs[9];
-                collide_node<C>(k, fv[j], rho[j], psi + pcell(x, dy), PX, fs);
+                collide_node<C>(k, fv[j], rho[j], psi + Gm::psi(x, dy), Gm::PX, fs);
                 if constexpr (s < K) {
-                    StoreL op{*this, (dy + M) * W + x, fs};
+                    StoreL op{*this, Gm::pop(x, dy), fs};
                     for9(op);
                 } else if (y0 + dy < ny) {
                     constexpr uint32_t z = sizeof(S);
@@ -455,8 +437,8 @@ __global__ void __launch_bounds__(NT) strip_kernel(const RunDev *__restrict__ ru
     static_assert(!kWriterRef<S>, "FP64 and FP32 storage");
     using C = typename Store<S>::C;
     using T = StripTile<S, K, W, TY, NT>;
-    __shared__ C psi[T::PN];
-    __shared__ S pop[9 * T::FN];
+    __shared__ C psi[T::Gm::PN];
+    __shared__ S pop[9 * T::Gm::FN];
     const int wi = work_index(xcd);
     const Tile t = ntx > 0 ? Tile{0, 0, wi * TY, 0} : tiles[wi];
     const RunDev &r = runs[t.run];
