@@ -8,10 +8,11 @@
 // fit a cache, and costs a launch and a chain of dependent loads, which
 // bounded the small ones.  Step s of the K collides the tile and a margin of
 // 2 (K - s) nodes, for which it needs psi one node further out, so the margin's
-// work is done again by the neighbouring tiles: 1.14 collisions and 1.29
-// densities per node and step for 64 x 16 tiles and K = 2.  HBM traffic halves
-// (82 B per node and 2 steps in FP32 by the counters) and the kernel is bound by
-// vector instruction issue: 380 a node and step, the vector units 93% busy.
+// work is done again by the neighbouring tiles: for K = 2 1.16 collisions and 1.33
+// densities per node and step with 64 x 16 tiles, 1.12 and 1.25 with 60 x 24.  HBM
+// traffic halves (FP32, by the counters: 72 B per node and 2 steps on 40 grids of
+// 256^2, 83 on 4096 x 2048) and the kernel is bound by vector instruction issue: 404
+// and 371 a node and step there.
 // The intermediate state passes through LDS in its storage form (FP32
 // deviations; bf16 with its writer densities and rounding bits), so that K steps
 // in one launch and K launches give the same bits.
@@ -500,7 +501,8 @@ template <typename S, int K, int W, int TY, int NT> constexpr Variant make_strip
 // K = 2 4.6 instead of 3.75 for 256; 4 x 64 and 8 x 64 lose 10-25% on heights
 // that they do not divide).
 // Threads of a tile are a multiple of 256 (four waves, one per SIMD: 576 ran 20%
-// slower than 512), and the first step's cells fill them in one or two rounds.
+// slower than 512), and the first step's cells fill them in one or two rounds,
+// those of 60 x 24 (1,792 on 768 threads) in two and a third.
 //  - K = 4 tiles for few nodes, where a step is the launch and one chain of
 //    latencies: the smaller the tile the shorter the chain, as long as each
 //    tile has a CU of its own, 256 of them (FP32, us a step: 180^2 2.23 with 12 x

@@ -65,7 +65,7 @@ __device__ __forceinline__ void load_inputs(Smem &S, const float *__restrict__ x
     if (i < CH * IN) S.x[i] = s0 + i / IN < n ? x[s0 * IN + i] : 0.0f;
 }
 
-// out[j] = tanh(b[j] + sum_k W2[j][k] in[k]) for the wave's two samples.
+// z = b2[j] + sum_k W2[j][k] in[k] for the wave's two samples (before the tanh).
 __device__ __forceinline__ void hidden2(const Smem &S, const float *in0, const float *in1, int j, float &z0, float &z1)
 {
     z0 = z1 = S.b2[j];

@@ -628,8 +628,8 @@ def mc_args(run):
 
 class LatticeMC:
     """One two-component (binary mixture) run on the GPU (include/lbm_mc.h):
-    FP64 or FP32 storage, two or four steps per launch (one from an odd step
-    count or for a remainder).  Fields are [ny][nx];
+    FP64 or FP32 storage, two or four steps per launch (one for a remainder and
+    on long flat grids).  Fields are [ny][nx];
     populations [2][9][ny][nx] (component A first)."""
 
     def __init__(self, run, precision: str = "fp32", device: str = "cuda"):
