@@ -58,3 +58,12 @@ def test_every_header_of_the_step_kernels_is_hashed():
                 seen.add(name)
                 todo.append(name)
     assert seen == hashed
+
+
+def test_committed_summaries_name_both_digests():
+    names = [n for n in os.listdir(os.path.join(ROOT, "profiles")) if n.startswith("traffic_") and n.endswith(".json")]
+    assert names
+    for name in names:
+        with open(os.path.join(ROOT, "profiles", name)) as fh:
+            t = json.load(fh)
+        assert len(t["kernel_source_sha256"]) == 64 and len(t["headers_sha256"]) == 64, name
